@@ -19,7 +19,7 @@ LIB = os.path.join(OUT_DIR, "libmifvm.so")
 ARCH = "gfx950"
 
 HIP_SOURCES = ["api.hip", "nn_api.hip", "fv_kernels.hip", "solve_kernels.hip", "ir_kernels.hip",
-               "nn_kernels.hip", "mf_kernels.hip", "gmres_kernels.hip", "streamer_kernels.hip",
+               "nn_kernels.hip", "mf_kernels.hip", "cg_iter.hip", "gmres_kernels.hip", "streamer_kernels.hip",
                "amg_kernels.hip", "amg_api.hip", "noalloc.hip", "batch_kernels.hip",
                "batch_api.hip"]
 CXX_SOURCES = ["mesh.cpp", "amg.cpp"]

@@ -16,6 +16,7 @@
 
 #include "../../include/mifvm.h"
 #include "api_util.h"
+#include "cg_iter.h"
 #include "gmres.h"
 #include "mesh.h"
 #include "nn.h"
@@ -163,6 +164,16 @@ size_t layout(const Mesh& m, char* base, Dev& d) {
     const int64_t nblk = (nc + 63) / 64;
     d.partial = carve<double>(base, off, 8 * (nblk + 1024));
     d.nm = int32_t(m.mesh_start.size() - 1);
+    const CgPlan cg = cg_plan(m);
+    d.cg_rows = cg.rows;
+    d.cg_threads = cg.threads;
+    d.cg_nblk = cg.nblk;
+    d.cg_vblk = cg.vblk;
+    // the stored product has at most 4 * threads partials of its own
+    d.cg_stride = std::max<int64_t>(cg.nblk, 4 * cg.threads);
+    d.cg_blk = carve<int4>(base, off, cg.cells.size());
+    d.cg_vert = carve<int4>(base, off, cg.vertices.size());
+    d.cg_parts = carve<int2>(base, off, cg.parts.size());
     d.mesh_start = carve<int64_t>(base, off, m.mesh_start.size());
     d.mesh_D = carve<double>(base, off, d.nm);
     d.mesh_dt = carve<double>(base, off, d.nm);
@@ -192,19 +203,49 @@ void drop_graphs(State& s) {
 using namespace mifvm;
 
 namespace {
-// one chunk of n CG iterations (plain FP64, matrix-free or stored K, or FP32
-// inner), no timing events
-hipError_t enqueue_cg_chunk(const State& s, int method, int n, hipStream_t q) {
+// whether a CG runs as the three-kernel iteration (cg_iter.hip): matrix-free
+// unless meshes share a vertex, on the stored matrix for a single mesh (a
+// tile of rows may straddle two)
+bool three_kernel_cg(const State& s) { return s.mf ? s.cg_split : s.d.nm == 1; }
+
+// one CG iteration (plain FP64 or FP32 inner, matrix-free or stored K), its
+// launches timed when timing is on
+hipError_t cg_iteration(State& s, int method, hipStream_t q) {
     const Dev& d = s.d;
-    for (int c = 0; c < n; ++c) {
-        hipError_t e = method == MIFVM_SOLVE_PLAIN
-                           ? (s.mf ? launch_mf_cg_spmv(d, s.bc[1], q) : launch_cg_spmv(d, q))
-                           : (s.mf ? launch_mf_cg32_spmv(d, s.bc[1], q) : launch_cg32_spmv(d, q));
-        if (e == hipSuccess) e = method == MIFVM_SOLVE_PLAIN ? launch_cg_axpy(d, q) : launch_cg32_axpy(d, q);
-        if (e == hipSuccess) e = method == MIFVM_SOLVE_PLAIN ? launch_cg_dir(d, q) : launch_cg32_dir(d, q);
-        if (e != hipSuccess) return e;
+    const bool f32 = method != MIFVM_SOLVE_PLAIN;
+    auto run = [&](int kid, auto fn) { return timed(s.timer, kid, q, fn); };
+    hipError_t e = hipSuccess;
+    if (three_kernel_cg(s)) {
+        const int kid[kCgParts] = {s.mf ? MIFVM_K_MF_GATHER : MIFVM_K_CG_SPMV, MIFVM_K_CG_AXPY, MIFVM_K_CG_DIR};
+        for (int part = 0; part < kCgParts && e == hipSuccess; ++part)
+            e = run(kid[part], [&] { return launch_cg_part(d, f32, !s.mf, part, q); });
+        return e;
     }
-    return hipSuccess;
+    if (s.mf) {
+        const int kid[kMfParts] = {MIFVM_K_MF_VERTEX, MIFVM_K_MF_GATHER, MIFVM_K_CG_ALPHA};
+        for (int part = 0; part < kMfParts && e == hipSuccess; ++part)
+            e = run(kid[part], [&] {
+                return f32 ? launch_mf_cg32_part(d, s.bc[1], part, q) : launch_mf_cg_part(d, s.bc[1], part, q);
+            });
+    } else {
+        e = run(MIFVM_K_CG_SPMV, [&] { return f32 ? launch_cg32_spmv(d, q) : launch_cg_spmv(d, q); });
+    }
+    if (e == hipSuccess) e = run(MIFVM_K_CG_AXPY, [&] { return f32 ? launch_cg32_axpy(d, q) : launch_cg_axpy(d, q); });
+    if (e == hipSuccess) e = run(MIFVM_K_CG_DIR, [&] { return f32 ? launch_cg32_dir(d, q) : launch_cg_dir(d, q); });
+    return e;
+}
+
+// n CG iterations, and the scalars the host reads after them
+hipError_t enqueue_cg_chunk(State& s, int method, int n, hipStream_t q) {
+    hipError_t e = hipSuccess;
+    for (int c = 0; c < n && e == hipSuccess; ++c) e = cg_iteration(s, method, q);
+    if (e == hipSuccess && three_kernel_cg(s)) e = launch_cg_commit(s.d, q);
+    return e;
+}
+
+// what a matrix-free loop needs once it is opened: the vertex values of p
+hipError_t cg_opened(State& s, int method, hipStream_t q) {
+    return s.mf && three_kernel_cg(s) ? launch_cg_open_vertices(s.d, method != MIFVM_SOLVE_PLAIN, q) : hipSuccess;
 }
 }  // namespace
 
@@ -365,6 +406,18 @@ int mifvm_state_create(const mifvm_mesh* mesh, const mifvm_params* params, void*
     UP(d.cell_perm, m.cell_perm); UP(d.vert_perm, m.vert_perm);
     UP(d.h_off, m.h_off); UP(d.h_idx, m.h_idx); UP(d.h_self, m.h_self);
     UP(d.mesh_start, m.mesh_start);
+    {
+        const CgPlan cg = cg_plan(m);
+        st.cg_split = cg_meshes_apart(m);
+        auto table = [&](void* dst, const void* src, size_t bytes) {
+            return bytes ? hipMemcpyAsync(dst, src, bytes, hipMemcpyHostToDevice, s) : hipSuccess;
+        };
+        e = table(d.cg_blk, cg.cells.data(), cg.cells.size() * sizeof(CgPlan::Item));
+        if (e == hipSuccess) e = table(d.cg_vert, cg.vertices.data(), cg.vertices.size() * sizeof(CgPlan::Item));
+        if (e == hipSuccess) e = table(d.cg_parts, cg.parts.data(), cg.parts.size() * sizeof(CgPlan::Range));
+        if (e == hipSuccess) e = hipStreamSynchronize(s);  // the tables are freed at scope exit
+        if (e != hipSuccess) return cleanup(hip_fail(e, "upload CG blocks"));
+    }
     {
         const std::vector<double> Dm(d.nm, st.diffusivity), zero(d.nm, 0.0);
         UP(d.mesh_D, Dm);
@@ -967,35 +1020,13 @@ int solve_impl(mifvm_state* st, const double* d_f, const double* f_internal, con
         s.cg_exec_chunk = chunk;
         s.cg_exec_method = graph_key;
     }
-    // one chunk of iterations: a graph replay, or timed direct launches
+    // one chunk of iterations: a graph replay, or direct launches
     auto run_chunk = [&]() -> int {
         if (use_graph) {
             HIPCHK(hipGraphLaunch(s.cg_exec, hs));
             return MIFVM_OK;
         }
-        for (int c = 0; c < chunk; ++c) {
-            if (run_method == MIFVM_SOLVE_PLAIN) {
-                if (matrix_free) {
-                    for (int part = 0; part < kMfParts; ++part)
-                        HIPCHK(timed(tm, (part == 0 ? MIFVM_K_MF_VERTEX : part == 1 ? MIFVM_K_MF_GATHER : MIFVM_K_CG_ALPHA), hs,
-                                     [&] { return launch_mf_cg_part(d, s.bc[1], part, hs); }));
-                } else {
-                    HIPCHK(timed(tm, MIFVM_K_CG_SPMV, hs, [&] { return launch_cg_spmv(d, hs); }));
-                }
-                HIPCHK(timed(tm, MIFVM_K_CG_AXPY, hs, [&] { return launch_cg_axpy(d, hs); }));
-                HIPCHK(timed(tm, MIFVM_K_CG_DIR, hs, [&] { return launch_cg_dir(d, hs); }));
-            } else if (matrix_free) {
-                for (int part = 0; part < kMfParts; ++part)
-                    HIPCHK(timed(tm, (part == 0 ? MIFVM_K_MF_VERTEX : part == 1 ? MIFVM_K_MF_GATHER : MIFVM_K_CG_ALPHA), hs,
-                                 [&] { return launch_mf_cg32_part(d, s.bc[1], part, hs); }));
-                HIPCHK(timed(tm, MIFVM_K_CG_AXPY, hs, [&] { return launch_cg32_axpy(d, hs); }));
-                HIPCHK(timed(tm, MIFVM_K_CG_DIR, hs, [&] { return launch_cg32_dir(d, hs); }));
-            } else {
-                HIPCHK(timed(tm, MIFVM_K_CG_SPMV, hs, [&] { return launch_cg32_spmv(d, hs); }));
-                HIPCHK(timed(tm, MIFVM_K_CG_AXPY, hs, [&] { return launch_cg32_axpy(d, hs); }));
-                HIPCHK(timed(tm, MIFVM_K_CG_DIR, hs, [&] { return launch_cg32_dir(d, hs); }));
-            }
-        }
+        HIPCHK(enqueue_cg_chunk(s, run_method, chunk, hs));
         return MIFVM_OK;
     };
     int restarts = learned.restarts, outer = 0;
@@ -1058,7 +1089,8 @@ int solve_impl(mifvm_state* st, const double* d_f, const double* f_internal, con
                 hipError_t e = launch_mf_apply(d, s.bc[1], d.x, d.tmp, hs);
                 if (e != hipSuccess) return e;
             }
-            return launch_cg_setup(d, tol, limit, restart, fresh, hs, matrix_free ? d.tmp : nullptr);
+            hipError_t e = launch_cg_setup(d, tol, limit, restart, fresh, hs, matrix_free ? d.tmp : nullptr);
+            return e == hipSuccess ? cg_opened(s, run_method, hs) : e;
         };
         HIPCHK(timed(tm, MIFVM_K_CG_SETUP, hs, [&] { return setup(budget, true); }));
         if ((rc = pull())) return rc;
@@ -1085,7 +1117,9 @@ int solve_impl(mifvm_state* st, const double* d_f, const double* f_internal, con
                     hipError_t e = launch_mf_apply(d, s.bc[1], d.x, d.tmp, hs);
                     if (e != hipSuccess) return e;
                 }
-                return launch_ir_residual(d, tol, tol_in, maxit, restart, fresh, matrix_free ? d.tmp : nullptr, hs);
+                hipError_t e =
+                    launch_ir_residual(d, tol, tol_in, maxit, restart, fresh, matrix_free ? d.tmp : nullptr, hs);
+                return e == hipSuccess ? cg_opened(s, run_method, hs) : e;
             }));
             fresh = false;
             if ((rc = pull())) return rc;

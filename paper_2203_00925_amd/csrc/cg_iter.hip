@@ -1,0 +1,470 @@
+// One iteration of Jacobi-preconditioned CG in three kernels, matrix-free in
+// FP64 or FP32 (the inner solve of the refined form):
+//   k_cg_product   q = K p from the cells' tables and the vertex values of
+//                  p; partial p.q;
+//   k_cg_residual  alpha = rz / p.q (every block adds the partials), r -=
+//                  alpha q, z = D^-1 r; partial rz, rr;
+//   k_cg_direction beta and the convergence tests (every block), x += alpha
+//                  p, p = z + beta p; its first blocks update the vertex
+//                  values of p by the same recurrence, A p = A z + beta A p
+//                  with A z summed over the vertex lists.
+// On the stored matrix (one mesh) the product is k_cg_product_stored and
+// there are no vertex values.
+//
+// Why three: the iteration is a chain of dependent kernels, each at least
+// 1.6 us from the launch before it plus its own latency chain, so on small
+// meshes their number is the time.  The vertex values need beta only for the
+// recurrence, not for the gathers, so they share a launch with the direction;
+// alpha and beta are formed by whoever needs them instead of in kernels of
+// one block.  No block reads a scalar that another block of the same kernel
+// writes: k_cg_direction leaves the new scalars in the SC_N_* slots and the
+// next product (or k_cg_commit, after a chunk's last iteration) copies them.
+#include <algorithm>
+
+#include "cg_iter.h"
+#include "halo_stage.h"
+#include "mf_cell.h"
+#include "reduce.h"
+#include "seg.h"
+#include "state.h"
+#include "xcd.h"
+
+namespace mifvm {
+namespace {
+
+constexpr int kMaxWaves = 8;              // 512 threads
+
+template <class R> struct CgVec;
+template <> struct CgVec<double> {
+    __device__ static double *x(const Dev& d) { return d.x; }
+    __device__ static double *r(const Dev& d) { return d.r; }
+    __device__ static double *z(const Dev& d) { return d.z; }
+    __device__ static double *p(const Dev& d) { return d.p; }
+    __device__ static double *q(const Dev& d) { return d.q; }
+    __device__ static const double *dinv(const Dev& d) { return d.k_dinv; }
+    __device__ static const double *diag(const Dev& d) { return d.k_diag; }
+    __device__ static const double *val(const Dev& d) { return d.k_val; }
+    __device__ static const double *alpha(const Dev& d) { return d.n_alpha; }
+};
+template <> struct CgVec<float> {
+    __device__ static float *x(const Dev& d) { return d.d32; }
+    __device__ static float *r(const Dev& d) { return d.r32; }
+    __device__ static float *z(const Dev& d) { return d.z32; }
+    __device__ static float *p(const Dev& d) { return d.p32; }
+    __device__ static float *q(const Dev& d) { return d.q32; }
+    __device__ static const float *dinv(const Dev& d) { return d.k_dinv32; }
+    __device__ static const float *diag(const Dev& d) { return d.k_diag32; }
+    __device__ static const float *val(const Dev& d) { return d.k_val32; }
+    __device__ static const float *alpha(const Dev& d) { return d.n_alpha32; }
+};
+
+// a block's rows, its mesh's scalars and partials
+struct Seg {
+    int64_t r0, r1;
+    double* sc;
+    int p0, np;
+    bool lead;                            // the mesh's first block
+};
+
+__device__ inline Seg cg_seg(const Dev& d, int64_t lb) {
+    if (d.nm == 1) {
+        const int64_t r0 = lb * d.cg_rows, r1 = r0 + d.cg_rows;
+        return {r0, r1 < d.nc ? r1 : d.nc, d.scal, 0, d.cg_nblk, lb == 0};
+    }
+    const int4 t = d.cg_blk[lb];
+    const int2 pr = d.cg_parts[t.x];
+    return {t.y, t.z, msc(d, t.x), pr.x, pr.y, lb == pr.x};
+}
+
+// Sum of K values over the block, in a fixed order; valid in every thread.
+// `lds`: K * kMaxWaves doubles, not in use by an earlier call.
+template <int K>
+__device__ inline void block_sums(double (&v)[K], double* lds) {
+    const int w = threadIdx.x >> 6, nw = blockDim.x >> 6;
+#pragma unroll
+    for (int k = 0; k < K; ++k) v[k] = wave_sum(v[k]);
+    if ((threadIdx.x & 63) == 0) {
+#pragma unroll
+        for (int k = 0; k < K; ++k) lds[k * kMaxWaves + w] = v[k];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        v[k] = lds[k * kMaxWaves];
+        for (int j = 1; j < nw; ++j) v[k] += lds[k * kMaxWaves + j];
+    }
+}
+
+// The K sums of a mesh's partials (part[k * stride + b]),
+// added by every block of a kernel: a thread's four loads go out together
+// (np is at most four times the block).
+template <int K>
+__device__ inline void sum_parts(const double* __restrict__ part, int64_t stride, int np, double* lds,
+                                 double (&out)[K]) {
+    const int T = blockDim.x;
+    double v[K][4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const int b = int(threadIdx.x) + j * T;
+        const bool in = b < np;
+#pragma unroll
+        for (int k = 0; k < K; ++k) v[k][j] = in ? part[k * stride + b] : 0.0;
+    }
+#pragma unroll
+    for (int k = 0; k < K; ++k) out[k] = (v[k][0] + v[k][1]) + (v[k][2] + v[k][3]);
+    block_sums<K>(out, lds);
+}
+
+// the scalars the last direction kernel left for the next iteration
+__device__ inline void commit(double* sc) {
+    sc[SC_RZ] = sc[SC_N_RZ];
+    sc[SC_RR] = sc[SC_N_RR];
+    sc[SC_IT] = sc[SC_N_IT];
+    sc[SC_SINCE] = sc[SC_N_SINCE];
+    sc[SC_DONE] = sc[SC_N_DONE];
+}
+
+__global__ __launch_bounds__(256) void k_cg_commit(Dev d) {
+    const int m = int(blockIdx.x) * 256 + threadIdx.x;
+    if (m < d.nm) commit(msc(d, m));
+}
+
+// q = K p row by row; partial p.q
+template <class R>
+__global__ __launch_bounds__(512) void k_cg_product(Dev d) {
+    __shared__ double lds[kMaxWaves];
+    const int64_t lb = xcd_block();
+    if (lb >= d.cg_nblk) return;
+    const Seg s = cg_seg(d, lb);
+    if (s.lead && threadIdx.x == 0) commit(s.sc);
+    if (s.sc[SC_N_DONE] != 0.0) return;
+    const R* __restrict__ p = CgVec<R>::p(d);
+    const R* __restrict__ pv = reinterpret_cast<const R*>(d.mf_xv);
+    R* __restrict__ q = CgVec<R>::q(d);
+    double v[1] = {0.0};
+    for (int64_t i = s.r0 + threadIdx.x; i < s.r1; i += blockDim.x) {
+        const R y = cell_row(d, p, pv, i);
+        q[i] = y;
+        v[0] += double(p[i]) * double(y);
+    }
+    block_sums<1>(v, lds);
+    if (threadIdx.x == 0) d.partial[lb] = v[0];
+}
+
+// The same on the stored matrix (one mesh): a block takes `tiles` consecutive
+// cell tiles, each tile's halo of p staged in LDS and addressed by 16-bit
+// local indices; the entries of a row in stored order.
+template <class R>
+__global__ __launch_bounds__(kBlock) void k_cg_product_stored(Dev d, int tiles) {
+    extern __shared__ __align__(16) unsigned char sp_raw[];
+    __shared__ double lds[kMaxWaves];
+    R* sp = reinterpret_cast<R*>(sp_raw);
+    double* sc = d.scal;
+    if (blockIdx.x == 0 && threadIdx.x == 0) commit(sc);
+    if (sc[SC_N_DONE] != 0.0) return;
+    const R* __restrict__ val = CgVec<R>::val(d);
+    const R* __restrict__ diag = CgVec<R>::diag(d);
+    R* __restrict__ q = CgVec<R>::q(d);
+    const int T = blockDim.x;
+    double v[1] = {0.0};
+    const int64_t t0 = int64_t(blockIdx.x) * tiles, t1 = t0 + tiles < d.ntiles ? t0 + tiles : d.ntiles;
+    for (int64_t t = t0; t < t1; ++t) {
+        if (t != t0) __syncthreads();                     // the last tile's readers
+        stage_halo_values(d, t, CgVec<R>::p(d), sp);
+        __syncthreads();
+        const int64_t i = t * T + threadIdx.x;
+        if (i < d.nc) {
+            const R pi = sp[d.h_self[t] + threadIdx.x];
+            const int64_t s = i >> 6;
+            const int64_t base = d.k_off[s] + (i & 63);
+            const int w = d.k_w[s];
+            R y = diag[i] * pi;
+            // 16 entries' loads in flight, then their sums in row order
+            for (int k0 = 0; k0 < w; k0 += 16) {
+                uint16_t l[16];
+                R a[16];
+#pragma unroll
+                for (int j = 0; j < 16; ++j) {
+                    const bool in = k0 + j < w;
+                    const int64_t at = base + int64_t(k0 + j) * 64;
+                    l[j] = in ? d.k_lidx[at] : uint16_t(0);
+                    a[j] = in ? val[at] : R(0);
+                }
+#pragma unroll
+                for (int j = 0; j < 16; ++j)
+                    if (k0 + j < w) y += a[j] * sp[l[j]];   // w is one slice's: uniform over the wave
+            }
+            q[i] = y;
+            v[0] += double(pi) * double(y);
+        }
+    }
+    block_sums<1>(v, lds);
+    if (threadIdx.x == 0) d.partial[blockIdx.x] = v[0];
+}
+
+// alpha; r -= alpha q; z = D^-1 r; partial rz, rr.  np: the product's partials
+// of a single mesh (its blocks may differ from this kernel's).
+template <class R>
+__global__ __launch_bounds__(512) void k_cg_residual(Dev d, int np) {
+    __shared__ double lds[3 * kMaxWaves];
+    const int64_t lb = xcd_block();
+    if (lb >= d.cg_nblk) return;
+    const Seg s = cg_seg(d, lb);
+    const R* __restrict__ q = CgVec<R>::q(d);
+    const R* __restrict__ dinv = CgVec<R>::dinv(d);
+    R* __restrict__ r = CgVec<R>::r(d);
+    R* __restrict__ z = CgVec<R>::z(d);
+    const int T = blockDim.x;
+    // the first row's loads go out before the scalars are known
+    int64_t i = s.r0 + threadIdx.x;
+    const int64_t last = s.r1 - 1;
+    int64_t c = i < last ? i : last;
+    R ri = r[c], qi = q[c], di = dinv[c];
+    if (s.sc[SC_DONE] != 0.0) return;
+    double pq[1];
+    sum_parts<1>(d.partial + s.p0, 0, d.nm == 1 ? np : s.np, lds, pq);
+    const double alpha = s.sc[SC_RZ] / pq[0];
+    if (s.lead && threadIdx.x == 0) {
+        s.sc[SC_PQ] = pq[0];
+        s.sc[SC_ALPHA] = alpha;
+    }
+    const R a = R(alpha);
+    double v[2] = {0.0, 0.0};
+    for (; i < s.r1; i += T) {
+        const int64_t n = i + T;
+        c = n < last ? n : last;
+        const R rn = r[c], qn = q[c], dn = dinv[c];    // the next row's, in flight
+        const R rc = ri - a * qi;
+        const R zc = di * rc;
+        r[i] = rc;
+        z[i] = zc;
+        v[0] += double(rc) * double(zc);
+        v[1] += double(rc) * double(rc);
+        ri = rn;
+        qi = qn;
+        di = dn;
+    }
+    block_sums<2>(v, lds + kMaxWaves);
+    if (threadIdx.x == 0) {
+        double* __restrict__ out = d.partial + d.cg_stride;
+        out[lb] = v[0];
+        out[d.cg_stride + lb] = v[1];
+    }
+}
+
+// The vertex value A z of one vertex, summed by kCgVertexLanes neighbouring
+// lanes: lane q takes the entries q, q + 4, ..., up to 6 at a time (an
+// interior vertex of the 6-tetrahedra cube has 24 cells, one round).  With
+// one lane per vertex (24 loads, then 24 gathers a lane) a small mesh has
+// too few wavefronts to cover the chain: 5.9 us at 9,261 vertices.
+template <class R>
+__device__ inline R vertex_sum(const Dev& d, const R* __restrict__ z, int64_t v, int q) {
+    constexpr int L = kCgVertexLanes, B = 6;
+    const R* __restrict__ alpha = CgVec<R>::alpha(d);
+    const int64_t sl = v >> 6;
+    const int64_t base = d.n_off[sl] + (v & 63);
+    const int w = d.n_w[sl];
+    R s = R(0);
+    for (int k0 = q; k0 < w; k0 += B * L) {
+        int e[B];
+        R al[B];
+#pragma unroll
+        for (int j = 0; j < B; ++j) {
+            const int k = k0 + j * L;
+            const bool in = k < w;
+            const int64_t at = base + int64_t(in ? k : 0) * 64;
+            e[j] = d.mf_nidx[at];
+            al[j] = in ? alpha[at] : R(0);
+        }
+        R xe[B];
+#pragma unroll
+        for (int j = 0; j < B; ++j) xe[j] = z[e[j] >= 0 ? e[j] : ~e[j]];
+#pragma unroll
+        for (int j = 0; j < B; ++j) s += al[j] * (e[j] >= 0 ? xe[j] : -xe[j]);
+    }
+#pragma unroll
+    for (int o = 1; o < L; o <<= 1) s += __shfl_xor(s, o, 64);
+    return s;
+}
+
+// beta and the tests; x += alpha p; p = z + beta p; A p = A z + beta A p.
+// VERTS: the first gridDim.x - nrow blocks take the vertices.
+template <class R, bool VERTS>
+__global__ __launch_bounds__(512) void k_cg_direction(Dev d, int nvert) {
+    __shared__ double lds[2 * kMaxWaves];
+    const int T = blockDim.x;
+    const bool vert = VERTS && int(blockIdx.x) < nvert;
+    const int blk = vert ? int(blockIdx.x) : int(blockIdx.x) - nvert;
+    const int per = (vert ? nvert : int(gridDim.x) - nvert) / kXcds;
+    const int64_t lb = int64_t(blk % kXcds) * per + blk / kXcds;
+    if (lb >= (vert ? d.cg_vblk : d.cg_nblk)) return;
+    if (VERTS && vert) {
+        int64_t v0 = lb * (T / kCgVertexLanes), v1 = v0 + T / kCgVertexLanes;
+        int m = 0, p0 = 0, np = d.cg_nblk;
+        if (v1 > d.nv) v1 = d.nv;
+        if (d.nm > 1) {
+            const int4 t = d.cg_vert[lb];
+            const int2 pr = d.cg_parts[t.x];
+            m = t.x;
+            v0 = t.y;
+            v1 = t.z;
+            p0 = pr.x;
+            np = pr.y;
+        }
+        const double* sc = msc(d, m);
+        if (sc[SC_DONE] != 0.0) return;
+        R* __restrict__ pv = reinterpret_cast<R*>(d.mf_xv);
+        const int q = threadIdx.x & (kCgVertexLanes - 1);
+        const int64_t v = v0 + (threadIdx.x / kCgVertexLanes);
+        const int64_t vc = v < v1 ? v : v1 - 1;
+        const R old = pv[vc];
+        const R zv = vertex_sum<R>(d, CgVec<R>::z(d), vc, q);
+        double t[1];
+        sum_parts<1>(d.partial + d.cg_stride + p0, 0, np, lds, t);
+        const R beta = R(t[0] / sc[SC_RZ]);
+        if (q == 0 && v < v1) pv[v] = zv + beta * old;
+        return;
+    }
+    const Seg s = cg_seg(d, lb);
+    const R* __restrict__ z = CgVec<R>::z(d);
+    R* __restrict__ x = CgVec<R>::x(d);
+    R* __restrict__ p = CgVec<R>::p(d);
+    int64_t i = s.r0 + threadIdx.x;
+    const int64_t last = s.r1 - 1;
+    int64_t c = i < last ? i : last;
+    R xi = x[c], pi = p[c], zi = z[c];
+    if (s.sc[SC_DONE] != 0.0) return;
+    double t[2];
+    sum_parts<2>(d.partial + d.cg_stride + s.p0, d.cg_stride, s.np, lds, t);
+    const double beta = t[0] / s.sc[SC_RZ];
+    const R a = R(s.sc[SC_ALPHA]), b = R(beta);
+    for (; i < s.r1; i += T) {
+        const int64_t n = i + T;
+        c = n < last ? n : last;
+        const R xn = x[c], pn = p[c], zn = z[c];
+        x[i] = xi + a * pi;
+        p[i] = zi + b * pi;
+        xi = xn;
+        pi = pn;
+        zi = zn;
+    }
+    // count; convergence (1), iteration limit (2) or a scheduled restart (3)
+    if (s.lead && threadIdx.x == 0) {
+        double* sc = s.sc;
+        const double it = sc[SC_IT] + 1.0, since = sc[SC_SINCE] + 1.0;
+        sc[SC_BETA] = beta;
+        sc[SC_N_RZ] = t[0];
+        sc[SC_N_RR] = t[1];
+        sc[SC_N_IT] = it;
+        sc[SC_N_SINCE] = since;
+        double done = 0.0;
+        if (t[1] <= sc[SC_TOL2BB]) done = 1.0;
+        else if (it >= sc[SC_MAXIT]) done = 2.0;
+        else if (sc[SC_RESTART] > 0.0 && since >= sc[SC_RESTART]) done = 3.0;
+        sc[SC_N_DONE] = done;
+    }
+}
+
+// vertex values of p when the loop opens (p = z of the true residual)
+template <class R>
+__global__ __launch_bounds__(512) void k_cg_open_vertices(Dev d) {
+    const int64_t v = xcd_block() * (blockDim.x / kCgVertexLanes) + threadIdx.x / kCgVertexLanes;
+    const int q = threadIdx.x & (kCgVertexLanes - 1);
+    const int64_t vc = v < d.nv ? v : d.nv - 1;
+    const R s = vertex_sum<R>(d, CgVec<R>::p(d), vc, q);
+    if (q == 0 && v < d.nv) reinterpret_cast<R*>(d.mf_xv)[v] = s;
+}
+
+unsigned pad8(int64_t n) { return unsigned((n + kXcds - 1) / kXcds * kXcds); }
+
+}  // namespace
+
+CgPlan cg_plan(const Mesh& m) {
+    CgPlan c;
+    const size_t nm = m.mesh_start.size() - 1;
+    int64_t most = 0;
+    for (size_t k = 0; k < nm; ++k) most = std::max(most, m.mesh_start[k + 1] - m.mesh_start[k]);
+    if (most > int64_t(kCgMaxParts) * 256) c.threads = 512;
+    const int64_t per = int64_t(kCgMaxParts) * c.threads;
+    c.rows = int32_t(c.threads * std::max<int64_t>(1, (most + per - 1) / per));
+    const int64_t vrows = c.threads / kCgVertexLanes;
+    if (nm == 1) {
+        c.nblk = int32_t((m.nc + c.rows - 1) / c.rows);
+        c.vblk = int32_t((m.nv + vrows - 1) / vrows);
+        return c;
+    }
+    // vertices are numbered by their lowest cell, so a mesh's are contiguous
+    int64_t v = 0;
+    for (size_t k = 0; k < nm; ++k) {
+        const int64_t c0 = m.mesh_start[k], c1 = m.mesh_start[k + 1];
+        c.parts.push_back({int32_t(c.cells.size()), int32_t((c1 - c0 + c.rows - 1) / c.rows)});
+        for (int64_t r = c0; r < c1; r += c.rows)
+            c.cells.push_back({int32_t(k), int32_t(r), int32_t(std::min<int64_t>(r + c.rows, c1)), 0});
+        int64_t lo = v, hi = m.nv;
+        while (lo < hi) {
+            const int64_t mid = (lo + hi) / 2;
+            if (m.nidx[m.nptr[mid]] < c1) lo = mid + 1;
+            else hi = mid;
+        }
+        for (; v < lo; v += vrows)
+            c.vertices.push_back({int32_t(k), int32_t(v), int32_t(std::min<int64_t>(v + vrows, lo)), 0});
+        v = lo;
+    }
+    c.nblk = int32_t(c.cells.size());
+    c.vblk = int32_t(c.vertices.size());
+    return c;
+}
+
+bool cg_meshes_apart(const Mesh& m) {
+    if (m.mesh_start.size() <= 2) return true;
+    auto cell = [&](int32_t e) { return e < m.nc ? e : m.gowner[e - m.nc]; };
+    size_t k = 0;
+    for (int64_t v = 0; v < m.nv; ++v) {
+        while (cell(m.nidx[m.nptr[v]]) >= m.mesh_start[k + 1]) ++k;
+        for (int64_t e = m.nptr[v]; e < m.nptr[v + 1]; ++e)
+            if (cell(m.nidx[e]) >= m.mesh_start[k + 1]) return false;
+    }
+    return true;
+}
+
+namespace {
+template <class R>
+hipError_t cg_part(const Dev& d, bool stored, int part, hipStream_t s) {
+    const dim3 T(d.cg_threads);
+    const unsigned rows = pad8(d.cg_nblk), verts = stored ? 0u : pad8(d.cg_vblk);
+    // tiles per block of the stored product: no more partials than the next
+    // kernel's blocks add in one round
+    const int64_t most = 4 * d.cg_threads;
+    const int tiles = int((d.ntiles + most - 1) / most);
+    const unsigned nst = unsigned((d.ntiles + tiles - 1) / tiles);
+    if (part == 0 && stored)
+        hipLaunchKernelGGL(k_cg_product_stored<R>, dim3(nst), dim3(d.tile_rows), size_t(d.halo_max) * sizeof(R), s, d,
+                           tiles);
+    else if (part == 0)
+        hipLaunchKernelGGL(k_cg_product<R>, dim3(rows), T, 0, s, d);
+    else if (part == 1)
+        hipLaunchKernelGGL(k_cg_residual<R>, dim3(rows), T, 0, s, d, stored ? int(nst) : int(d.cg_nblk));
+    else if (stored)
+        hipLaunchKernelGGL((k_cg_direction<R, false>), dim3(rows), T, 0, s, d, 0);
+    else
+        hipLaunchKernelGGL((k_cg_direction<R, true>), dim3(rows + verts), T, 0, s, d, int(verts));
+    return hipGetLastError();
+}
+}  // namespace
+
+hipError_t launch_cg_part(const Dev& d, bool fp32, bool stored, int part, hipStream_t s) {
+    return fp32 ? cg_part<float>(d, stored, part, s) : cg_part<double>(d, stored, part, s);
+}
+
+hipError_t launch_cg_open_vertices(const Dev& d, bool fp32, hipStream_t s) {
+    if (fp32) hipLaunchKernelGGL(k_cg_open_vertices<float>, dim3(rows_m(d.nv * kCgVertexLanes, 256)), dim3(256), 0, s, d);
+    else hipLaunchKernelGGL(k_cg_open_vertices<double>, dim3(rows_m(d.nv * kCgVertexLanes, 256)), dim3(256), 0, s, d);
+    return hipGetLastError();
+}
+
+hipError_t launch_cg_commit(const Dev& d, hipStream_t s) {
+    hipLaunchKernelGGL(k_cg_commit, dim3((d.nm + 255) / 256), dim3(256), 0, s, d);
+    return hipGetLastError();
+}
+
+}  // namespace mifvm

@@ -8,6 +8,15 @@
 
 namespace mifvm {
 
+// what the three-kernel iteration's first product takes over (cg_iter.hip)
+__device__ inline void cg_stage_scalars(double* sc) {
+    sc[SC_N_RZ] = sc[SC_RZ];
+    sc[SC_N_RR] = sc[SC_RR];
+    sc[SC_N_IT] = sc[SC_IT];
+    sc[SC_N_SINCE] = sc[SC_SINCE];
+    sc[SC_N_DONE] = sc[SC_DONE];
+}
+
 // alpha = rz / (p . q)
 template <int Unused>
 __global__ __launch_bounds__(1024) void k_cg_alpha(Dev d, int64_t nparts, int64_t rows_per_block) {

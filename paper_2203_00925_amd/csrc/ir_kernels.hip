@@ -92,6 +92,7 @@ __global__ __launch_bounds__(1024) void k_ir_residual_fin(Dev d, int64_t nparts,
         sc[SC_TOL2BB] = fmax(tol_in * tol_in * trr32, 0.25 * sc[SC_TOL2BB_OUT]);
         sc[SC_SINCE] = 0.0;
         sc[SC_DONE] = (trr <= sc[SC_TOL2BB_OUT] || tbb == 0.0) ? 1.0 : (sc[SC_IT] >= sc[SC_MAXIT] ? 2.0 : 0.0);
+        cg_stage_scalars(sc);
     }
 }
 

@@ -276,6 +276,7 @@ __global__ __launch_bounds__(1024) void k_cg_setup_fin(Dev d, int64_t nparts, do
         }
         sc[SC_SINCE] = 0.0;
         sc[SC_DONE] = (trr <= sc[SC_TOL2BB] || tbb == 0.0) ? 1.0 : (sc[SC_IT] >= sc[SC_MAXIT] ? 2.0 : 0.0);
+        cg_stage_scalars(sc);
     }
 }
 

@@ -114,6 +114,13 @@ struct Dev {
     int32_t* mfc_vid;
     double *mfc_w, *mfc_r;
     float *mfc_w32, *mfc_r32;
+    // the CG iteration's blocks: rows per block, threads, counts; for several
+    // meshes each block's (mesh, begin, end) of rows and of vertices, and each
+    // mesh's (first block, blocks); the partials of one sum lie cg_stride apart
+    int32_t cg_rows, cg_threads, cg_nblk, cg_vblk;
+    int64_t cg_stride;
+    int4 *cg_blk, *cg_vert;
+    int2* cg_parts;
     double* partial;                      // reduction partials ([k][block], k < 4)
     double* scal;                         // solver scalars, [nm][SC_COUNT_]
 };
@@ -183,6 +190,7 @@ struct State {
     NnStateDev* nn_state = nullptr;       // owned host record
     bool kt_ready = false;                // K^T values match K
     bool mf = false;                      // the running solve applies K matrix-free
+    bool cg_split = true;                 // no vertex lies in two meshes (the three-kernel iteration's need)
     GmDev* gm = nullptr;                  // FGMRES workspace (owned host record)
     hipGraphExec_t gm_exec = nullptr;     // one captured FGMRES cycle
     int gm_exec_key = 0;
@@ -255,6 +263,16 @@ hipError_t launch_cg_spmv(const Dev& d, hipStream_t s);
 hipError_t launch_cg_axpy(const Dev& d, hipStream_t s);
 hipError_t launch_cg_dir(const Dev& d, hipStream_t s);
 
+// launchers (cg_iter.hip): the parts of one CG iteration in order (0 the
+// product, 1 the residual, 2 the direction), FP64 or the FP32 inner form, on
+// the stored matrix (one mesh) or matrix-free; the vertex values of p before
+// the first matrix-free iteration of an opened loop; the scalars after the
+// last iteration of a chunk
+constexpr int kCgParts = 3;
+hipError_t launch_cg_part(const Dev& d, bool fp32, bool stored, int part, hipStream_t s);
+hipError_t launch_cg_open_vertices(const Dev& d, bool fp32, hipStream_t s);
+hipError_t launch_cg_commit(const Dev& d, hipStream_t s);
+
 // launchers (mf_kernels.hip): y = K x from the discretisation (no stored matrix)
 // skip: a device flag; the product is skipped when it is non-zero (nullptr: never)
 hipError_t launch_mf_apply(const Dev& d, const BcTable& bc, const double* x, double* y, hipStream_t s,
@@ -294,6 +312,8 @@ enum Scal {
     // learned preconditioner: input scales and flexible-CG dot products
     SC_NN_INV_SR, SC_NN_INV_SD, SC_NN_SD, SC_NN_RR, SC_NN_DD, SC_ZR, SC_ZRO, SC_NN_RDR, SC_NN_DSCALE,
     SC_NORM,                              // mifvm_norm_l2 (mesh 0's slots)
+    // what the CG's direction kernel leaves for the next iteration
+    SC_N_RZ, SC_N_RR, SC_N_IT, SC_N_SINCE, SC_N_DONE,
     SC_COUNT_ = 32
 };
 
