@@ -162,18 +162,21 @@ size_t layout(const Mesh& m, char* base, Dev& d) {
     d.mfc_r32 = carve<float>(base, off, 4 * nc);
     // per-block partials of up to 4 sums x 2 mesh slots, for blocks of >= 64 rows
     const int64_t nblk = (nc + 63) / 64;
-    d.partial = carve<double>(base, off, 8 * (nblk + 1024));
+    d.partial = carve<double>(base, off, 8 * (nblk + 1024) + 3 * kCgMaxProductBlocks);
     d.nm = int32_t(m.mesh_start.size() - 1);
     const CgPlan cg = cg_plan(m);
-    d.cg_rows = cg.rows;
     d.cg_threads = cg.threads;
+    d.cg_rows = cg.rows;
+    d.cg_prows = cg.prows;
     d.cg_nblk = cg.nblk;
+    d.cg_pblk = cg.pblk;
     d.cg_vblk = cg.vblk;
-    // the stored product has at most 4 * threads partials of its own
-    d.cg_stride = std::max<int64_t>(cg.nblk, 4 * cg.threads);
+    // the stored product's partials may be more than the matrix-free one's
+    d.cg_stride = std::max<int64_t>(std::max(cg.nblk, cg.pblk), kCgMaxProductBlocks);
     d.cg_blk = carve<int4>(base, off, cg.cells.size());
+    d.cg_prod = carve<int4>(base, off, cg.product.size());
     d.cg_vert = carve<int4>(base, off, cg.vertices.size());
-    d.cg_parts = carve<int2>(base, off, cg.parts.size());
+    d.cg_parts = carve<int4>(base, off, cg.parts.size());
     d.mesh_start = carve<int64_t>(base, off, m.mesh_start.size());
     d.mesh_D = carve<double>(base, off, d.nm);
     d.mesh_dt = carve<double>(base, off, d.nm);
@@ -413,6 +416,7 @@ int mifvm_state_create(const mifvm_mesh* mesh, const mifvm_params* params, void*
             return bytes ? hipMemcpyAsync(dst, src, bytes, hipMemcpyHostToDevice, s) : hipSuccess;
         };
         e = table(d.cg_blk, cg.cells.data(), cg.cells.size() * sizeof(CgPlan::Item));
+        if (e == hipSuccess) e = table(d.cg_prod, cg.product.data(), cg.product.size() * sizeof(CgPlan::Item));
         if (e == hipSuccess) e = table(d.cg_vert, cg.vertices.data(), cg.vertices.size() * sizeof(CgPlan::Item));
         if (e == hipSuccess) e = table(d.cg_parts, cg.parts.data(), cg.parts.size() * sizeof(CgPlan::Range));
         if (e == hipSuccess) e = hipStreamSynchronize(s);  // the tables are freed at scope exit
@@ -942,6 +946,8 @@ int solve_impl(mifvm_state* st, const double* d_f, const double* f_internal, con
     const int method = opts ? opts->method : MIFVM_SOLVE_PLAIN;
     const int graph_opt = opts ? opts->graph : -1;
     const bool use_graph = !s.timer.on && (graph_opt == 1 || (graph_opt < 0 && s.tuned_graph == 1));
+    // untuned: the CG's chunks replay a graph once the first one is under way
+    bool auto_graph = !s.timer.on && graph_opt < 0 && s.tuned_chunk == 0;
     const double tol_in = opts && opts->inner_tol > 0 ? opts->inner_tol : 1e-4;
     double* hist = opts ? opts->history : nullptr;
     const int hist_cap = opts && opts->history ? opts->history_cap : 0;
@@ -1014,19 +1020,32 @@ int solve_impl(mifvm_state* st, const double* d_f, const double* f_internal, con
     }
     const int run_method = method == MIFVM_SOLVE_LEARNED ? MIFVM_SOLVE_PLAIN : method;
     const int graph_key = run_method + (matrix_free ? 16 : 0);
-    if (use_graph && (method != MIFVM_SOLVE_LEARNED || learned.fell_back) && method != MIFVM_SOLVE_AMG &&
-        method != MIFVM_SOLVE_FGMRES && (s.cg_exec == nullptr || s.cg_exec_chunk != chunk || s.cg_exec_method != graph_key)) {
-        HIPCHK(capture_graph(s, &s.cg_exec, [&](hipStream_t q) { return enqueue_cg_chunk(s, run_method, chunk, q); }));
-        s.cg_exec_chunk = chunk;
+    auto captured = [&]() { return s.cg_exec && s.cg_exec_chunk == chunk && s.cg_exec_method == graph_key; };
+    auto capture_chunk = [&]() -> hipError_t {
+        if (captured()) return hipSuccess;
+        hipError_t e =
+            capture_graph(s, &s.cg_exec, [&](hipStream_t q) { return enqueue_cg_chunk(s, run_method, chunk, q); });
+        s.cg_exec_chunk = e == hipSuccess ? chunk : 0;
         s.cg_exec_method = graph_key;
-    }
-    // one chunk of iterations: a graph replay, or direct launches
+        return e;
+    };
+    // One chunk of iterations.  Launching a kernel with the state's pointers
+    // takes the host 3.8 us, replaying it as a graph node the GPU 1.7 us, and
+    // the kernels of a small mesh are shorter than either: the first chunk of
+    // a state's first solve is launched, its graph is captured while that
+    // chunk runs, and the others replay it (a capture that fails leaves them
+    // launched).
     auto run_chunk = [&]() -> int {
-        if (use_graph) {
+        if (use_graph) HIPCHK(capture_chunk());
+        if (use_graph || (auto_graph && captured())) {
             HIPCHK(hipGraphLaunch(s.cg_exec, hs));
             return MIFVM_OK;
         }
         HIPCHK(enqueue_cg_chunk(s, run_method, chunk, hs));
+        if (auto_graph && capture_chunk() != hipSuccess) {
+            (void)hipGetLastError();
+            auto_graph = false;
+        }
         return MIFVM_OK;
     };
     int restarts = learned.restarts, outer = 0;

@@ -8,24 +8,26 @@
 
 namespace mifvm {
 
-// A block works on rows of one mesh only, `rows` consecutive ones, and
-// writes one partial per dot product.  Every block of the next kernel adds
-// all the partials of its mesh itself, so no mesh gets more than 1024 of them
-// (1024 doubles are 8 KB, an L2 hit for all but the first block of an XCD):
-// meshes of up to 1024 * 256 cells take one row per thread of a 256-thread
-// block, larger ones several rows per thread of a 512-thread block.
-constexpr int kCgMaxParts = 1024;
+// A block works on rows of one mesh only and writes one partial per dot
+// product; every block of the next kernel adds all the partials of its mesh
+// itself.  The vector kernels take up to 1024 blocks a mesh (four a CU, so
+// that the CUs stay even: 844 blocks made a product of 1.3M rows 18% slower
+// than 5,063), several rows a thread where a mesh has more than 1024 * 256.
+// The product's gathers want many short blocks instead: one row a thread up
+// to 8192 blocks (their partials, 64 KB, come from L2 for all but the first
+// block of an XCD).
+constexpr int kCgMaxBlocks = 1024, kCgMaxProductBlocks = 8192;
 constexpr int kCgVertexLanes = 4;         // lanes that share a vertex list
 
 struct CgPlan {
-    int32_t threads = 256;
-    int32_t rows = 256;                   // rows per block
-    int32_t nblk = 0, vblk = 0;           // blocks of rows, blocks of vertices
+    int32_t threads = 256, rows = 256;    // vector kernels: threads and rows of a block
+    int32_t prows = 256;                  // product: rows of a 256-thread block
+    int32_t nblk = 0, pblk = 0, vblk = 0; // blocks of rows, of product rows, of vertices
     // per block its mesh and row (vertex) range, per mesh its first block
     // and block count; filled for several meshes only (one mesh: arithmetic)
-    struct Item { int32_t mesh, begin, end, pad; };
-    struct Range { int32_t first, count; };
-    std::vector<Item> cells, vertices;
+    struct Item { int32_t mesh, begin, end, lead; };
+    struct Range { int32_t first, count, pfirst, pcount; };
+    std::vector<Item> cells, product, vertices;
     std::vector<Range> parts;
 };
 

@@ -58,22 +58,21 @@ template <> struct CgVec<float> {
     __device__ static const float *alpha(const Dev& d) { return d.n_alpha32; }
 };
 
-// a block's rows, its mesh's scalars and partials
+// a block's rows, its mesh's scalars and the partials it adds (the mesh's)
 struct Seg {
     int64_t r0, r1;
     double* sc;
-    int p0, np;
+    int p0, np, pp0, pnp;                 // first and count: the vector kernels', the product's
     bool lead;                            // the mesh's first block
 };
 
 __device__ inline Seg cg_seg(const Dev& d, int64_t lb) {
     if (d.nm == 1) {
         const int64_t r0 = lb * d.cg_rows, r1 = r0 + d.cg_rows;
-        return {r0, r1 < d.nc ? r1 : d.nc, d.scal, 0, d.cg_nblk, lb == 0};
+        return {r0, r1 < d.nc ? r1 : d.nc, d.scal, 0, d.cg_nblk, 0, d.cg_pblk, lb == 0};
     }
-    const int4 t = d.cg_blk[lb];
-    const int2 pr = d.cg_parts[t.x];
-    return {t.y, t.z, msc(d, t.x), pr.x, pr.y, lb == pr.x};
+    const int4 t = d.cg_blk[lb], pr = d.cg_parts[t.x];
+    return {t.y, t.z, msc(d, t.x), pr.x, pr.y, pr.z, pr.w, lb == pr.x};
 }
 
 // Sum of K values over the block, in a fixed order; valid in every thread.
@@ -95,23 +94,26 @@ __device__ inline void block_sums(double (&v)[K], double* lds) {
     }
 }
 
-// The K sums of a mesh's partials (part[k * stride + b]),
-// added by every block of a kernel: a thread's four loads go out together
-// (np is at most four times the block).
+// The K sums of a mesh's partials (part[k * stride + b]), added by every
+// block of a kernel; a thread's four loads of a round go out together.
 template <int K>
 __device__ inline void sum_parts(const double* __restrict__ part, int64_t stride, int np, double* lds,
                                  double (&out)[K]) {
     const int T = blockDim.x;
-    double v[K][4];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        const int b = int(threadIdx.x) + j * T;
-        const bool in = b < np;
+    for (int k = 0; k < K; ++k) out[k] = 0.0;
+    for (int b0 = threadIdx.x; b0 < np; b0 += 4 * T) {
+        double v[K][4];
 #pragma unroll
-        for (int k = 0; k < K; ++k) v[k][j] = in ? part[k * stride + b] : 0.0;
+        for (int j = 0; j < 4; ++j) {
+            const int b = b0 + j * T;
+            const bool in = b < np;
+#pragma unroll
+            for (int k = 0; k < K; ++k) v[k][j] = in ? part[k * stride + b] : 0.0;
+        }
+#pragma unroll
+        for (int k = 0; k < K; ++k) out[k] += (v[k][0] + v[k][1]) + (v[k][2] + v[k][3]);
     }
-#pragma unroll
-    for (int k = 0; k < K; ++k) out[k] = (v[k][0] + v[k][1]) + (v[k][2] + v[k][3]);
     block_sums<K>(out, lds);
 }
 
@@ -131,18 +133,28 @@ __global__ __launch_bounds__(256) void k_cg_commit(Dev d) {
 
 // q = K p row by row; partial p.q
 template <class R>
-__global__ __launch_bounds__(512) void k_cg_product(Dev d) {
+__global__ __launch_bounds__(kBlock) void k_cg_product(Dev d) {
     __shared__ double lds[kMaxWaves];
     const int64_t lb = xcd_block();
-    if (lb >= d.cg_nblk) return;
-    const Seg s = cg_seg(d, lb);
-    if (s.lead && threadIdx.x == 0) commit(s.sc);
-    if (s.sc[SC_N_DONE] != 0.0) return;
+    if (lb >= d.cg_pblk) return;
+    int64_t r0 = lb * d.cg_prows, r1 = r0 + d.cg_prows;
+    if (r1 > d.nc) r1 = d.nc;
+    double* sc = d.scal;
+    bool lead = lb == 0;
+    if (d.nm > 1) {
+        const int4 t = d.cg_prod[lb];
+        r0 = t.y;
+        r1 = t.z;
+        sc = msc(d, t.x);
+        lead = t.w != 0;
+    }
+    if (lead && threadIdx.x == 0) commit(sc);
+    if (sc[SC_N_DONE] != 0.0) return;
     const R* __restrict__ p = CgVec<R>::p(d);
     const R* __restrict__ pv = reinterpret_cast<const R*>(d.mf_xv);
     R* __restrict__ q = CgVec<R>::q(d);
     double v[1] = {0.0};
-    for (int64_t i = s.r0 + threadIdx.x; i < s.r1; i += blockDim.x) {
+    for (int64_t i = r0 + threadIdx.x; i < r1; i += kBlock) {
         const R y = cell_row(d, p, pv, i);
         q[i] = y;
         v[0] += double(p[i]) * double(y);
@@ -222,7 +234,7 @@ __global__ __launch_bounds__(512) void k_cg_residual(Dev d, int np) {
     R ri = r[c], qi = q[c], di = dinv[c];
     if (s.sc[SC_DONE] != 0.0) return;
     double pq[1];
-    sum_parts<1>(d.partial + s.p0, 0, d.nm == 1 ? np : s.np, lds, pq);
+    sum_parts<1>(d.partial + s.pp0, 0, d.nm == 1 ? np : s.pnp, lds, pq);
     const double alpha = s.sc[SC_RZ] / pq[0];
     if (s.lead && threadIdx.x == 0) {
         s.sc[SC_PQ] = pq[0];
@@ -304,7 +316,7 @@ __global__ __launch_bounds__(512) void k_cg_direction(Dev d, int nvert) {
         if (v1 > d.nv) v1 = d.nv;
         if (d.nm > 1) {
             const int4 t = d.cg_vert[lb];
-            const int2 pr = d.cg_parts[t.x];
+            const int4 pr = d.cg_parts[t.x];
             m = t.x;
             v0 = t.y;
             v1 = t.z;
@@ -384,12 +396,17 @@ CgPlan cg_plan(const Mesh& m) {
     const size_t nm = m.mesh_start.size() - 1;
     int64_t most = 0;
     for (size_t k = 0; k < nm; ++k) most = std::max(most, m.mesh_start[k + 1] - m.mesh_start[k]);
-    if (most > int64_t(kCgMaxParts) * 256) c.threads = 512;
-    const int64_t per = int64_t(kCgMaxParts) * c.threads;
-    c.rows = int32_t(c.threads * std::max<int64_t>(1, (most + per - 1) / per));
+    const int64_t share = (most + kCgMaxBlocks - 1) / kCgMaxBlocks;
+    if (share > 256) {                     // rows a thread, then threads in whole wavefronts
+        const int64_t per = (share + 511) / 512;
+        c.threads = int32_t(((share + per - 1) / per + 63) / 64 * 64);
+        c.rows = int32_t(c.threads * per);
+    }
+    c.prows = int32_t(256 * std::max<int64_t>(1, (most + 256 * kCgMaxProductBlocks - 1) / (256 * kCgMaxProductBlocks)));
     const int64_t vrows = c.threads / kCgVertexLanes;
     if (nm == 1) {
         c.nblk = int32_t((m.nc + c.rows - 1) / c.rows);
+        c.pblk = int32_t((m.nc + c.prows - 1) / c.prows);
         c.vblk = int32_t((m.nv + vrows - 1) / vrows);
         return c;
     }
@@ -397,20 +414,26 @@ CgPlan cg_plan(const Mesh& m) {
     int64_t v = 0;
     for (size_t k = 0; k < nm; ++k) {
         const int64_t c0 = m.mesh_start[k], c1 = m.mesh_start[k + 1];
-        c.parts.push_back({int32_t(c.cells.size()), int32_t((c1 - c0 + c.rows - 1) / c.rows)});
-        for (int64_t r = c0; r < c1; r += c.rows)
-            c.cells.push_back({int32_t(k), int32_t(r), int32_t(std::min<int64_t>(r + c.rows, c1)), 0});
+        auto split = [&](std::vector<CgPlan::Item>& out, int64_t from, int64_t to, int64_t step) {
+            for (int64_t r = from; r < to; r += step)
+                out.push_back({int32_t(k), int32_t(r), int32_t(std::min(r + step, to)), r == from ? 1 : 0});
+        };
+        const CgPlan::Range first = {int32_t(c.cells.size()), 0, int32_t(c.product.size()), 0};
+        split(c.cells, c0, c1, c.rows);
+        split(c.product, c0, c1, c.prows);
+        c.parts.push_back({first.first, int32_t(c.cells.size()) - first.first, first.pfirst,
+                           int32_t(c.product.size()) - first.pfirst});
         int64_t lo = v, hi = m.nv;
         while (lo < hi) {
             const int64_t mid = (lo + hi) / 2;
             if (m.nidx[m.nptr[mid]] < c1) lo = mid + 1;
             else hi = mid;
         }
-        for (; v < lo; v += vrows)
-            c.vertices.push_back({int32_t(k), int32_t(v), int32_t(std::min<int64_t>(v + vrows, lo)), 0});
+        split(c.vertices, v, lo, vrows);
         v = lo;
     }
     c.nblk = int32_t(c.cells.size());
+    c.pblk = int32_t(c.product.size());
     c.vblk = int32_t(c.vertices.size());
     return c;
 }
@@ -432,18 +455,15 @@ template <class R>
 hipError_t cg_part(const Dev& d, bool stored, int part, hipStream_t s) {
     const dim3 T(d.cg_threads);
     const unsigned rows = pad8(d.cg_nblk), verts = stored ? 0u : pad8(d.cg_vblk);
-    // tiles per block of the stored product: no more partials than the next
-    // kernel's blocks add in one round
-    const int64_t most = 4 * d.cg_threads;
-    const int tiles = int((d.ntiles + most - 1) / most);
+    const int tiles = int((d.ntiles + kCgMaxProductBlocks - 1) / kCgMaxProductBlocks);
     const unsigned nst = unsigned((d.ntiles + tiles - 1) / tiles);
     if (part == 0 && stored)
         hipLaunchKernelGGL(k_cg_product_stored<R>, dim3(nst), dim3(d.tile_rows), size_t(d.halo_max) * sizeof(R), s, d,
                            tiles);
     else if (part == 0)
-        hipLaunchKernelGGL(k_cg_product<R>, dim3(rows), T, 0, s, d);
+        hipLaunchKernelGGL(k_cg_product<R>, dim3(pad8(d.cg_pblk)), dim3(kBlock), 0, s, d);
     else if (part == 1)
-        hipLaunchKernelGGL(k_cg_residual<R>, dim3(rows), T, 0, s, d, stored ? int(nst) : int(d.cg_nblk));
+        hipLaunchKernelGGL(k_cg_residual<R>, dim3(rows), T, 0, s, d, stored ? int(nst) : int(d.cg_pblk));
     else if (stored)
         hipLaunchKernelGGL((k_cg_direction<R, false>), dim3(rows), T, 0, s, d, 0);
     else

@@ -114,13 +114,14 @@ struct Dev {
     int32_t* mfc_vid;
     double *mfc_w, *mfc_r;
     float *mfc_w32, *mfc_r32;
-    // the CG iteration's blocks: rows per block, threads, counts; for several
-    // meshes each block's (mesh, begin, end) of rows and of vertices, and each
-    // mesh's (first block, blocks); the partials of one sum lie cg_stride apart
-    int32_t cg_rows, cg_threads, cg_nblk, cg_vblk;
+    // the CG iteration's blocks (cg_iter.h): threads and rows of a vector
+    // kernel's block, rows of a product's, counts; for several meshes each
+    // block's (mesh, begin, end, first of the mesh) of rows, product rows and
+    // vertices, and each mesh's (first block, blocks) of both kinds; the
+    // partials of one sum lie cg_stride apart
+    int32_t cg_threads, cg_rows, cg_prows, cg_nblk, cg_pblk, cg_vblk;
     int64_t cg_stride;
-    int4 *cg_blk, *cg_vert;
-    int2* cg_parts;
+    int4 *cg_blk, *cg_prod, *cg_vert, *cg_parts;
     double* partial;                      // reduction partials ([k][block], k < 4)
     double* scal;                         // solver scalars, [nm][SC_COUNT_]
 };
