@@ -38,7 +38,6 @@ size_t layout(const Mesh& m, char* base, Dev& d) {
     d.xc = carve<double>(base, off, 3 * NX);
     d.minv = carve<double>(base, off, 6 * nc);
     d.xyz4 = carve<double4>(base, off, NX);
-    d.fx4 = carve<double4>(base, off, nf);
     d.c2f = carve<int32_t>(base, off, 4 * nc);
     d.c2n = carve<int32_t>(base, off, 4 * nc);
     d.s_off = carve<int64_t>(base, off, m.stencil.off.size());
@@ -66,16 +65,23 @@ size_t layout(const Mesh& m, char* base, Dev& d) {
     d.n_idx = carve<int32_t>(base, off, m.node.idx.size());
     d.n_alpha = carve<double>(base, off, m.node.val.size());
     d.n_len = carve<int32_t>(base, off, nv);
-    d.tv_max = m.tv_max;
-    d.e_off = carve<int64_t>(base, off, m.enbr.off.size());
-    d.e_w = carve<int32_t>(base, off, m.enbr.width.size());
-    d.e_lidx = carve<uint16_t>(base, off, m.e_lidx.size() > 0 ? m.e_lidx.size() : 1);
-    d.c2v_l = carve<uint16_t>(base, off, 4 * nc);
-    d.fv_off = carve<int64_t>(base, off, m.fv_off.size());
-    d.fv_len = carve<int32_t>(base, off, m.fv_len.size() > 0 ? m.fv_len.size() : 1);
-    d.f_off = carve<int64_t>(base, off, m.fnode.off.size());
-    d.f_w = carve<int32_t>(base, off, m.fnode.width.size() > 0 ? m.fnode.width.size() : 1);
-    d.f_lidx = carve<uint16_t>(base, off, m.f_lidx.size() > 0 ? m.f_lidx.size() : 1);
+    d.g_rows = m.g_rows;
+    d.g_max = m.g_max;
+    d.gv_max = m.gv_max;
+    d.g_tiles = (int64_t)m.g_self.size();
+    d.g_off = carve<int64_t>(base, off, m.g_off.size());
+    d.g_idx = carve<int32_t>(base, off, m.g_idx.size());
+    d.g_self = carve<int32_t>(base, off, m.g_self.size());
+    d.gv_off = carve<int64_t>(base, off, m.gv_off.size());
+    d.gv_idx = carve<int32_t>(base, off, m.gv_idx.size());
+    d.g_cell = carve<uint4>(base, off, nc);
+    d.ge_off = carve<int64_t>(base, off, m.ge_off.size());
+    d.ge_idx = carve<uint4>(base, off, m.ge_idx.size() / 8 + 1);
+    d.vpos = carve<double4>(base, off, nv);
+    d.vmean = carve<double4>(base, off, nv);
+    d.vslope = carve<double4>(base, off, nv);
+    d.vmom = carve<double4>(base, off, nv);
+    d.vmom32 = carve<float4>(base, off, nv);
     d.k_off = carve<int64_t>(base, off, m.kmat.off.size());
     d.k_w = carve<int32_t>(base, off, m.kmat.width.size());
     d.k_col = carve<int32_t>(base, off, m.kmat.idx.size());
@@ -99,9 +105,6 @@ size_t layout(const Mesh& m, char* base, Dev& d) {
     d.h_idx = carve<int32_t>(base, off, m.h_idx.size());
     d.h_self = carve<int32_t>(base, off, m.h_self.size());
     d.k_lidx = carve<uint16_t>(base, off, m.k_lidx.size());
-    d.c2n_l = carve<uint16_t>(base, off, m.c2n_l.size());
-    d.n_lidx = carve<uint16_t>(base, off, m.n_lidx.size());
-    d.v_off = carve<int64_t>(base, off, m.v_off.size());
     d.cell_perm = carve<int32_t>(base, off, nc);
     d.vert_perm = carve<int32_t>(base, off, nv);
     d.u = carve<double>(base, off, NX);
@@ -303,10 +306,8 @@ int mifvm_mesh_get_info(const mifvm_mesh* mesh, mifvm_mesh_info* out) {
     Dev d{};
     out->ws_bytes = layout(m, nullptr, d);
     out->edge_nbr_entries = (int64_t)m.eidx.size();
-    out->foreign_rows = (int64_t)m.fv_idx.size();
-    int64_t fe = 0;
-    for (int32_t n : m.fv_len) fe += n;
-    out->foreign_entries = fe;
+    out->foreign_rows = m.foreign_rows;
+    out->foreign_entries = m.foreign_entries;
     return MIFVM_OK;
 }
 
@@ -391,6 +392,11 @@ int mifvm_state_create(const mifvm_mesh* mesh, const mifvm_params* params, void*
     hipError_t e = hipHostMalloc(reinterpret_cast<void**>(&st.h_scal),
                                  size_t(st.d.nm) * SC_COUNT_ * sizeof(double), hipHostMallocDefault);
     if (e != hipSuccess) return cleanup(hip_fail(e, "hipHostMalloc"));
+#define UPB(dst, vec)                                           \
+    do {                                                        \
+        hipError_t e2 = up_bytes(dst, vec, s);                  \
+        if (e2 != hipSuccess) return cleanup(hip_fail(e2, "upload " #vec)); \
+    } while (0)
 #define UP(dst, vec)                                            \
     do {                                                        \
         hipError_t e2 = up(dst, vec, s);                        \
@@ -402,9 +408,11 @@ int mifvm_state_create(const mifvm_mesh* mesh, const mifvm_params* params, void*
     UP(d.kAC, m.kAC); UP(d.kBC, m.kBC); UP(d.kRL, m.kRL); UP(d.fx, m.fx); UP(d.S, m.S); UP(d.area, m.area);
     UP(d.gowner, m.gowner); UP(d.gtag, m.gtag); UP(d.gdist, m.gdist); UP(d.gbtri, m.gbtri);
     UP(d.n_off, m.node.off); UP(d.n_w, m.node.width); UP(d.n_idx, m.node.idx); UP(d.n_alpha, m.node.val);
-    UP(d.n_len, m.n_len); UP(d.e_off, m.enbr.off); UP(d.e_w, m.enbr.width); UP(d.e_lidx, m.e_lidx);
-    UP(d.c2v_l, m.c2v_l); UP(d.fv_off, m.fv_off); UP(d.fv_len, m.fv_len);
-    UP(d.f_off, m.fnode.off); UP(d.f_w, m.fnode.width); UP(d.f_lidx, m.f_lidx);
+    UP(d.n_len, m.n_len);
+    UP(d.g_off, m.g_off); UP(d.g_idx, m.g_idx); UP(d.g_self, m.g_self);
+    UP(d.gv_off, m.gv_off); UP(d.gv_idx, m.gv_idx); UP(d.ge_off, m.ge_off);
+    UPB(d.g_cell, m.g_cell); UPB(d.ge_idx, m.ge_idx);
+    UPB(d.vpos, m.vpos); UPB(d.vmean, m.vmean); UPB(d.vslope, m.vslope);
     UP(d.k_off, m.kmat.off); UP(d.k_w, m.kmat.width); UP(d.k_col, m.kmat.idx); UP(d.k_len, m.klen);
     UP(d.cell_perm, m.cell_perm); UP(d.vert_perm, m.vert_perm);
     UP(d.h_off, m.h_off); UP(d.h_idx, m.h_idx); UP(d.h_self, m.h_self);
@@ -429,23 +437,19 @@ int mifvm_state_create(const mifvm_mesh* mesh, const mifvm_params* params, void*
         e = hipStreamSynchronize(s);                       // Dm/zero are freed at scope exit
         if (e != hipSuccess) return cleanup(hip_fail(e, "upload mesh parameters"));
     }
-    UP(d.k_lidx, m.k_lidx); UP(d.c2n_l, m.c2n_l);
-    UP(d.n_lidx, m.n_lidx); UP(d.v_off, m.v_off);
-    {   // packed records of the centres and face centroids (gathered by tiles)
-        std::vector<double> rec(4 * (m.nc + m.nb)), frec(4 * m.nf);
+    UP(d.k_lidx, m.k_lidx);
+    {   // packed records of the centres (gathered by tiles)
+        std::vector<double> rec(4 * (m.nc + m.nb));
         const int64_t NXh = m.nc + m.nb;
         for (int64_t e = 0; e < NXh; ++e) {
             rec[4 * e] = m.xc[e]; rec[4 * e + 1] = m.xc[NXh + e]; rec[4 * e + 2] = m.xc[2 * NXh + e]; rec[4 * e + 3] = 0.0;
         }
-        for (int64_t f = 0; f < m.nf; ++f) {
-            frec[4 * f] = m.fx[f]; frec[4 * f + 1] = m.fx[m.nf + f]; frec[4 * f + 2] = m.fx[2 * m.nf + f]; frec[4 * f + 3] = 0.0;
-        }
         hipError_t e1 = hipMemcpyAsync(d.xyz4, rec.data(), rec.size() * 8, hipMemcpyHostToDevice, s);
-        if (e1 == hipSuccess) e1 = hipMemcpyAsync(d.fx4, frec.data(), frec.size() * 8, hipMemcpyHostToDevice, s);
-        if (e1 == hipSuccess) e1 = hipStreamSynchronize(s);      // rec/frec are freed at scope exit
+        if (e1 == hipSuccess) e1 = hipStreamSynchronize(s);      // rec is freed at scope exit
         if (e1 != hipSuccess) return cleanup(hip_fail(e1, "upload packed records"));
     }
 #undef UP
+#undef UPB
     const int64_t NX = m.nc + m.nb;
     e = hipMemsetAsync(d.u, 0, NX * sizeof(double), s);
     if (e == hipSuccess) e = hipMemsetAsync(d.src, 0, m.nc * sizeof(double), s);
@@ -665,6 +669,7 @@ int residual_parts(State& s, hipStream_t hs, bool ghosts = true) {
     KernelTimer& t = s.timer;
     if (ghosts)
         HIPCHK(timed(t, MIFVM_K_GHOST_FILL, hs, [&] { return launch_ghost_fill(d, s.fp32, s.bc[0], hs); }));
+    HIPCHK(timed(t, MIFVM_K_NODE_INTERP, hs, [&] { return launch_vertex_moments(d, s.fp32, hs); }));
     HIPCHK(timed(t, MIFVM_K_GRAD_LIMITER, hs, [&] { return launch_grad_limiter(d, s.fp32, hs, true); }));
     HIPCHK(timed(t, MIFVM_K_FACE_FLUX, hs, [&] { return launch_face_flux(d, s.fp32, s.bc[0], hs); }));
     return MIFVM_OK;
@@ -703,6 +708,7 @@ int mifvm_step(mifvm_state* st, int32_t n_steps, double dt, void* stream) {
             stage_buffers(d, s.fp32, k, &uin, &uout);
             if (fill)
                 HIPCHK(timed(t, MIFVM_K_GHOST_FILL, hs, [&] { return launch_ghost_fill(d, s.fp32, s.bc[0], hs); }));
+            HIPCHK(timed(t, MIFVM_K_NODE_INTERP, hs, [&] { return launch_vertex_moments(d, s.fp32, hs, uin); }));
             HIPCHK(timed(t, MIFVM_K_GRAD_LIMITER, hs,
                          [&] { return launch_grad_limiter(d, s.fp32, hs, false, uin); }));
             HIPCHK(timed(t, MIFVM_K_FV_CELL, hs,
@@ -725,7 +731,8 @@ hipError_t enqueue_steps(const State& s, int n, double dt, hipStream_t q) {
         const void* uin;
         void* uout;
         stage_buffers(d, s.fp32, k % 3, &uin, &uout);
-        e = launch_grad_limiter(d, s.fp32, q, false, uin);
+        e = launch_vertex_moments(d, s.fp32, q, uin);
+        if (e == hipSuccess) e = launch_grad_limiter(d, s.fp32, q, false, uin);
         if (e == hipSuccess) e = launch_cell_step(d, s.fp32, s.bc[0], uin, uout, alpha[k % 3], q);
     }
     return e;

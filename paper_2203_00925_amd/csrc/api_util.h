@@ -51,6 +51,13 @@ inline hipError_t up(T* dst, const std::vector<T>& src, hipStream_t s) {
     return hipMemcpyAsync(dst, src.data(), src.size() * sizeof(T), hipMemcpyHostToDevice, s);
 }
 
+// the same into an array of records of T
+template <class D, class T>
+inline hipError_t up_bytes(D* dst, const std::vector<T>& src, hipStream_t s) {
+    if (src.empty()) return hipSuccess;
+    return hipMemcpyAsync(dst, src.data(), src.size() * sizeof(T), hipMemcpyHostToDevice, s);
+}
+
 inline int reduce_blocks(int64_t n) {
     int64_t b = (n + mifvm::kBlock - 1) / mifvm::kBlock;
     return int(b < 1024 ? (b < 1 ? 1 : b) : 1024);

@@ -1,14 +1,14 @@
 // Kernels of the explicit finite-volume residual (eq. (4) of the paper) and
 // its Runge-Kutta update (eq. (6)), for CDNA4 wave64.
 //
-// A Runge-Kutta stage is two gather kernels, each owner-computes and free
+// A Runge-Kutta stage is three gather kernels, each owner-computes and free
 // of atomics:
-//   k_grad_moments  per tile of cells: least-squares gradient (Algorithm 1,
+//   k_vertex_moments  per vertex: the moments of its list that the gradient
+//                   needs, and the least-squares interpolation (Algorithm 2);
+//   k_grad_cells    per tile of cells: least-squares gradient (Algorithm 1,
 //                   in star-moment form), then the Barth-Jespersen limiter
 //                   over the 4 face neighbours and the MUSCL values at the
-//                   cell's face centroids; the same kernel computes the
-//                   vertex values of the least-squares interpolation
-//                   (Algorithm 2);
+//                   cell's face centroids;
 //   k_cell_step     per cell: the upwind convective fluxes (eq. (15)) minus
 //                   the diamond diffusive fluxes (eq. (diamond)) of its four
 //                   faces, summed, and the stage update.
@@ -41,9 +41,6 @@ __device__ inline int64_t gtid() { return int64_t(blockIdx.x) * blockDim.x + thr
 
 inline int grid_for(int64_t n) { return int((n + kBlock - 1) / kBlock); }
 
-template <class R> struct Vec4T;
-template <> struct Vec4T<double> { using T = double4; };
-template <> struct Vec4T<float> { using T = float4; };
 template <class R> struct Vec2T;
 template <> struct Vec2T<double> { using T = double2; };
 template <> struct Vec2T<float> { using T = float2; };
@@ -71,55 +68,6 @@ __global__ __launch_bounds__(kBlock) void k_ghost_fill(int64_t nc, int64_t nb,
     u[nc + g] = ug;
 }
 
-// Stage tile t's halo in LDS (positions relative to `ref`) as two 16-byte
-// arrays, (x, y) and (z, u): random reads of 16-byte items spread over twice
-// as many LDS bank groups as the halves of 32-byte records would.  Each
-// thread's 8 index loads go out together, then its 8 gathers, then the LDS
-// stores; `from` skips the part already staged.
-template <class R>
-struct HaloSoA {
-    using V2 = typename Vec2T<R>::T;
-    using V4 = typename Vec4T<R>::T;
-    V2* xy;
-    V2* zu;
-    __device__ V4 operator[](int l) const {
-        const V2 a = xy[l], b = zu[l];
-        return mk4(a.x, a.y, b.x, b.y);
-    }
-};
-
-template <class R>
-__device__ inline void stage_halo_soa(const Dev& d, const R* __restrict__ u, HaloSoA<R> sm, int64_t t, double4 ref,
-                                      int from = 0) {
-    const int T = blockDim.x;
-    const int64_t h0 = d.h_off[t];
-    const int hn = int(d.h_off[t + 1] - h0);
-    const double4* __restrict__ P = d.xyz4;
-    for (int hb = from; hb < hn; hb += 8 * T) {
-        int e[8];
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            const int h = hb + j * T + threadIdx.x;
-            e[j] = d.h_idx[h0 + (h < hn ? h : 0)];
-        }
-        double4 r[8];
-        R ue[8];
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            r[j] = P[e[j]];
-            ue[j] = u[e[j]];
-        }
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            const int h = hb + j * T + threadIdx.x;
-            if (h < hn) {
-                sm.xy[h] = mk2(R(r[j].x - ref.x), R(r[j].y - ref.y));
-                sm.zu[h] = mk2(R(r[j].z - ref.z), ue[j]);
-            }
-        }
-    }
-}
-
 // ---- gradient in star-moment form ------------------------------------------
 // The sum of Algorithm 1, J_i = sum_{j in N(i)} (x_j - x_i)(u_j - u_i) over
 // the node-neighbour stencil N(i) (every cell and ghost sharing a vertex
@@ -129,235 +77,220 @@ __device__ inline void stage_halo_soa(const Dev& d, const R* __restrict__ u, Hal
 // (i itself adds zeros).  For a list L of n entities with mean position xb,
 // mean value ub and centred moment C = sum (x_j - xb)(u_j - ub),
 //   T_L(i) = C + n (xb - x_i)(ub - u_i).
-// Each list is summed once per vertex instead of once per cell of its ~24
-// cells, and a cell reads 4 vertex records, its 4 face neighbours and ~13
-// edge neighbours instead of ~70 stencil entries.  Every term is a product
-// of differences of nearby values, so no large value cancels.
+// Every term is a product of differences of nearby values, so no large value
+// cancels.
 //
-// One block per tile of d.tile_rows cells.  The tile's halo (every cell and
-// ghost the tile's stencils reference) is staged in LDS and addressed by
-// 16-bit local indices, so global memory sees one gather per halo entity and
-// streamed index lists.  Every vertex the tile's cells touch (its own, then the foreign ones, whose lists
-// lie in the same halo) gets its record (xb, n), (C, ub) in LDS, from sums
-// shifted by the list's first entry (pad entries repeat it and add zeros):
-//   s = sum (x_j - x_0), q = sum (u_j - u_0), c = sum (x_j - x_0)(u_j - u_0),
-//   xb = x_0 + s/n, ub = u_0 + q/n, C = c - s q/n;
-// own vertices also store u_v = sum alpha u_j (Algorithm 2).
+// k_vertex_moments forms (C, ub) of every vertex list once, and with it the
+// least-squares vertex value of Algorithm 2: its weights are 1/n + b . (x_j -
+// xb) with a slope b per vertex, so u_v = ub + b . C, and no weight per list
+// entry is read.  k_grad_cells then needs, per cell, 4 vertex records, 4 face
+// neighbours and ~14 edge-only neighbours instead of ~70 stencil entries.
+
+// (C, ub) and u_v of one vertex, summed by 4 neighbouring lanes: lane q takes
+// the entries q, q + 4, ..., six loads of each kind in flight.  Values are
+// taken relative to the list's first entry's.
+template <class R>
+__global__ __launch_bounds__(kBlock) void k_vertex_moments(Dev d, FvArrays<R> a) {
+    constexpr int L = 4, B = 6;
+    const int64_t v = xcd_block() * (kBlock / L) + threadIdx.x / L;
+    const int q = threadIdx.x & (L - 1);
+    const int64_t vc = v < d.nv ? v : d.nv - 1;
+    const int64_t sl = vc >> 6;
+    const int64_t base = d.n_off[sl] + (vc & 63);
+    const int n = d.n_len[vc];
+    const double4 xb = d.vmean[vc], sb = d.vslope[vc];
+    const double4* __restrict__ P = d.xyz4;
+    const R* __restrict__ u = a.u;
+    R cx = R(0), cy = R(0), cz = R(0), su = R(0), u0 = R(0);
+    for (int k0 = 0; k0 < n; k0 += B * L) {               // uniform over the 4 lanes
+        int e[B];
+#pragma unroll
+        for (int j = 0; j < B; ++j) {
+            const int k = k0 + j * L + q;
+            e[j] = d.n_idx[base + int64_t(k < n ? k : 0) * 64];
+        }
+        double4 pe[B];
+        R ue[B];
+#pragma unroll
+        for (int j = 0; j < B; ++j) {
+            pe[j] = P[e[j]];
+            ue[j] = u[e[j]];
+        }
+        if (k0 == 0) u0 = __shfl(ue[0], int(threadIdx.x & 63 & ~(L - 1)), 64);
+#pragma unroll
+        for (int j = 0; j < B; ++j) {
+            const bool in = k0 + j * L + q < n;
+            const R du = in ? ue[j] - u0 : R(0);
+            cx += R(pe[j].x - xb.x) * du;
+            cy += R(pe[j].y - xb.y) * du;
+            cz += R(pe[j].z - xb.z) * du;
+            su += du;
+        }
+    }
+#pragma unroll
+    for (int o = 1; o < L; o <<= 1) {
+        cx += __shfl_xor(cx, o, 64);
+        cy += __shfl_xor(cy, o, 64);
+        cz += __shfl_xor(cz, o, 64);
+        su += __shfl_xor(su, o, 64);
+    }
+    if (q != 0 || v >= d.nv) return;
+    const R ub = u0 + su / R(n);
+    a.vmom[v] = mk4(cx, cy, cz, ub);
+    a.unode[v] = ub + (R(sb.x) * cx + R(sb.y) * cy + R(sb.z) * cz);
+}
+
+// One block per tile of d.g_rows cells.  The tile's halo (its cells and the
+// entities sharing an edge or a face with one, 2.9 per cell) is staged in LDS
+// as two arrays of 16-byte items, (x, y) and (z, u), and the records of the
+// vertices its cells touch (0.49 per cell) as five and a half: random reads of
+// 16-byte items spread over the bank groups.  39 KB a tile, so four tiles
+// share a CU.  Loads go out in two waves before the one barrier: the indices
+// and the cell's own tables (16 bytes a load: 8 local indices), then the
+// gathers they address; out-of-range slots read a valid address and are
+// discarded, so no load sits under a branch.
+//
+// The limiter's face centroids come from the cell's vertices: with x_i the
+// mean of the four and x_f of three of them, x_f - x_i = (x_i - x_v)/3 for the
+// vertex v across from the face.
 template <class R, bool PARTS>
-__global__ __launch_bounds__(kBlock) void k_grad_moments(Dev d, FvArrays<R> a) {
+__global__ __launch_bounds__(kBlock, 4) void k_grad_cells(Dev d, FvArrays<R> a) {
     using V2 = typename Vec2T<R>::T;
     using V4 = typename Vec4T<R>::T;
     extern __shared__ __align__(16) unsigned char sm_raw[];
-    // [halo] (x, y), [halo] (z, u), then the touched vertices' records as
-    // four 16-byte arrays (xb_x, xb_y), (xb_z, n), (C_x, C_y), (C_z, ub): a
-    // random vertex's first 16 bytes then fall in any of 8 bank groups, not 2
-    const int hcap = (d.halo_max + 1) & ~1;
-    const HaloSoA<R> sm{reinterpret_cast<V2*>(sm_raw), reinterpret_cast<V2*>(sm_raw) + hcap};
-    const int tvc = d.tv_max;
-    V2* va = sm.zu + hcap;
-    V2* vb = va + tvc;
-    V2* vc = vb + tvc;
-    V2* vd = vc + tvc;
-    constexpr bool rel = std::is_same<R, float>::value;
+    const int hc = d.g_max, vcap = d.gv_max;
+    V2* const xy = reinterpret_cast<V2*>(sm_raw);         // halo
+    V2* const zu = xy + hc;
+    V2* const va = zu + hc;                               // vertices: (xb_x, xb_y), (xb_z, n),
+    V2* const vb = va + vcap;
+    V2* const vc = vb + vcap;                             // (C_x, C_y), (C_z, ub),
+    V2* const vd = vc + vcap;
+    V2* const ve = vd + vcap;                             // (x_v, y_v), z_v
+    R* const vf = reinterpret_cast<R*>(ve + vcap);
+    constexpr bool rel = std::is_same<R, float>::value;   // FP32: positions relative to the tile's first cell
     const int64_t nc = d.nc;
     const int64_t t = xcd_block();
-    if (t >= d.ntiles) return;
+    if (t >= d.g_tiles) return;
     const int T = blockDim.x;
     const int64_t i = t * T + threadIdx.x;
     const bool cell = i < nc;
-    const int lself = d.h_self[t] + threadIdx.x;
-
-    // Global loads are issued in two waves before the first barrier, so the
-    // tile pays about two memory latencies before its LDS work: first every
-    // load that depends on no other (the first 8T halo indices, the cell's
-    // tables, the slice headers of its edge-neighbour list and of the vertex
-    // list it will sum), then the loads addressed by those (the halo
-    // gathers, the first batches of both lists).  Out-of-range slots read a
-    // valid address and are discarded, so no load sits under a branch.
-    const int64_t h0 = d.h_off[t];
-    const int hn = int(d.h_off[t + 1] - h0);
-    int he[8];
-#pragma unroll
-    for (int j = 0; j < 8; ++j) {
-        const int h = j * T + threadIdx.x;
-        he[j] = d.h_idx[h0 + (h < hn ? h : 0)];
-    }
     const int64_t ic = cell ? i : nc - 1;
-    uint16_t nl[4], lv[4];
-    int fc[4];
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-        fc[k] = d.c2f[k * nc + ic];
-        nl[k] = d.c2n_l[k * nc + ic];
-        lv[k] = d.c2v_l[k * nc + ic];
-    }
-    const int64_t eoff = d.e_off[ic >> 6];
-    const int ew = cell ? d.e_w[ic >> 6] : 0;
+    const int64_t h0 = d.g_off[t], w0 = d.gv_off[t];
+    const int hn = int(d.g_off[t + 1] - h0), wn = int(d.gv_off[t + 1] - w0);
+    const int self = d.g_self[t] + (cell ? int(threadIdx.x) : 0);
+    const int64_t s = ic >> 6;
+    const int64_t eb = d.ge_off[s];
+    const int ew = int(d.ge_off[s + 1] - eb) >> 6;        // groups of 8 edge-only neighbours
+    const uint4* __restrict__ ep = d.ge_idx + eb + (ic & 63);
 
-    const int64_t v0 = d.v_off[t], f0 = d.fv_off[t];
-    const int own = int(d.v_off[t + 1] - v0), nfor = int(d.fv_off[t + 1] - f0);
-    int r = threadIdx.x;
-    bool mine = true;
-    int64_t row = 0, vbase = 0;
-    int vw = 0, vn = 1;
-    const uint16_t* __restrict__ li = d.n_lidx;
-    constexpr int VB = 8;               // vertex-list entries per batch
-    uint16_t vl[VB];
-    R val[VB];
-    // row meta of vertex row r (threads past the rows read row 0 of the
-    // tile-owned lists and sum nothing)
-    auto vmeta = [&]() {
-        const bool act = r < own + nfor;
-        mine = !act || r < own;
-        row = !act ? 0 : (mine ? v0 + r : f0 + (r - own));
-        const int64_t sl = row >> 6;
-        const int64_t* __restrict__ op = mine ? d.n_off : d.f_off;
-        const int32_t* __restrict__ wp = mine ? d.n_w : d.f_w;
-        const int32_t* __restrict__ np = mine ? d.n_len : d.fv_len;
-        vbase = op[sl] + (row & 63);
-        vw = act ? wp[sl] : 0;
-        vn = np[row];
-        li = mine ? d.n_lidx : d.f_lidx;
-    };
-    auto vbatch = [&]() {
+    constexpr int HB = 4;
+    int he[HB];
 #pragma unroll
-        for (int j = 0; j < VB; ++j) {
-            const bool in = j < vw;
-            vl[j] = in ? li[vbase + int64_t(j) * 64] : uint16_t(0);
-            val[j] = (mine && in) ? a.n_alpha[vbase + int64_t(j) * 64] : R(0);
-        }
-    };
-    vmeta();
-
-    const double4* __restrict__ P = d.xyz4;
-    double4 hp[8];
-    R hu[8];
-#pragma unroll
-    for (int j = 0; j < 8; ++j) {
-        hp[j] = P[he[j]];
-        hu[j] = a.u[he[j]];
-    }
-#pragma unroll
-    for (int k = 0; k < 4; ++k) fc[k] = fc[k] < 0 ? ~fc[k] : fc[k];
-    const uint16_t* __restrict__ eidx = d.e_lidx + (cell ? eoff + (i & 63) : 0);
-    constexpr int EB = 16;              // edge-only neighbours per batch
-    uint16_t el[EB];
-#pragma unroll
-    for (int j = 0; j < EB; ++j) el[j] = j < ew ? eidx[int64_t(j) * 64] : uint16_t(lself);
-    vbatch();
-
-    const double4 ref = rel ? d.xyz4[t * T] : make_double4(0.0, 0.0, 0.0, 0.0);
-#pragma unroll
-    for (int j = 0; j < 8; ++j) {
+    for (int j = 0; j < HB; ++j) {
         const int h = j * T + threadIdx.x;
-        if (h < hn) {
-            sm.xy[h] = mk2(R(hp[j].x - ref.x), R(hp[j].y - ref.y));
-            sm.zu[h] = mk2(R(hp[j].z - ref.z), hu[j]);
-        }
+        he[j] = d.g_idx[h0 + (h < hn ? h : 0)];
     }
-    if (hn > 8 * T) stage_halo_soa<R>(d, a.u, sm, t, ref, 8 * T);
-    __syncthreads();
-
-    for (; r < own + nfor; r += T) {
-        if (r != int(threadIdx.x)) {
-            vmeta();
-            vbatch();
-        }
-        const uint16_t l0 = vl[0];
-        const V4 q0 = sm[l0];
-        R un = R(0), sx = R(0), sy = R(0), sz = R(0), su = R(0), cx = R(0), cy = R(0), cz = R(0);
-        for (int k0 = 0; k0 < vw; k0 += VB) {
-            // next batch in flight while this one is summed (pad = first entry)
-            uint16_t nlx[VB];
-            R nal[VB];
+    int wv = d.gv_idx[w0 + (int(threadIdx.x) < wn ? int(threadIdx.x) : 0)];
+    const uint4 cl = d.g_cell[ic];
+    uint4 e0 = ew > 0 ? ep[0] : make_uint4(0, 0, 0, 0), e1 = ew > 1 ? ep[64] : make_uint4(0, 0, 0, 0);
+    const double4* __restrict__ P = d.xyz4;
+    const R* __restrict__ u = a.u;
+    const double4 ref = rel ? P[t * T] : make_double4(0.0, 0.0, 0.0, 0.0);
+    double4 hp[HB];
+    R hu[HB];
 #pragma unroll
-            for (int j = 0; j < VB; ++j) {
-                const bool in = k0 + VB + j < vw;
-                const int64_t at = vbase + int64_t(k0 + VB + j) * 64;
-                nlx[j] = in ? li[at] : l0;
-                nal[j] = (mine && in) ? a.n_alpha[at] : R(0);
-            }
-#pragma unroll
-            for (int j = 0; j < VB; ++j) {
-                const V4 q = sm[k0 + j < vw ? vl[j] : l0];
-                const R dx = q.x - q0.x, dy = q.y - q0.y, dz = q.z - q0.z, du = q.w - q0.w;
-                un += val[j] * q.w;
-                sx += dx; sy += dy; sz += dz; su += du;
-                cx += dx * du; cy += dy * du; cz += dz * du;
-            }
-#pragma unroll
-            for (int j = 0; j < VB; ++j) {
-                vl[j] = nlx[j];
-                val[j] = nal[j];
-            }
-        }
-        const R inv = R(1) / R(vn);
-        const R mu = su * inv;
-        va[r] = mk2(q0.x + sx * inv, q0.y + sy * inv);
-        vb[r] = mk2(q0.z + sz * inv, R(vn));
-        vc[r] = mk2(cx - sx * mu, cy - sy * mu);
-        vd[r] = mk2(cz - sz * mu, q0.w + mu);
-        if (mine) a.unode[row] = un;
+    for (int j = 0; j < HB; ++j) {
+        hp[j] = P[he[j]];
+        hu[j] = u[he[j]];
     }
-    // loads used at the end (limiter, M^-1) go out before the barrier
-    double4 xf[4];
+    auto put_vertex = [&](int w, const double4& xb, const double4& xv, const V4& mo) {
+        va[w] = mk2(R(xb.x - ref.x), R(xb.y - ref.y));
+        vb[w] = mk2(R(xb.z - ref.z), R(xb.w));
+        vc[w] = mk2(mo.x, mo.y);
+        vd[w] = mk2(mo.z, mo.w);
+        ve[w] = mk2(R(xv.x - ref.x), R(xv.y - ref.y));
+        vf[w] = R(xv.z - ref.z);
+    };
+    {
+        const double4 xb = d.vmean[wv], xv = d.vpos[wv];
+        const V4 mo = a.vmom[wv];
 #pragma unroll
-    for (int k = 0; k < 4; ++k) xf[k] = d.fx4[fc[k]];
+        for (int j = 0; j < HB; ++j) {
+            const int h = j * T + threadIdx.x;
+            if (h < hn) {
+                xy[h] = mk2(R(hp[j].x - ref.x), R(hp[j].y - ref.y));
+                zu[h] = mk2(R(hp[j].z - ref.z), hu[j]);
+            }
+        }
+        if (int(threadIdx.x) < wn) put_vertex(threadIdx.x, xb, xv, mo);
+    }
     const R* __restrict__ m = a.minv;
     const R m0 = m[ic], m1 = m[nc + ic], m2 = m[2 * nc + ic];
     const R m3 = m[3 * nc + ic], m4 = m[4 * nc + ic], m5 = m[5 * nc + ic];
+    for (int h = HB * T + threadIdx.x; h < hn; h += T) {
+        const int e = d.g_idx[h0 + h];
+        const double4 p = P[e];
+        xy[h] = mk2(R(p.x - ref.x), R(p.y - ref.y));
+        zu[h] = mk2(R(p.z - ref.z), u[e]);
+    }
+    for (int w = T + threadIdx.x; w < wn; w += T) {
+        wv = d.gv_idx[w0 + w];
+        put_vertex(w, d.vmean[wv], d.vpos[wv], a.vmom[wv]);
+    }
     __syncthreads();
     if (!cell) return;
 
-    const V4 me = sm[lself];
-    const R xi = me.x, yi = me.y, zi = me.z, ui = me.w;
+    const V2 sxy = xy[self], szu = zu[self];
+    const R xi = sxy.x, yi = sxy.y, zi = szu.x, ui = szu.y;
+    const uint32_t fl[2] = {cl.x, cl.y}, vl[2] = {cl.z, cl.w};
     R jx = R(0), jy = R(0), jz = R(0);
+    R ox[4], oy[4], oz[4];                                // x_i - x_v
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
-        const V2 pa = va[lv[k]], pb = vb[lv[k]], pc = vc[lv[k]], pd = vd[lv[k]];
-        const V4 vs = mk4(pa.x, pa.y, pb.x, pb.y), vm = mk4(pc.x, pc.y, pd.x, pd.y);
-        const R nd = vs.w * (vm.w - ui);
-        jx += vm.x + (vs.x - xi) * nd;
-        jy += vm.y + (vs.y - yi) * nd;
-        jz += vm.z + (vs.z - zi) * nd;
+        const int l = int(vl[k >> 1] >> (16 * (k & 1))) & 0xffff;
+        const V2 A = va[l], Bv = vb[l], C = vc[l], Dv = vd[l], E = ve[l];
+        const R nd = Bv.y * (Dv.y - ui);
+        jx += C.x + (A.x - xi) * nd;
+        jy += C.y + (A.y - yi) * nd;
+        jz += Dv.x + (Bv.x - zi) * nd;
+        ox[k] = xi - E.x;
+        oy[k] = yi - E.y;
+        oz[k] = zi - vf[l];
     }
     R umax = ui, umin = ui;
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
-        const V4 o = sm[nl[k]];
-        const R du2 = R(2) * (o.w - ui);
-        jx -= (o.x - xi) * du2;
-        jy -= (o.y - yi) * du2;
-        jz -= (o.z - zi) * du2;
-        umax = fmax(umax, o.w);
-        umin = fmin(umin, o.w);
+        const int l = int(fl[k >> 1] >> (16 * (k & 1))) & 0xffff;
+        const V2 p = xy[l], z = zu[l];
+        const R du2 = R(2) * (z.y - ui);
+        jx -= (p.x - xi) * du2;
+        jy -= (p.y - yi) * du2;
+        jz -= (z.x - zi) * du2;
+        umax = fmax(umax, z.y);
+        umin = fmin(umin, z.y);
     }
-    // edge-only neighbours (slice padding = the cell itself, which adds zeros)
-    for (int k0 = 0; k0 < ew; k0 += EB) {
-        uint16_t nx[EB];
+    auto edges = [&](const uint4& g) {                    // 8 edge-only neighbours (padding = the cell: adds zeros)
+        const uint32_t w[4] = {g.x, g.y, g.z, g.w};
 #pragma unroll
-        for (int j = 0; j < EB; ++j)
-            nx[j] = k0 + EB + j < ew ? eidx[int64_t(k0 + EB + j) * 64] : uint16_t(lself);
-#pragma unroll
-        for (int j = 0; j < EB; ++j) {
-            if (k0 + j < ew) {          // uniform over the wave (one slice)
-                const V4 o = sm[el[j]];
-                const R du = o.w - ui;
-                jx -= (o.x - xi) * du;
-                jy -= (o.y - yi) * du;
-                jz -= (o.z - zi) * du;
-            }
+        for (int k = 0; k < 8; ++k) {
+            const int l = int(w[k >> 1] >> (16 * (k & 1))) & 0xffff;
+            const V2 p = xy[l], z = zu[l];
+            const R du = z.y - ui;
+            jx -= (p.x - xi) * du;
+            jy -= (p.y - yi) * du;
+            jz -= (z.x - zi) * du;
         }
-#pragma unroll
-        for (int j = 0; j < EB; ++j) el[j] = nx[j];
-    }
+    };
+    if (ew > 0) edges(e0);
+    if (ew > 1) edges(e1);
+    for (int g = 2; g < ew; ++g) edges(ep[int64_t(g) * 64]);
     const R gx = m0 * jx + m1 * jy + m2 * jz;
     const R gy = m1 * jx + m3 * jy + m4 * jz;
     const R gz = m2 * jx + m4 * jy + m5 * jz;
     R psi = R(1), dl[4];
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
-        dl[k] = gx * (R(xf[k].x - ref.x) - xi) + gy * (R(xf[k].y - ref.y) - yi) + gz * (R(xf[k].z - ref.z) - zi);
+        dl[k] = (gx * ox[k] + gy * oy[k] + gz * oz[k]) * (R(1) / R(3));
         R ph = R(1);
         if (dl[k] > R(0)) ph = fmin(R(1), (umax - ui) / dl[k]);
         else if (dl[k] < R(0)) ph = fmin(R(1), (umin - ui) / dl[k]);
@@ -726,13 +659,13 @@ __global__ void k_set_dt(Dev d, double dt, double cfl) {
 // ---- launchers ---------------------------------------------------------------
 FvArrays<double> fv64(const Dev& d) {
     return {d.u, d.grad, d.psi, d.unode, d.flux, d.phi, d.minv, d.kAC, d.kBC, d.kRL, d.area,
-            d.vol, d.src, d.n_alpha, d.fx, d.xc, d.gdist, d.uf, d.fvc_w, d.fvc_r, d.fvc_phi};
+            d.vol, d.src, d.n_alpha, d.fx, d.xc, d.gdist, d.uf, d.fvc_w, d.fvc_r, d.fvc_phi, d.vmom};
 }
 
 FvArrays<float> fv32(const Dev& d) {
     return {d.u32, d.grad32, d.psi32, d.unode32, d.flux32, d.phi32, d.minv32, d.kAC32, d.kBC32,
             d.kRL32, d.area32, d.vol32, d.src32, d.n_alpha32, d.fx32, d.xc32, d.gdist32,
-            d.uf32, d.fvc_w32, d.fvc_r32, d.fvc_phi32};
+            d.uf32, d.fvc_w32, d.fvc_r32, d.fvc_phi32, d.vmom32};
 }
 
 template <class R>
@@ -747,20 +680,17 @@ hipError_t launch_ghost_fill(const Dev& d, bool fp32, const BcTable& bc, hipStre
     return fp32 ? launch_ghost_fill_t(d, fv32(d), bc, s) : launch_ghost_fill_t(d, fv64(d), bc, s);
 }
 
-// The star-moment tile kernel in either precision (it also computes the
-// vertex values): LDS of the halo's two 2-vectors and the touched vertices'
-// four 2-vectors
+// the gradient tiles' LDS: the halo's two 2-vectors, the vertices' five and z
 template <class R>
-size_t moments_lds_bytes(const Dev& d) {
-    using V2 = typename Vec2T<R>::T;
-    return size_t(2 * ((d.halo_max + 1) & ~1) + 4 * d.tv_max) * sizeof(V2);
+size_t grad_lds_bytes(const Dev& d) {
+    return (size_t(2 * d.g_max + 5 * d.gv_max) * 2 + d.gv_max) * sizeof(R);
 }
 
 template <class R, bool PARTS>
 hipError_t allow_lds(const Dev& d) {
-    const size_t lds = moments_lds_bytes<R>(d);
+    const size_t lds = grad_lds_bytes<R>(d);
     if (lds <= 65536) return hipSuccess;
-    return hipFuncSetAttribute(reinterpret_cast<const void*>(&k_grad_moments<R, PARTS>),
+    return hipFuncSetAttribute(reinterpret_cast<const void*>(&k_grad_cells<R, PARTS>),
                                hipFuncAttributeMaxDynamicSharedMemorySize, int(lds));
 }
 
@@ -773,20 +703,32 @@ hipError_t setup_fv_kernels(const Dev& d) {
 }
 
 template <class R>
-void launch_grad_t(const Dev& d, FvArrays<R> a, bool parts, const void* u_in, hipStream_t s) {
-    const dim3 b(d.tile_rows);
-    // grid padded to a multiple of 8 for the XCD-contiguous tile order
-    const dim3 gx(unsigned((d.ntiles + kXcds - 1) / kXcds * kXcds));
+FvArrays<R> with_u(FvArrays<R> a, const void* u_in) {
     if (u_in) a.u = const_cast<R*>(static_cast<const R*>(u_in));   // read only
+    return a;
+}
+
+hipError_t launch_vertex_moments(const Dev& d, bool fp32, hipStream_t s, const void* u_in) {
+    const dim3 g(rows_m(d.nv * 4, kBlock)), b(kBlock);
+    if (fp32) hipLaunchKernelGGL(k_vertex_moments<float>, g, b, 0, s, d, with_u(fv32(d), u_in));
+    else hipLaunchKernelGGL(k_vertex_moments<double>, g, b, 0, s, d, with_u(fv64(d), u_in));
+    return hipGetLastError();
+}
+
+template <class R>
+void launch_grad_t(const Dev& d, const FvArrays<R>& a, bool parts, hipStream_t s) {
+    const dim3 b(d.g_rows);
+    // grid padded to a multiple of 8 for the XCD-contiguous tile order
+    const dim3 gx(unsigned((d.g_tiles + kXcds - 1) / kXcds * kXcds));
     if (parts)
-        hipLaunchKernelGGL((k_grad_moments<R, true>), gx, b, moments_lds_bytes<R>(d), s, d, a);
+        hipLaunchKernelGGL((k_grad_cells<R, true>), gx, b, grad_lds_bytes<R>(d), s, d, a);
     else
-        hipLaunchKernelGGL((k_grad_moments<R, false>), gx, b, moments_lds_bytes<R>(d), s, d, a);
+        hipLaunchKernelGGL((k_grad_cells<R, false>), gx, b, grad_lds_bytes<R>(d), s, d, a);
 }
 
 hipError_t launch_grad_limiter(const Dev& d, bool fp32, hipStream_t s, bool parts, const void* u_in) {
-    if (fp32) launch_grad_t(d, fv32(d), parts, u_in, s);
-    else launch_grad_t(d, fv64(d), parts, u_in, s);
+    if (fp32) launch_grad_t(d, with_u(fv32(d), u_in), parts, s);
+    else launch_grad_t(d, with_u(fv64(d), u_in), parts, s);
     return hipGetLastError();
 }
 hipError_t launch_face_flux(const Dev& d, bool fp32, const BcTable& bc, hipStream_t s) {

@@ -528,6 +528,9 @@ int preprocess(const double* xyz, int64_t nv, const int32_t* tets, int64_t nc,
     mark("vertex lists");
     // -- 11. least-squares vertex weights (Algorithm 2) -------------------------
     M.nalpha.assign(M.nidx.size(), 0.0);
+    M.vpos.assign(4 * nv, 0.0);
+    M.vmean.assign(4 * nv, 0.0);
+    M.vslope.assign(4 * nv, 0.0);
     for (int64_t v = 0; v < nv; ++v) {
         V3 xv = P(vnew2old[v]);
         double A[4][4] = {{0}};
@@ -537,12 +540,21 @@ int preprocess(const double* xyz, int64_t nv, const int32_t* tets, int64_t nc,
             for (int i = 0; i < 4; ++i)
                 for (int j = 0; j < 4; ++j) A[i][j] += r[i] * r[j];
         }
+        const double sum[3] = {A[0][1], A[0][2], A[0][3]};
         double rhs[4] = {1, 0, 0, 0}, w[4];
         if (!solve4(A, rhs, w)) { err = "singular vertex least-squares system"; return E_MESH; }
         for (int64_t e = M.nptr[v]; e < M.nptr[v + 1]; ++e) {
             int32_t id = M.nidx[e];
             M.nalpha[e] = w[0] + w[1] * (M.xc[id] - xv.x) + w[2] * (M.xc[NX + id] - xv.y) +
                           w[3] * (M.xc[2 * NX + id] - xv.z);
+        }
+        const double n = double(M.n_len[v]);
+        const double pos[4] = {xv.x, xv.y, xv.z, 0.0}, mean[4] = {xv.x + sum[0] / n, xv.y + sum[1] / n, xv.z + sum[2] / n, n};
+        const double slope[4] = {w[1], w[2], w[3], 0.0};
+        for (int k = 0; k < 4; ++k) {
+            M.vpos[4 * v + k] = pos[k];
+            M.vmean[4 * v + k] = mean[k];
+            M.vslope[4 * v + k] = slope[k];
         }
     }
 
@@ -622,7 +634,6 @@ int preprocess(const double* xyz, int64_t nv, const int32_t* tets, int64_t nc,
               [&](int64_t r) { return M.nidx[M.nptr[r]]; }, M.node);
     if (!no_matrix)
         pack_sell(M.sptr, M.sidx, nullptr, &M.klen, nc, [](int64_t r) { return (int32_t)r; }, M.kmat);
-    pack_sell(M.eptr, M.eidx, nullptr, nullptr, nc, [](int64_t r) { return (int32_t)r; }, M.enbr);
 
     mark("slicing");
     // -- 14. tiles and their halos -------------------------------------------------
@@ -662,119 +673,142 @@ int preprocess(const double* xyz, int64_t nv, const int32_t* tets, int64_t nc,
     }
     if (M.halo_max > kHaloCap) { err = "stencil neighbourhood too large for the LDS tile"; return E_MESH; }
     mark("tile halos");
-    // vertices of each tile (vertices are ordered by their lowest cell)
-    {
-        const int64_t nt = (int64_t)M.h_self.size();
-        M.v_off.assign(nt + 1, 0);
-        for (int64_t v = 0; v < nv; ++v) M.v_off[vmin[vnew2old[v]] / M.tile_rows + 1]++;
-        for (int64_t t = 0; t < nt; ++t) M.v_off[t + 1] += M.v_off[t];
-    }
     // global -> local through a dense map filled for one tile at a time
-    M.n_lidx.assign(M.node.idx.size(), 0);
     M.k_lidx.assign(M.kmat.idx.size(), 0);
-    M.c2n_l.assign(4 * nc, 0);
-    M.e_lidx.assign(M.enbr.idx.size(), 0);
-    M.c2v_l.assign(4 * nc, 0);
-    std::vector<int64_t> fptr(1, 0);
-    std::vector<int32_t> fent;                 // foreign lists, local halo indices
-    M.fv_off.assign(M.h_self.size() + 1, 0);
-    M.fv_idx.clear();
-    M.fv_len.clear();
-    M.tv_max = 0;
+    std::vector<int32_t> g2l(nc + nb, -1);
     const auto& cell_verts = T;
-    {
-        std::vector<int32_t> g2l(nc + nb, -1);
-        std::vector<int32_t> v2l(nv, -1);
+    if (!no_matrix) {
         const int64_t T = M.tile_rows;
-        const int64_t nt = (int64_t)M.h_self.size();
-        for (int64_t t = 0; t < nt; ++t) {
+        for (int64_t t = 0; t < (int64_t)M.h_self.size(); ++t) {
             for (int64_t h = M.h_off[t]; h < M.h_off[t + 1]; ++h) g2l[M.h_idx[h]] = int32_t(h - M.h_off[t]);
-            const int64_t t0 = t * T, t1 = std::min(nc, t0 + T);
-            for (int64_t r = t0; r < t1; ++r) {
-                const int64_t sl = r >> 6;
-                const int lane = int(r & 63);
-                for (int64_t k = 0; !no_matrix && k < M.kmat.width[sl]; ++k) {
-                    const int64_t at = M.kmat.off[sl] + k * 64 + lane;
+            for (int64_t r = t * T; r < std::min(nc, t * T + T); ++r)
+                for (int64_t k = 0; k < M.kmat.width[r >> 6]; ++k) {
+                    const int64_t at = M.kmat.off[r >> 6] + k * 64 + (r & 63);
                     M.k_lidx[at] = (uint16_t)g2l[M.kmat.idx[at]];
                 }
-                for (int k = 0; k < 4; ++k) M.c2n_l[k * nc + r] = (uint16_t)g2l[M.c2n[k * nc + r]];
-                for (int64_t k = 0; k < M.enbr.width[sl]; ++k) {
-                    const int64_t at = M.enbr.off[sl] + k * 64 + lane;
-                    M.e_lidx[at] = (uint16_t)g2l[M.enbr.idx[at]];
-                }
-            }
-            // vertices the tile's cells touch: own first, then foreign (sorted)
-            const int64_t own = M.v_off[t + 1] - M.v_off[t];
-            for (int64_t v = M.v_off[t]; v < M.v_off[t + 1]; ++v) v2l[v] = int32_t(v - M.v_off[t]);
-            const size_t fbeg = M.fv_idx.size();
-            for (int64_t r = t0; r < t1; ++r) {
-                const auto& tt = cell_verts[new2old[r]];
-                for (int k = 0; k < 4; ++k) {
-                    const int32_t v = vold2new[tt[k]];
-                    if (v2l[v] == -1) { v2l[v] = -2; M.fv_idx.push_back(v); }
-                }
-            }
-            std::sort(M.fv_idx.begin() + fbeg, M.fv_idx.end());
-            for (size_t q = fbeg; q < M.fv_idx.size(); ++q) {
-                const int32_t v = M.fv_idx[q];
-                v2l[v] = int32_t(own + int64_t(q - fbeg));
-                M.fv_len.push_back(M.n_len[v]);
-                for (int64_t e = M.nptr[v]; e < M.nptr[v + 1]; ++e) {
-                    const int32_t l = g2l[M.nidx[e]];
-                    if (l < 0) { err = "internal error: vertex list outside the tile halo"; return E_MESH; }
-                    fent.push_back(l);
-                }
-                fptr.push_back((int64_t)fent.size());
-            }
-            M.fv_off[t + 1] = (int64_t)M.fv_idx.size();
-            M.tv_max = std::max<int32_t>(M.tv_max, int32_t(own + int64_t(M.fv_idx.size() - fbeg)));
-            for (int64_t r = t0; r < t1; ++r) {
-                const auto& tt = cell_verts[new2old[r]];
-                for (int k = 0; k < 4; ++k) M.c2v_l[k * nc + r] = (uint16_t)v2l[vold2new[tt[k]]];
-            }
-            for (int64_t v = M.v_off[t]; v < M.v_off[t + 1]; ++v) v2l[v] = -1;
-            for (size_t q = fbeg; q < M.fv_idx.size(); ++q) v2l[M.fv_idx[q]] = -1;
-            for (int64_t v = M.v_off[t]; v < M.v_off[t + 1]; ++v) {
-                const int64_t sl = v >> 6;
-                const int lane = int(v & 63);
-                for (int64_t k = 0; k < M.node.width[sl]; ++k) {
-                    const int64_t at = M.node.off[sl] + k * 64 + lane;
-                    const int32_t l = g2l[M.node.idx[at]];
-                    if (l < 0) { err = "internal error: vertex list outside its tile halo"; return E_MESH; }
-                    M.n_lidx[at] = (uint16_t)l;
-                }
-            }
             for (int64_t h = M.h_off[t]; h < M.h_off[t + 1]; ++h) g2l[M.h_idx[h]] = -1;
         }
     }
-    {   // foreign vertex lists in 64-row slices (pad = the row's first entry)
-        const int64_t nfr = (int64_t)M.fv_idx.size();
-        pack_sell(fptr, fent, nullptr, nullptr, nfr, [&](int64_t r) { return fent[fptr[r]]; }, M.fnode);
-        M.f_lidx.assign(M.fnode.idx.begin(), M.fnode.idx.end());
-        M.fnode.idx.clear();
-        M.fnode.idx.shrink_to_fit();
+    {   // vertices a tile of tile_rows cells touches that another tile owns (reported)
+        std::vector<int64_t> tile_of(nv, -1);
+        M.foreign_rows = M.foreign_entries = 0;
+        M.tv_max = 0;
+        int32_t here = 0;
+        for (int64_t r = 0; r < nc; ++r) {
+            const int64_t t = r / M.tile_rows;
+            if (r % M.tile_rows == 0) here = 0;
+            for (int k = 0; k < 4; ++k) {
+                const int32_t v = vold2new[cell_verts[new2old[r]][k]];
+                if (tile_of[v] == t) continue;
+                if (tile_of[v] != -1) {
+                    ++M.foreign_rows;
+                    M.foreign_entries += M.n_len[v];
+                }
+                tile_of[v] = t;
+                M.tv_max = std::max(M.tv_max, ++here);
+            }
+        }
     }
-    mark("local indices");
-    // every local index must name the same entity as the global one
-    auto verify = [&](const Sell64& sl, const std::vector<uint16_t>& loc) -> bool {
-        for (int64_t s_ = 0; s_ < sl.nslices; ++s_)
-            for (int lane = 0; lane < 64; ++lane) {
-                const int64_t r = s_ * 64 + lane;
-                if (r >= nc) continue;
-                const int64_t t = r / M.tile_rows;
-                for (int64_t k = 0; k < sl.width[s_]; ++k) {
-                    const int64_t at = sl.off[s_] + k * 64 + lane;
-                    if (int64_t(loc[at]) >= M.h_off[t + 1] - M.h_off[t] || M.h_idx[M.h_off[t] + loc[at]] != sl.idx[at])
-                        return false;
+    mark("matrix indices");
+    // -- 15. gradient tiles ----------------------------------------------------------
+    // The halo of a gradient tile: its cells, and the cells and ghosts that
+    // share an edge or a face with one; the vertices its cells touch.
+    {
+        const int64_t T = M.tile_rows, nt = (nc + T - 1) / T;
+        M.g_rows = int32_t(T);
+        M.g_off.assign(nt + 1, 0);
+        M.g_idx.clear();
+        M.g_idx.reserve(size_t(nc) * 3);
+        M.g_self.assign(nt, 0);
+        M.gv_off.assign(nt + 1, 0);
+        M.gv_idx.clear();
+        M.gv_idx.reserve(size_t(nc) / 2 + 4);
+        M.g_max = M.gv_max = 0;
+        M.g_cell.assign(8 * nc, 0);
+        const int64_t ns = (nc + 63) / 64;
+        M.ge_off.assign(ns + 1, 0);
+        for (int64_t s = 0; s < ns; ++s) {
+            int64_t w = 0;
+            for (int64_t r = s * 64; r < std::min(nc, s * 64 + 64); ++r) w = std::max(w, M.eptr[r + 1] - M.eptr[r]);
+            M.ge_off[s + 1] = M.ge_off[s] + (w + 7) / 8 * 64;
+        }
+        M.ge_idx.assign(8 * M.ge_off[ns], 0);
+        std::fill(seen.begin(), seen.end(), -1);
+        std::vector<int32_t> v2l(nv, -1), buf;
+        for (int64_t t = 0; t < nt; ++t) {
+            const int64_t t0 = t * T, t1 = std::min(nc, t0 + T);
+            buf.clear();
+            auto take = [&](int32_t e) {
+                if (seen[e] != t) {
+                    seen[e] = t;
+                    buf.push_back(e);
+                }
+            };
+            for (int64_t r = t0; r < t1; ++r) take(int32_t(r));
+            for (int64_t e = M.eptr[t0]; e < M.eptr[t1]; ++e) take(M.eidx[e]);
+            for (int64_t r = t0; r < t1; ++r)
+                for (int k = 0; k < 4; ++k) take(M.c2n[k * nc + r]);
+            std::sort(buf.begin(), buf.end());
+            for (size_t h = 0; h < buf.size(); ++h) g2l[buf[h]] = int32_t(h);
+            M.g_self[t] = g2l[t0];
+            M.g_idx.insert(M.g_idx.end(), buf.begin(), buf.end());
+            M.g_off[t + 1] = (int64_t)M.g_idx.size();
+            M.g_max = std::max<int32_t>(M.g_max, (int32_t)buf.size());
+            buf.clear();
+            for (int64_t r = t0; r < t1; ++r)
+                for (int k = 0; k < 4; ++k) {
+                    const int32_t v = vold2new[cell_verts[new2old[r]][k]];
+                    if (v2l[v] == -1) {
+                        v2l[v] = 0;
+                        buf.push_back(v);
+                    }
+                }
+            std::sort(buf.begin(), buf.end());
+            for (size_t q = 0; q < buf.size(); ++q) v2l[buf[q]] = int32_t(q);
+            M.gv_idx.insert(M.gv_idx.end(), buf.begin(), buf.end());
+            M.gv_off[t + 1] = (int64_t)M.gv_idx.size();
+            M.gv_max = std::max<int32_t>(M.gv_max, (int32_t)buf.size());
+            for (int64_t r = t0; r < t1; ++r) {
+                for (int k = 0; k < 4; ++k) {
+                    const int32_t code = M.c2f[k * nc + r], f = code >= 0 ? code : ~code;
+                    // the vertex across from face k
+                    int32_t opp = -1;
+                    for (int q = 0; q < 4; ++q) {
+                        const int32_t v = vold2new[cell_verts[new2old[r]][q]];
+                        if (v != M.fA[f] && v != M.fB[f] && v != M.fC[f]) opp = v;
+                    }
+                    M.g_cell[8 * r + k] = (uint16_t)g2l[M.c2n[k * nc + r]];
+                    M.g_cell[8 * r + 4 + k] = (uint16_t)v2l[opp];
+                }
+                const int64_t s = r >> 6, w = (M.ge_off[s + 1] - M.ge_off[s]) / 64 * 8, n = M.eptr[r + 1] - M.eptr[r];
+                for (int64_t k = 0; k < w; ++k) {
+                    const int32_t e = k < n ? M.eidx[M.eptr[r] + k] : int32_t(r);
+                    M.ge_idx[8 * (M.ge_off[s] + (k >> 3) * 64 + (r & 63)) + (k & 7)] = (uint16_t)g2l[e];
                 }
             }
-        return true;
-    };
-    bool ok = verify(M.kmat, M.k_lidx) && verify(M.enbr, M.e_lidx);
-    for (int64_t i = 0; ok && i < nc; ++i) {
-        const int64_t t = i / M.tile_rows;
-        ok = M.h_idx[M.h_off[t] + M.h_self[t] + (i - t * M.tile_rows)] == i;
-        for (int k = 0; ok && k < 4; ++k) ok = M.h_idx[M.h_off[t] + M.c2n_l[k * nc + i]] == M.c2n[k * nc + i];
+            for (int32_t v : buf) v2l[v] = -1;
+            for (int64_t h = M.g_off[t]; h < M.g_off[t + 1]; ++h) g2l[M.g_idx[h]] = -1;
+        }
+    }
+    mark("gradient tiles");
+    // every local index must name the same entity as the global one
+    bool ok = true;
+    for (int64_t r = 0; ok && r < nc; ++r) {
+        const int64_t t = r / M.tile_rows, h0 = M.h_off[t], hn = M.h_off[t + 1] - h0;
+        ok = M.h_idx[h0 + M.h_self[t] + (r - t * M.tile_rows)] == r;
+        for (int64_t k = 0; ok && !no_matrix && k < M.kmat.width[r >> 6]; ++k) {
+            const int64_t at = M.kmat.off[r >> 6] + k * 64 + (r & 63);
+            ok = int64_t(M.k_lidx[at]) < hn && M.h_idx[h0 + M.k_lidx[at]] == M.kmat.idx[at];
+        }
+        const int64_t g = r / M.g_rows, g0 = M.g_off[g], gn = M.g_off[g + 1] - g0;
+        ok = ok && M.g_idx[g0 + M.g_self[g] + (r - g * M.g_rows)] == r;
+        for (int k = 0; ok && k < 4; ++k)
+            ok = int64_t(M.g_cell[8 * r + k]) < gn && M.g_idx[g0 + M.g_cell[8 * r + k]] == M.c2n[k * nc + r] &&
+                 int64_t(M.g_cell[8 * r + 4 + k]) < M.gv_off[g + 1] - M.gv_off[g];
+        for (int64_t k = 0; ok && k < M.eptr[r + 1] - M.eptr[r]; ++k) {
+            const int64_t at = 8 * (M.ge_off[r >> 6] + (k >> 3) * 64 + (r & 63)) + (k & 7);
+            ok = int64_t(M.ge_idx[at]) < gn && M.g_idx[g0 + M.ge_idx[at]] == M.eidx[M.eptr[r] + k];
+        }
     }
     if (!ok) { err = "internal error: tile-local index mismatch"; return E_MESH; }
     mark("verification");

@@ -64,33 +64,35 @@ struct Mesh {
     std::vector<int32_t> h_idx;       // halo entities
     std::vector<int32_t> h_self;      // ntiles: local index of the tile's first cell
     std::vector<uint16_t> k_lidx;     // like kmat.idx, local
-    std::vector<uint16_t> c2n_l;      // 4 x nc local index of the face neighbour
-    // vertices are numbered by their lowest cell, so the vertices of tile t
-    // (those whose lowest cell lies in it) are [v_off[t], v_off[t+1]); their
-    // cell/ghost lists lie inside the tile's halo
-    std::vector<int64_t> v_off;       // ntiles + 1
-    std::vector<uint16_t> n_lidx;     // like node.idx, local to the owning tile
     // Star-moment form of the gradient sum of Algorithm 1.  An entity of the
     // stencil of cell i shares m in {1, 2, 3} vertices with i, so the sum
     // over the stencil equals the sum over the 4 vertex lists of i minus
     // (m - 1) times each entity with m > 1: the entities sharing exactly an
     // edge (m = 2, listed here) and the 4 face neighbours (m = 3, c2n).
     std::vector<int64_t> eptr; std::vector<int32_t> eidx;   // edge-only neighbours, CSR
-    Sell64 enbr;                      // the same, pad = the row itself
-    std::vector<uint16_t> e_lidx;     // like enbr.idx, local to the tile
     int32_t enbr_max = 0;
+    // per vertex (4 doubles each): its position, its list's mean position and
+    // length, and the slope b of its least-squares weights
+    // alpha_e = 1/n + b . (x_e - mean)
     std::vector<int32_t> n_len;       // nv: vertex list lengths
-    // Vertices a tile's cells touch: the tile's own ([v_off[t], v_off[t+1]))
-    // and the foreign ones, listed per tile with their vertex lists in the
-    // tile's local halo indices (pad = first entry).  Tile-local vertex
-    // number: own v -> v - v_off[t], foreign row r -> own count + r - fv_off[t].
-    std::vector<int64_t> fv_off;      // ntiles + 1
-    std::vector<int32_t> fv_idx;      // foreign vertex ids
-    std::vector<int32_t> fv_len;      // their list lengths
-    Sell64 fnode;                     // their lists, idx local (stored in f_lidx)
-    std::vector<uint16_t> f_lidx;
-    std::vector<uint16_t> c2v_l;      // 4 x nc tile-local vertex number
-    int32_t tv_max = 0;               // most vertices touched by one tile
+    std::vector<double> vpos, vmean, vslope;
+    // Gradient tiles of g_rows consecutive cells: the halo (sorted; the cells
+    // and the entities sharing an edge or a face with one), the vertices the
+    // cells touch (sorted), and the local indices a cell reads: g_cell[8 i]
+    // its 4 face neighbours (c2f order), then its 4 vertices, k across from
+    // face k; its edge-only neighbours in groups of 8, group q of row
+    // 64 s + lane at ge_idx[8 (ge_off[s] + 64 q + lane)], padded with the
+    // cell itself.
+    int32_t g_rows = 256, g_max = 0, gv_max = 0;
+    std::vector<int64_t> g_off, gv_off;
+    std::vector<int32_t> g_idx, g_self, gv_idx;
+    std::vector<uint16_t> g_cell;
+    std::vector<int64_t> ge_off;
+    std::vector<uint16_t> ge_idx;
+    // vertices that tiles of tile_rows cells touch and another tile owns, and
+    // their list entries; the most vertices one of these tiles touches
+    int64_t foreign_rows = 0, foreign_entries = 0;
+    int32_t tv_max = 0;
     // tiles of the network's fused forward, built on first use
     mutable std::shared_ptr<const NnTiles> nn_tiles;
 };

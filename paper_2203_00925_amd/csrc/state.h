@@ -42,7 +42,6 @@ struct Dev {
     // cells
     double *vol, *xc;                     // xc: 3 x (nc+nb)
     double4* xyz4;                        // nc+nb centres as (x, y, z, 0) records
-    double4* fx4;                         // nf face centroids as (x, y, z, 0) records
     double* minv;                         // 6 x nc
     int32_t *c2f, *c2n;                   // 4 x nc
     int64_t* s_off; int32_t* s_w; int32_t* s_idx;
@@ -66,15 +65,17 @@ struct Dev {
     int32_t tile_rows, halo_max;
     int64_t ntiles;
     int64_t* h_off; int32_t* h_idx; int32_t* h_self;
-    uint16_t *k_lidx, *c2n_l, *n_lidx;
-    int64_t* v_off;
-    // star-moment gradient: edge-only neighbours (64-row slices, local),
-    // tile-local vertex numbers, the foreign vertices of each tile
-    int32_t tv_max;
-    int64_t* e_off; int32_t* e_w; uint16_t* e_lidx;
-    uint16_t* c2v_l;
-    int64_t* fv_off; int32_t* fv_len;
-    int64_t* f_off; int32_t* f_w; uint16_t* f_lidx;
+    uint16_t* k_lidx;
+    // star-moment gradient (mesh.h): the tiles' halos and vertices, a cell's
+    // local indices (one 16-byte record; edge-only neighbours 8 to a record),
+    // the vertices' static records and, per stage, (C, ub) of each list
+    int32_t g_rows, g_max, gv_max;
+    int64_t g_tiles;
+    int64_t *g_off, *gv_off, *ge_off;
+    int32_t *g_idx, *g_self, *gv_idx;
+    uint4 *g_cell, *ge_idx;
+    double4 *vpos, *vmean, *vslope, *vmom;
+    float4* vmom32;
     // renumbering
     int32_t *cell_perm, *vert_perm;       // internal -> user
     // fields
@@ -126,6 +127,10 @@ struct Dev {
     double* scal;                         // solver scalars, [nm][SC_COUNT_]
 };
 
+template <class R> struct Vec4T;
+template <> struct Vec4T<double> { using T = double4; };
+template <> struct Vec4T<float> { using T = float4; };
+
 // The arrays one precision of the step reads and writes.
 template <class R>
 struct FvArrays {
@@ -134,6 +139,7 @@ struct FvArrays {
     // the per-cell stage: face values [4][nc], vertex and kRL weights, outward phi
     R* uf;
     const R *cw, *cr, *cphi;
+    typename Vec4T<R>::T* vmom;           // [nv] moments of the vertex lists
 };
 
 constexpr int kNumKernels = 22;
@@ -216,6 +222,9 @@ size_t layout(const Mesh& m, char* base, Dev& d);
 
 // launchers (fv_kernels.hip)
 hipError_t launch_ghost_fill(const Dev& d, bool fp32, const BcTable& bc, hipStream_t s);
+// moments and least-squares values of every vertex's list, from u_in (the
+// state's u in the step's precision if null); the gradient reads them
+hipError_t launch_vertex_moments(const Dev& d, bool fp32, hipStream_t s, const void* u_in = nullptr);
 // parts: write the gradient and limiter arrays (the face kernel reads
 // them); without parts, the per-face MUSCL values of the cell step instead,
 // from u_in (the state's u in the step's precision if null)
