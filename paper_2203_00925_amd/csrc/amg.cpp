@@ -240,36 +240,83 @@ int amg_build(AmgCsr&& A, double theta, int max_levels, int64_t coarse_max, doub
     return 0;
 }
 
-void amg_pack(const AmgCsr& A, Sell64& off, std::vector<double>& diag) {
-    const int64_t n = A.n;
-    diag.assign(n, 0.0);
-    off.nslices = (n + 63) / 64;
-    off.off.assign(off.nslices + 1, 0);
-    off.width.assign(off.nslices, 0);
-    std::vector<int32_t> len(n, 0);
-    for (int64_t i = 0; i < n; ++i)
-        for (int64_t e = A.ptr[i]; e < A.ptr[i + 1]; ++e) {
-            if (A.col[e] == i) diag[i] += A.val[e];
-            else len[i]++;
+void amg_pack(const AmgHierarchy& h, std::vector<AmgPacked>& out) {
+    const int nl = int(h.lv.size());
+    out.assign(nl, AmgPacked());
+    std::vector<int32_t> inv;                             // the coarser level's rows, old -> new
+    for (int l = nl - 1; l >= 0; --l) {
+        const AmgLevel& L = h.lv[l];
+        AmgPacked& P = out[l];
+        const int64_t n = L.A.n;
+        std::vector<int32_t> order(n);                    // new -> old
+        if (l == nl - 1) {
+            for (int64_t i = 0; i < n; ++i) order[i] = int32_t(i);
+        } else {
+            P.mptr.assign(L.ncoarse + 1, 0);
+            for (int64_t i = 0; i < n; ++i) P.mptr[inv[L.agg[i]] + 1]++;
+            for (int64_t k = 0; k < L.ncoarse; ++k) P.mptr[k + 1] += P.mptr[k];
+            std::vector<int32_t> pos(P.mptr.begin(), P.mptr.end() - 1);
+            for (int64_t i = 0; i < n; ++i) order[pos[inv[L.agg[i]]]++] = int32_t(i);
         }
-    for (int64_t s = 0; s < off.nslices; ++s) {
-        int32_t w = 0;
-        for (int64_t r = s * 64; r < std::min(n, s * 64 + 64); ++r) w = std::max(w, len[r]);
-        off.width[s] = w;
-        off.off[s + 1] = off.off[s] + int64_t(w) * 64;
-    }
-    off.idx.assign(off.off[off.nslices], 0);
-    off.val.assign(off.off[off.nslices], 0.0);
-    for (int64_t i = 0; i < n; ++i) {
-        const int64_t s = i >> 6, lane = i & 63;
-        int64_t k = 0;
-        for (int64_t e = A.ptr[i]; e < A.ptr[i + 1]; ++e) {
-            if (A.col[e] == i) continue;
-            off.idx[off.off[s] + k * 64 + lane] = A.col[e];
-            off.val[off.off[s] + k * 64 + lane] = A.val[e];
-            ++k;
+        if (l == 0) {                                     // the state's cells keep their order
+            P.midx = nl > 1 ? order : std::vector<int32_t>();
+            break;
         }
-        for (; k < off.width[s]; ++k) off.idx[off.off[s] + k * 64 + lane] = int32_t(i);   // value 0
+        std::vector<int32_t> here(n);
+        for (int64_t i = 0; i < n; ++i) here[order[i]] = int32_t(i);
+        P.diag.assign(n, 0.0);
+        std::vector<int32_t> len(n, 0);
+        for (int64_t r = 0; r < n; ++r) {
+            const int64_t i = order[r];
+            for (int64_t e = L.A.ptr[i]; e < L.A.ptr[i + 1]; ++e) {
+                if (L.A.col[e] == i) P.diag[r] += L.A.val[e];
+                else len[r]++;
+            }
+        }
+        if (l < nl - 1) {
+            // blocks of whole aggregates with at most 64 rows (one slice), or
+            // one larger aggregate over several slices
+            P.bslice.push_back(0);
+            P.bagg.push_back(0);
+            for (int64_t a = 0; a < L.ncoarse;) {
+                const int32_t r0 = P.mptr[a];
+                int64_t to = a + 1;
+                while (to < L.ncoarse && P.mptr[to + 1] - r0 <= 64) ++to;
+                for (int32_t r = r0; r < P.mptr[to]; r += 64) P.srow.push_back(r);
+                P.bslice.push_back(int32_t(P.srow.size()));
+                P.bagg.push_back(int32_t(to));
+                a = to;
+            }
+            P.srow.push_back(int32_t(n));
+            const int64_t ns = int64_t(P.srow.size()) - 1;
+            P.off.assign(ns + 1, 0);
+            P.width.assign(ns, 0);
+            for (int64_t q = 0; q < ns; ++q) {
+                for (int32_t r = P.srow[q]; r < P.srow[q + 1]; ++r) P.width[q] = std::max(P.width[q], len[r]);
+                P.off[q + 1] = P.off[q] + int64_t(P.width[q]) * 64;
+            }
+            P.idx.assign(P.off[ns], 0);
+            P.val.assign(P.off[ns], 0.0);
+            for_chunks(ns, setup_threads(n), [&](int, int64_t lo, int64_t hi) {
+                for (int64_t q = lo; q < hi; ++q)
+                    for (int64_t lane = 0; lane < 64; ++lane) {
+                        const int64_t r = P.srow[q] + lane;
+                        int64_t at = P.off[q] + lane, k = 0;
+                        if (r < P.srow[q + 1]) {
+                            const int64_t i = order[r];
+                            for (int64_t e = L.A.ptr[i]; e < L.A.ptr[i + 1]; ++e) {
+                                if (L.A.col[e] == i) continue;
+                                P.idx[at] = here[L.A.col[e]];
+                                P.val[at] = L.A.val[e];
+                                at += 64;
+                                ++k;
+                            }
+                        }
+                        for (; k < P.width[q]; ++k, at += 64) P.idx[at] = P.srow[q];   // value 0
+                    }
+            });
+        }
+        inv.swap(here);
     }
 }
 

@@ -63,6 +63,25 @@ struct AmgLevel {
     int64_t ncoarse = 0;
 };
 
+// A level as the device stores it.  The rows of the levels between the finest
+// and the coarsest are renumbered so that the members of an aggregate are
+// consecutive (ascending as before), the aggregates in the coarser level's new
+// order: a block of rows then holds whole aggregates, so one kernel forms a
+// residual and its restriction, and the owner of a coarse row prolongs to
+// consecutive rows.  The finest level keeps the state's order and lists its
+// members.
+struct AmgPacked {
+    std::vector<int32_t> mptr, midx;      // members of each next-level row (midx: finest level only)
+    std::vector<double> diag;
+    // off-diagonal entries: slice q holds rows [srow[q], srow[q+1]), at most
+    // 64, entry k of its row j at off[q] + 64 k + j (pad: value 0)
+    std::vector<int64_t> off;
+    std::vector<int32_t> width, srow, idx;
+    std::vector<double> val;
+    // block b: slices [bslice[b], bslice[b+1]), aggregates [bagg[b], bagg[b+1])
+    std::vector<int32_t> bslice, bagg;
+};
+
 struct AmgHierarchy {
     std::vector<AmgLevel> lv;             // lv[0] is the input matrix
     std::vector<double> cinv;             // dense inverse of the coarsest matrix, row-major
@@ -70,6 +89,7 @@ struct AmgHierarchy {
     int gamma = 1;                        // cycle of the device (1 V, 2 W)
     int max_levels = 10;
     int64_t coarse_max = 1024;
+    std::vector<AmgPacked> packed;        // device form, made when first asked for
 };
 
 // Builds the hierarchy of A (moved into lv[0]).  Returns 0 or a negative
@@ -77,8 +97,7 @@ struct AmgHierarchy {
 int amg_build(AmgCsr&& A, double theta, int max_levels, int64_t coarse_max, double omega, AmgHierarchy& H,
               std::string& err);
 
-// 64-row slices of a level's off-diagonal entries (pad: the row itself with
-// value 0) and its diagonal, as the device stores them.
-void amg_pack(const AmgCsr& A, Sell64& off, std::vector<double>& diag);
+// the device form of every level
+void amg_pack(const AmgHierarchy& h, std::vector<AmgPacked>& out);
 
 }  // namespace mifvm

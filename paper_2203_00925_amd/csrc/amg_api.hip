@@ -42,7 +42,7 @@ void fill_info(const AmgHierarchy& h, mifvm_amg_info* info) {
 }
 
 // device bytes of a hierarchy (level 0 lives in the state)
-size_t amg_layout(const AmgHierarchy& h, int64_t nc, char* base, AmgDev* a) {
+size_t amg_layout(const AmgHierarchy& h, int64_t nc, int64_t nv, char* base, AmgDev* a) {
     size_t off = 0;
     AmgDev tmp;
     AmgDev& A = a ? *a : tmp;
@@ -50,17 +50,19 @@ size_t amg_layout(const AmgHierarchy& h, int64_t nc, char* base, AmgDev* a) {
     A.omega = h.omega;
     A.gamma = h.gamma;
     for (int l = 0; l < A.nl; ++l) {
-        const AmgLevel& L = h.lv[l];
+        const AmgPacked& P = h.packed[l];
         AmgLevelDev& D = A.lv[l];
-        D.n = L.A.n;
+        D.n = h.lv[l].A.n;
         if (l >= 1) {
-            Sell64 s;
-            std::vector<double> diag;
-            amg_pack(L.A, s, diag);
-            D.off = carve<int64_t>(base, off, s.off.size());
-            D.w = carve<int32_t>(base, off, std::max<size_t>(s.width.size(), 1));
-            D.idx = carve<int32_t>(base, off, std::max<size_t>(s.idx.size(), 1));
-            D.val = carve<double>(base, off, std::max<size_t>(s.val.size(), 1));
+            D.nslices = int32_t(P.width.size());
+            D.nblk = int32_t(P.bslice.empty() ? 0 : P.bslice.size() - 1);
+            D.off = carve<int64_t>(base, off, P.off.size());
+            D.w = carve<int32_t>(base, off, P.width.size());
+            D.srow = carve<int32_t>(base, off, P.srow.size());
+            D.idx = carve<int32_t>(base, off, P.idx.size());
+            D.val = carve<double>(base, off, P.val.size());
+            D.bslice = carve<int32_t>(base, off, P.bslice.size());
+            D.bagg = carve<int32_t>(base, off, P.bagg.size());
             D.diag = carve<double>(base, off, D.n);
             D.dinv = carve<double>(base, off, D.n);
             D.b = carve<double>(base, off, D.n);
@@ -70,15 +72,15 @@ size_t amg_layout(const AmgHierarchy& h, int64_t nc, char* base, AmgDev* a) {
             D.e = carve<double>(base, off, D.n);
         }
         if (l + 1 < A.nl) {
-            D.agg = carve<int32_t>(base, off, D.n);
-            D.mptr = carve<int64_t>(base, off, L.ncoarse + 1);
-            D.midx = carve<int32_t>(base, off, D.n);
+            D.mptr = carve<int32_t>(base, off, P.mptr.size());
+            if (l == 0) D.midx = carve<int32_t>(base, off, P.midx.size());
         }
     }
     A.cinv = carve<double>(base, off, h.cinv.size());
     A.r_old = carve<double>(base, off, nc);
     A.s0 = carve<double>(base, off, nc);
     A.s1 = carve<double>(base, off, nc);
+    A.zv = carve<double>(base, off, nv);
     return (off + 255) & ~size_t(255);
 }
 
@@ -142,7 +144,7 @@ int amg_phase(State& s, double tol, int maxit, int chunk, int restart, bool use_
     const AmgSmoother* fine = learned ? &nn : nullptr;
     auto open = [&](bool fresh) -> int {
         HIPCHK(timed(tm, MIFVM_K_CG_SETUP, hs,
-                     [&] { return launch_amg_open(d, bc, a, tol, maxit, restart, fresh, hs, fine); }));
+                     [&] { return launch_amg_open(d, bc, a, tol, maxit, restart, fresh, matrix_free, hs, fine); }));
         return pull();
     };
     const int key = chunk + (matrix_free ? 1 << 20 : 0) + (learned ? 1 << 21 : 0);
@@ -201,11 +203,12 @@ int mifvm_amg_build(mifvm_state* st, const mifvm_amg_opts* opts, mifvm_amg_info*
     rc = amg_build(std::move(A), theta, levels, cmax, omega, *h, err);
     if (rc) return fail(rc, err);
     h->gamma = opts && opts->cycle == 2 ? 2 : 1;
+    amg_pack(*h, h->packed);
     amg_release(s);
     s.amg_host = h.release();
     if (info) {
         fill_info(*s.amg_host, info);
-        info->ws_bytes = amg_layout(*s.amg_host, s.d.nc, nullptr, nullptr);
+        info->ws_bytes = amg_layout(*s.amg_host, s.d.nc, s.d.nv, nullptr, nullptr);
         info->setup_ms = std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - t0).count();
     }
     return MIFVM_OK;
@@ -223,45 +226,35 @@ int mifvm_amg_attach(mifvm_state* st, void* d_ws, size_t ws_bytes, void* stream)
     }
     if (!s.amg_host) return fail(MIFVM_E_STATE, "no hierarchy: call mifvm_amg_build first");
     const AmgHierarchy& h = *s.amg_host;
-    const size_t need = amg_layout(h, s.d.nc, nullptr, nullptr);
+    const size_t need = amg_layout(h, s.d.nc, s.d.nv, nullptr, nullptr);
     if (ws_bytes < need || (reinterpret_cast<uintptr_t>(d_ws) & 255))
         return fail(MIFVM_E_WORKSPACE, "multigrid workspace too small or misaligned: need " + std::to_string(need));
     auto a = std::make_unique<AmgDev>();
-    amg_layout(h, s.d.nc, static_cast<char*>(d_ws), a.get());
+    amg_layout(h, s.d.nc, s.d.nv, static_cast<char*>(d_ws), a.get());
     hipStream_t hs = S(stream);
+    std::vector<std::vector<double>> dinv(a->nl);   // outlives the copies
+    for (int l = 1; l < a->nl; ++l)
+        for (double v : h.packed[l].diag) {
+            if (!(v != 0.0) || !std::isfinite(v))
+                return fail(MIFVM_E_STATE, "zero or non-finite diagonal on a coarse level");
+            dinv[l].push_back(1.0 / v);
+        }
     for (int l = 0; l < a->nl; ++l) {
-        const AmgLevel& L = h.lv[l];
+        const AmgPacked& P = h.packed[l];
         AmgLevelDev& D = a->lv[l];
         if (l >= 1) {
-            Sell64 sl;
-            std::vector<double> diag;
-            amg_pack(L.A, sl, diag);
-            std::vector<double> dinv(diag.size());
-            for (size_t i = 0; i < diag.size(); ++i) {
-                if (!(diag[i] != 0.0) || !std::isfinite(diag[i]))
-                    return fail(MIFVM_E_STATE, "zero or non-finite diagonal on a coarse level");
-                dinv[i] = 1.0 / diag[i];
-            }
-            HIPCHK(up(D.off, sl.off, hs));
-            HIPCHK(up(D.w, sl.width, hs));
-            HIPCHK(up(D.idx, sl.idx, hs));
-            HIPCHK(up(D.val, sl.val, hs));
-            HIPCHK(up(D.diag, diag, hs));
-            HIPCHK(up(D.dinv, dinv, hs));
-            HIPCHK(hipStreamSynchronize(hs));       // the packed host vectors are freed here
+            HIPCHK(up(D.off, P.off, hs));
+            HIPCHK(up(D.w, P.width, hs));
+            HIPCHK(up(D.srow, P.srow, hs));
+            HIPCHK(up(D.idx, P.idx, hs));
+            HIPCHK(up(D.val, P.val, hs));
+            HIPCHK(up(D.bslice, P.bslice, hs));
+            HIPCHK(up(D.bagg, P.bagg, hs));
+            HIPCHK(up(D.diag, P.diag, hs));
+            HIPCHK(up(D.dinv, dinv[l], hs));
         }
-        if (l + 1 < a->nl) {
-            std::vector<int64_t> mptr(L.ncoarse + 1, 0);
-            for (int32_t g : L.agg) mptr[g + 1]++;
-            for (int64_t k = 0; k < L.ncoarse; ++k) mptr[k + 1] += mptr[k];
-            std::vector<int32_t> midx(L.A.n);
-            std::vector<int64_t> pos(mptr.begin(), mptr.end() - 1);
-            for (int64_t i = 0; i < L.A.n; ++i) midx[pos[L.agg[i]]++] = int32_t(i);
-            HIPCHK(up(D.agg, L.agg, hs));
-            HIPCHK(up(D.mptr, mptr, hs));
-            HIPCHK(up(D.midx, midx, hs));
-            HIPCHK(hipStreamSynchronize(hs));
-        }
+        HIPCHK(up(D.mptr, P.mptr, hs));
+        HIPCHK(up(D.midx, P.midx, hs));
     }
     HIPCHK(up(a->cinv, h.cinv, hs));
     HIPCHK(hipStreamSynchronize(hs));

@@ -13,20 +13,17 @@ namespace mifvm {
 
 struct AmgLevelDev {
     int64_t n = 0;
-    // level >= 1: off-diagonal entries in 64-row slices, diagonal, inverse diagonal
+    // levels between the finest and the coarsest (amg.h, AmgPacked)
+    int32_t nslices = 0, nblk = 0;
     int64_t* off = nullptr;
-    int32_t* w = nullptr;
-    int32_t* idx = nullptr;
+    int32_t *w = nullptr, *srow = nullptr, *idx = nullptr, *bslice = nullptr, *bagg = nullptr;
     double* val = nullptr;
-    double* diag = nullptr;
-    double* dinv = nullptr;
-    // every level but the coarsest: row -> aggregate, and the members of each
-    // aggregate (CSR over the next level's rows)
-    int32_t* agg = nullptr;
-    int64_t* mptr = nullptr;
-    int32_t* midx = nullptr;
-    // level >= 1: right-hand side, iterate, product; the W-cycle's second
-    // visit: its right-hand side (residual) and correction
+    double *diag = nullptr, *dinv = nullptr;
+    // every level but the coarsest: the members of each aggregate (consecutive
+    // rows, or listed in midx on the finest level)
+    int32_t *mptr = nullptr, *midx = nullptr;
+    // level >= 1: right-hand side, iterate, first visit's result; a second
+    // visit's right-hand side and iterate
     double *b = nullptr, *x = nullptr, *t = nullptr, *r = nullptr, *e = nullptr;
 };
 
@@ -37,7 +34,8 @@ struct AmgDev {
     AmgLevelDev lv[kAmgMaxLevels];
     double* cinv = nullptr;           // dense inverse of the coarsest matrix, row-major
     double* r_old = nullptr;          // flexible CG [nc]
-    double *s0 = nullptr, *s1 = nullptr;   // finest-level scratch of a learned smoother [nc]
+    double *s0 = nullptr, *s1 = nullptr;   // finest level: the smoothed iterate, its residual [nc]
+    double* zv = nullptr;             // its vertex values [nv]
 };
 
 // out = M(in) on the finest level: a learned smoother replacing the Jacobi
@@ -49,9 +47,10 @@ using AmgSmoother = std::function<hipError_t(const double* in, double* out, hipS
 hipError_t launch_amg_cycle(const Dev& d, const BcTable& bc_pot, const AmgDev& a, const double* b0, double* x0,
                             const double* flag, hipStream_t s, const AmgSmoother* fine = nullptr);
 // open (or reopen) the flexible CG: r = b - K x, the convergence tests,
-// z = V(r), p = z, rz
+// z = V(r), p = z, rz (matrix_free: what the iteration's product needs of p)
 hipError_t launch_amg_open(const Dev& d, const BcTable& bc_pot, const AmgDev& a, double tol, int maxit,
-                           int restart, bool fresh, hipStream_t s, const AmgSmoother* fine = nullptr);
+                           int restart, bool fresh, bool matrix_free, hipStream_t s,
+                           const AmgSmoother* fine = nullptr);
 // one iteration: q = K p (matrix-free or stored), x, r, the tests, z = V(r),
 // Polak-Ribiere beta, p = z + beta p
 hipError_t launch_amg_iteration(const Dev& d, const BcTable& bc_pot, const AmgDev& a, bool matrix_free,

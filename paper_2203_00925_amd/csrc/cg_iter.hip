@@ -22,100 +22,12 @@
 #include <algorithm>
 
 #include "cg_iter.h"
+#include "cg_dev.h"
 #include "halo_stage.h"
 #include "mf_cell.h"
-#include "reduce.h"
-#include "seg.h"
-#include "state.h"
-#include "xcd.h"
 
 namespace mifvm {
 namespace {
-
-constexpr int kMaxWaves = 8;              // 512 threads
-
-template <class R> struct CgVec;
-template <> struct CgVec<double> {
-    __device__ static double *x(const Dev& d) { return d.x; }
-    __device__ static double *r(const Dev& d) { return d.r; }
-    __device__ static double *z(const Dev& d) { return d.z; }
-    __device__ static double *p(const Dev& d) { return d.p; }
-    __device__ static double *q(const Dev& d) { return d.q; }
-    __device__ static const double *dinv(const Dev& d) { return d.k_dinv; }
-    __device__ static const double *diag(const Dev& d) { return d.k_diag; }
-    __device__ static const double *val(const Dev& d) { return d.k_val; }
-    __device__ static const double *alpha(const Dev& d) { return d.n_alpha; }
-};
-template <> struct CgVec<float> {
-    __device__ static float *x(const Dev& d) { return d.d32; }
-    __device__ static float *r(const Dev& d) { return d.r32; }
-    __device__ static float *z(const Dev& d) { return d.z32; }
-    __device__ static float *p(const Dev& d) { return d.p32; }
-    __device__ static float *q(const Dev& d) { return d.q32; }
-    __device__ static const float *dinv(const Dev& d) { return d.k_dinv32; }
-    __device__ static const float *diag(const Dev& d) { return d.k_diag32; }
-    __device__ static const float *val(const Dev& d) { return d.k_val32; }
-    __device__ static const float *alpha(const Dev& d) { return d.n_alpha32; }
-};
-
-// a block's rows, its mesh's scalars and the partials it adds (the mesh's)
-struct Seg {
-    int64_t r0, r1;
-    double* sc;
-    int p0, np, pp0, pnp;                 // first and count: the vector kernels', the product's
-    bool lead;                            // the mesh's first block
-};
-
-__device__ inline Seg cg_seg(const Dev& d, int64_t lb) {
-    if (d.nm == 1) {
-        const int64_t r0 = lb * d.cg_rows, r1 = r0 + d.cg_rows;
-        return {r0, r1 < d.nc ? r1 : d.nc, d.scal, 0, d.cg_nblk, 0, d.cg_pblk, lb == 0};
-    }
-    const int4 t = d.cg_blk[lb], pr = d.cg_parts[t.x];
-    return {t.y, t.z, msc(d, t.x), pr.x, pr.y, pr.z, pr.w, lb == pr.x};
-}
-
-// Sum of K values over the block, in a fixed order; valid in every thread.
-// `lds`: K * kMaxWaves doubles, not in use by an earlier call.
-template <int K>
-__device__ inline void block_sums(double (&v)[K], double* lds) {
-    const int w = threadIdx.x >> 6, nw = blockDim.x >> 6;
-#pragma unroll
-    for (int k = 0; k < K; ++k) v[k] = wave_sum(v[k]);
-    if ((threadIdx.x & 63) == 0) {
-#pragma unroll
-        for (int k = 0; k < K; ++k) lds[k * kMaxWaves + w] = v[k];
-    }
-    __syncthreads();
-#pragma unroll
-    for (int k = 0; k < K; ++k) {
-        v[k] = lds[k * kMaxWaves];
-        for (int j = 1; j < nw; ++j) v[k] += lds[k * kMaxWaves + j];
-    }
-}
-
-// The K sums of a mesh's partials (part[k * stride + b]), added by every
-// block of a kernel; a thread's four loads of a round go out together.
-template <int K>
-__device__ inline void sum_parts(const double* __restrict__ part, int64_t stride, int np, double* lds,
-                                 double (&out)[K]) {
-    const int T = blockDim.x;
-#pragma unroll
-    for (int k = 0; k < K; ++k) out[k] = 0.0;
-    for (int b0 = threadIdx.x; b0 < np; b0 += 4 * T) {
-        double v[K][4];
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int b = b0 + j * T;
-            const bool in = b < np;
-#pragma unroll
-            for (int k = 0; k < K; ++k) v[k][j] = in ? part[k * stride + b] : 0.0;
-        }
-#pragma unroll
-        for (int k = 0; k < K; ++k) out[k] += (v[k][0] + v[k][1]) + (v[k][2] + v[k][3]);
-    }
-    block_sums<K>(out, lds);
-}
 
 // the scalars the last direction kernel left for the next iteration
 __device__ inline void commit(double* sc) {
@@ -262,41 +174,6 @@ __global__ __launch_bounds__(512) void k_cg_residual(Dev d, int np) {
         out[lb] = v[0];
         out[d.cg_stride + lb] = v[1];
     }
-}
-
-// The vertex value A z of one vertex, summed by kCgVertexLanes neighbouring
-// lanes: lane q takes the entries q, q + 4, ..., up to 6 at a time (an
-// interior vertex of the 6-tetrahedra cube has 24 cells, one round).  With
-// one lane per vertex (24 loads, then 24 gathers a lane) a small mesh has
-// too few wavefronts to cover the chain: 5.9 us at 9,261 vertices.
-template <class R>
-__device__ inline R vertex_sum(const Dev& d, const R* __restrict__ z, int64_t v, int q) {
-    constexpr int L = kCgVertexLanes, B = 6;
-    const R* __restrict__ alpha = CgVec<R>::alpha(d);
-    const int64_t sl = v >> 6;
-    const int64_t base = d.n_off[sl] + (v & 63);
-    const int w = d.n_w[sl];
-    R s = R(0);
-    for (int k0 = q; k0 < w; k0 += B * L) {
-        int e[B];
-        R al[B];
-#pragma unroll
-        for (int j = 0; j < B; ++j) {
-            const int k = k0 + j * L;
-            const bool in = k < w;
-            const int64_t at = base + int64_t(in ? k : 0) * 64;
-            e[j] = d.mf_nidx[at];
-            al[j] = in ? alpha[at] : R(0);
-        }
-        R xe[B];
-#pragma unroll
-        for (int j = 0; j < B; ++j) xe[j] = z[e[j] >= 0 ? e[j] : ~e[j]];
-#pragma unroll
-        for (int j = 0; j < B; ++j) s += al[j] * (e[j] >= 0 ? xe[j] : -xe[j]);
-    }
-#pragma unroll
-    for (int o = 1; o < L; o <<= 1) s += __shfl_xor(s, o, 64);
-    return s;
 }
 
 // beta and the tests; x += alpha p; p = z + beta p; A p = A z + beta A p.
@@ -451,19 +328,28 @@ bool cg_meshes_apart(const Mesh& m) {
 }
 
 namespace {
+// tiles per block of the stored product
+int stored_tiles(const Dev& d) { return int((d.ntiles + kCgMaxProductBlocks - 1) / kCgMaxProductBlocks); }
+}  // namespace
+
+int cg_product_parts(const Dev& d, bool stored) {
+    return stored ? int((d.ntiles + stored_tiles(d) - 1) / stored_tiles(d)) : int(d.cg_pblk);
+}
+
+namespace {
 template <class R>
 hipError_t cg_part(const Dev& d, bool stored, int part, hipStream_t s) {
     const dim3 T(d.cg_threads);
     const unsigned rows = pad8(d.cg_nblk), verts = stored ? 0u : pad8(d.cg_vblk);
-    const int tiles = int((d.ntiles + kCgMaxProductBlocks - 1) / kCgMaxProductBlocks);
-    const unsigned nst = unsigned((d.ntiles + tiles - 1) / tiles);
+    const int tiles = stored_tiles(d);
+    const unsigned nst = unsigned(cg_product_parts(d, true));
     if (part == 0 && stored)
         hipLaunchKernelGGL(k_cg_product_stored<R>, dim3(nst), dim3(d.tile_rows), size_t(d.halo_max) * sizeof(R), s, d,
                            tiles);
     else if (part == 0)
         hipLaunchKernelGGL(k_cg_product<R>, dim3(pad8(d.cg_pblk)), dim3(kBlock), 0, s, d);
     else if (part == 1)
-        hipLaunchKernelGGL(k_cg_residual<R>, dim3(rows), T, 0, s, d, stored ? int(nst) : int(d.cg_pblk));
+        hipLaunchKernelGGL(k_cg_residual<R>, dim3(rows), T, 0, s, d, cg_product_parts(d, stored));
     else if (stored)
         hipLaunchKernelGGL((k_cg_direction<R, false>), dim3(rows), T, 0, s, d, 0);
     else

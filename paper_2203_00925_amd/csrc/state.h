@@ -280,6 +280,7 @@ hipError_t launch_cg_dir(const Dev& d, hipStream_t s);
 // last iteration of a chunk
 constexpr int kCgParts = 3;
 hipError_t launch_cg_part(const Dev& d, bool fp32, bool stored, int part, hipStream_t s);
+int cg_product_parts(const Dev& d, bool stored);   // partials the product of a single mesh leaves
 hipError_t launch_cg_open_vertices(const Dev& d, bool fp32, hipStream_t s);
 hipError_t launch_cg_commit(const Dev& d, hipStream_t s);
 
