@@ -26,7 +26,7 @@ __device__ inline int64_t tid_a() { return int64_t(blockIdx.x) * blockDim.x + th
 inline unsigned grid_a(int64_t n) { return unsigned((n + kBlock - 1) / kBlock); }
 __device__ inline bool done(const double* flag) { return flag && *flag != 0.0; }
 
-constexpr int kLanes = 4;                 // lanes that share a coarse row
+constexpr int kShare = 4;                 // wavefronts that share a slice of coarse rows
 
 // x = w D^-1 b
 __global__ __launch_bounds__(kBlock) void k_amg_smooth0(int64_t n, double w, const double* __restrict__ dinv,
@@ -68,23 +68,27 @@ __global__ __launch_bounds__(kBlock) void k_amg_restrict0(int64_t nco, const int
     if (xc) xc[I] = w * di * s;
 }
 
-// (A x)_row of one coarse row, summed by kLanes neighbouring lanes (valid in
-// all of them): lane q takes the entries q, q + 4, ..., eight at a time.  At
-// 2,800 rows of 20 entries one lane per row leaves 44 wavefronts, each a
-// chain of three rounds.
-__device__ inline double row_product(const AmgLevelDev& L, const double* __restrict__ x, int slice, int lr, int64_t row,
-                                     int q) {
+// (A x) of a slice's rows, lane j of every wavefront its row j: wavefront q of
+// the block takes the entries q, q + 4, ... of all 64 rows, eight at a time,
+// and the four sums meet in LDS.  At 2,800 rows of 20 entries one wavefront a
+// slice leaves 44, each a chain of three rounds; four neighbouring lanes a row
+// would share the entries as well, but load a slice's columns and values in
+// quarters of its lines.  Valid in every thread; `part` is free again after
+// the next barrier.
+__device__ inline double row_product(const AmgLevelDev& L, const double* __restrict__ x, int slice, int64_t row,
+                                     double (*part)[64]) {
     constexpr int B = 8;
-    const int64_t base = L.off[slice] + lr;
+    const int lane = threadIdx.x & 63, q = threadIdx.x >> 6;
+    const int64_t base = L.off[slice] + lane;
     const int w = L.w[slice];
     const double dg = L.diag[row], xr = x[row];
     double y = 0.0;
-    for (int k0 = q; k0 < w; k0 += B * kLanes) {
+    for (int k0 = q; k0 < w; k0 += B * kShare) {
         int c[B];
         double a[B];
 #pragma unroll
         for (int j = 0; j < B; ++j) {
-            const int k = k0 + j * kLanes;
+            const int k = k0 + j * kShare;
             const bool in = k < w;
             const int64_t at = base + int64_t(in ? k : k0) * 64;
             c[j] = L.idx[at];
@@ -96,9 +100,9 @@ __device__ inline double row_product(const AmgLevelDev& L, const double* __restr
 #pragma unroll
         for (int j = 0; j < B; ++j) y += a[j] * xe[j];
     }
-#pragma unroll
-    for (int o = 1; o < kLanes; o <<= 1) y += __shfl_xor(y, o, 64);
-    return y + dg * xr;
+    part[q][lane] = y;
+    __syncthreads();
+    return dg * xr + ((part[0][lane] + part[1][lane]) + (part[2][lane] + part[3][lane]));
 }
 
 // r = b - A x, restricted: b_c[I] = sum of r over I's members, and x_c = w
@@ -107,19 +111,19 @@ __global__ __launch_bounds__(kBlock) void k_amg_down(AmgLevelDev L, const double
                                                      const double* __restrict__ x, double w,
                                                      const double* __restrict__ dinv_c, double* __restrict__ bc,
                                                      double* __restrict__ xc, const double* flag) {
-    __shared__ double rs[64];
+    __shared__ double part[kShare][64], rs[64];
     if (done(flag)) return;
     const int64_t blk = xcd_block();
     if (blk >= L.nblk) return;
-    const int lr = threadIdx.x / kLanes, q = threadIdx.x & (kLanes - 1);
+    const int lane = threadIdx.x & 63;
     const int s0 = L.bslice[blk], s1 = L.bslice[blk + 1], a0 = L.bagg[blk], a1 = L.bagg[blk + 1];
     double big = 0.0;                                     // an aggregate over several slices
     for (int s = s0; s < s1; ++s) {
         const int r0 = L.srow[s], n = L.srow[s + 1] - r0;
-        const int64_t row = r0 + (lr < n ? lr : n - 1);
-        const double t = row_product(L, x, s, lr, row, q);
-        const double r = lr < n ? b[row] - t : 0.0;
-        if (q == 0) rs[lr] = r;
+        const int64_t row = r0 + (lane < n ? lane : n - 1);
+        const double br = b[row];
+        const double t = row_product(L, x, s, row, part);
+        if (int(threadIdx.x) < n) rs[threadIdx.x] = br - t;
         __syncthreads();
         if (s1 - s0 == 1) {
             const int I = a0 + int(threadIdx.x);
@@ -150,26 +154,27 @@ __global__ __launch_bounds__(kBlock) void k_amg_up(AmgLevelDev L, const double* 
                                                    const double* __restrict__ first, const int32_t* __restrict__ mptr,
                                                    const int32_t* __restrict__ midx, double* __restrict__ fine,
                                                    const double* flag) {
+    __shared__ double part[kShare][64];
     if (done(flag)) return;
     const int64_t s = xcd_block();
     if (s >= L.nslices) return;
-    const int lr = threadIdx.x / kLanes, q = threadIdx.x & (kLanes - 1);
+    const int lane = threadIdx.x & 63, q = threadIdx.x >> 6;
     const int r0 = L.srow[s], n = L.srow[s + 1] - r0;
-    const int64_t row = r0 + (lr < n ? lr : n - 1);
+    const int64_t row = r0 + (lane < n ? lane : n - 1);
     const double br = b[row], di = L.dinv[row], xr = x[row], f = first ? first[row] : 0.0;
     int m0 = 0, m1 = 0;
     if (!KEEP) {
         m0 = mptr[row];
         m1 = mptr[row + 1];
     }
-    double z = xr + w * di * (br - row_product(L, x, int(s), lr, row, q));
-    if (lr >= n) return;
+    double z = xr + w * di * (br - row_product(L, x, int(s), row, part));
+    if (lane >= n) return;
     if (KEEP) {
         if (q == 0) keep[row] = z;
         return;
     }
     if (first) z = f + z;
-    for (int m = m0 + q; m < m1; m += kLanes) {
+    for (int m = m0 + q; m < m1; m += kShare) {
         const int i = midx ? midx[m] : m;
         fine[i] = fine[i] + z;
     }
@@ -179,15 +184,16 @@ __global__ __launch_bounds__(kBlock) void k_amg_up(AmgLevelDev L, const double* 
 __global__ __launch_bounds__(kBlock) void k_amg_mid(AmgLevelDev L, const double* __restrict__ b,
                                                     const double* __restrict__ x, double w, double* __restrict__ r,
                                                     double* __restrict__ e, const double* flag) {
+    __shared__ double part[kShare][64];
     if (done(flag)) return;
     const int64_t s = xcd_block();
     if (s >= L.nslices) return;
-    const int lr = threadIdx.x / kLanes, q = threadIdx.x & (kLanes - 1);
+    const int lane = threadIdx.x & 63;
     const int r0 = L.srow[s], n = L.srow[s + 1] - r0;
-    const int64_t row = r0 + (lr < n ? lr : n - 1);
+    const int64_t row = r0 + (lane < n ? lane : n - 1);
     const double br = b[row], di = L.dinv[row];
-    const double v = br - row_product(L, x, int(s), lr, row, q);
-    if (lr < n && q == 0) {
+    const double v = br - row_product(L, x, int(s), row, part);
+    if (int(threadIdx.x) < n) {
         r[row] = v;
         e[row] = w * di * v;
     }
