@@ -69,7 +69,7 @@ __global__ __launch_bounds__(kBlock) void k_amg_restrict0(int64_t nco, const int
 }
 
 // (A x) of a slice's rows, lane j of every wavefront its row j: wavefront q of
-// the block takes the entries q, q + 4, ... of all 64 rows, eight at a time,
+// the block takes the entries q, q + 4, ... of all 64 rows, twelve at a time,
 // and the four sums meet in LDS.  At 2,800 rows of 20 entries one wavefront a
 // slice leaves 44, each a chain of three rounds; four neighbouring lanes a row
 // would share the entries as well, but load a slice's columns and values in
@@ -77,7 +77,7 @@ __global__ __launch_bounds__(kBlock) void k_amg_restrict0(int64_t nco, const int
 // the next barrier.
 __device__ inline double row_product(const AmgLevelDev& L, const double* __restrict__ x, int slice, int64_t row,
                                      double (*part)[64]) {
-    constexpr int B = 8;
+    constexpr int B = 12;
     const int lane = threadIdx.x & 63, q = threadIdx.x >> 6;
     const int64_t base = L.off[slice] + lane;
     const int w = L.w[slice];
@@ -112,11 +112,11 @@ __global__ __launch_bounds__(kBlock) void k_amg_down(AmgLevelDev L, const double
                                                      const double* __restrict__ dinv_c, double* __restrict__ bc,
                                                      double* __restrict__ xc, const double* flag) {
     __shared__ double part[kShare][64], rs[64];
-    if (done(flag)) return;
     const int64_t blk = xcd_block();
     if (blk >= L.nblk) return;
     const int lane = threadIdx.x & 63;
     const int s0 = L.bslice[blk], s1 = L.bslice[blk + 1], a0 = L.bagg[blk], a1 = L.bagg[blk + 1];
+    if (done(flag)) return;
     double big = 0.0;                                     // an aggregate over several slices
     for (int s = s0; s < s1; ++s) {
         const int r0 = L.srow[s], n = L.srow[s + 1] - r0;
@@ -155,11 +155,11 @@ __global__ __launch_bounds__(kBlock) void k_amg_up(AmgLevelDev L, const double* 
                                                    const int32_t* __restrict__ midx, double* __restrict__ fine,
                                                    const double* flag) {
     __shared__ double part[kShare][64];
-    if (done(flag)) return;
     const int64_t s = xcd_block();
     if (s >= L.nslices) return;
     const int lane = threadIdx.x & 63, q = threadIdx.x >> 6;
     const int r0 = L.srow[s], n = L.srow[s + 1] - r0;
+    if (done(flag)) return;
     const int64_t row = r0 + (lane < n ? lane : n - 1);
     const double br = b[row], di = L.dinv[row], xr = x[row], f = first ? first[row] : 0.0;
     int m0 = 0, m1 = 0;
@@ -185,11 +185,11 @@ __global__ __launch_bounds__(kBlock) void k_amg_mid(AmgLevelDev L, const double*
                                                     const double* __restrict__ x, double w, double* __restrict__ r,
                                                     double* __restrict__ e, const double* flag) {
     __shared__ double part[kShare][64];
-    if (done(flag)) return;
     const int64_t s = xcd_block();
     if (s >= L.nslices) return;
     const int lane = threadIdx.x & 63;
     const int r0 = L.srow[s], n = L.srow[s + 1] - r0;
+    if (done(flag)) return;
     const int64_t row = r0 + (lane < n ? lane : n - 1);
     const double br = b[row], di = L.dinv[row];
     const double v = br - row_product(L, x, int(s), row, part);
