@@ -125,9 +125,7 @@ __device__ inline R vertex_sum(const Dev& d, const R* __restrict__ z, int64_t v,
 #pragma unroll
         for (int j = 0; j < B; ++j) s += al[j] * (e[j] >= 0 ? xe[j] : -xe[j]);
     }
-#pragma unroll
-    for (int o = 1; o < L; o <<= 1) s += __shfl_xor(s, o, 64);
-    return s;
+    return quad_sum(s);
 }
 
 }  // namespace mifvm

@@ -12,15 +12,69 @@
 
 namespace mifvm {
 
+// A lane's partner value, lanes O apart by exclusive or (O a power of two):
+// register moves within the vector unit (the LDS crossbar that __shfl goes
+// through takes several times as long, and a small kernel's reductions are
+// part of its latency chain: 48k-cell solve 4.76 -> 4.53 ms, 619k refined 25.9
+// -> 24.6 ms).  O = 32, 16: the halves and rows swapped; O < 16:
+// a rotation of each row of 16 lanes, which reaches the partner's value once
+// the larger steps have made the row periodic, and exact exchanges for the
+// quad's steps used on their own.
+template <int CTRL>
+__device__ inline double lane_dpp(double v) {
+    const int lo = __builtin_amdgcn_mov_dpp(__double2loint(v), CTRL, 0xf, 0xf, true);
+    const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(v), CTRL, 0xf, 0xf, true);
+    return __hiloint2double(hi, lo);
+}
+template <int CTRL>
+__device__ inline float lane_dpp(float v) {
+    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), CTRL, 0xf, 0xf, true));
+}
+constexpr int kDppXor1 = 0xB1, kDppXor2 = 0x4E;             // quad permutations 1032, 2301
+constexpr int kDppRor1 = 0x121, kDppRor2 = 0x122, kDppRor4 = 0x124, kDppRor8 = 0x128;
+
+// v of both rows (halves) of each pair: first the even row's (lower half's)
+struct LanePair { double a, b; };
+__device__ inline LanePair swap_halves(double v) {
+    const auto lo = __builtin_amdgcn_permlane32_swap(__double2loint(v), __double2loint(v), false, false);
+    const auto hi = __builtin_amdgcn_permlane32_swap(__double2hiint(v), __double2hiint(v), false, false);
+    return {__hiloint2double(int(hi[0]), int(lo[0])), __hiloint2double(int(hi[1]), int(lo[1]))};
+}
+__device__ inline LanePair swap_rows(double v) {
+    const auto lo = __builtin_amdgcn_permlane16_swap(__double2loint(v), __double2loint(v), false, false);
+    const auto hi = __builtin_amdgcn_permlane16_swap(__double2hiint(v), __double2hiint(v), false, false);
+    return {__hiloint2double(int(hi[0]), int(lo[0])), __hiloint2double(int(hi[1]), int(lo[1]))};
+}
+
 __device__ inline double wave_sum(double v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+    LanePair p = swap_halves(v);
+    v = p.a + p.b;
+    p = swap_rows(v);
+    v = p.a + p.b;
+    v += lane_dpp<kDppRor8>(v);
+    v += lane_dpp<kDppRor4>(v);
+    v += lane_dpp<kDppRor2>(v);
+    v += lane_dpp<kDppRor1>(v);
     return v;
 }
 
 __device__ inline double wave_min(double v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v = fmin(v, __shfl_xor(v, o, 64));
+    LanePair p = swap_halves(v);
+    v = fmin(p.a, p.b);
+    p = swap_rows(v);
+    v = fmin(p.a, p.b);
+    v = fmin(v, lane_dpp<kDppRor8>(v));
+    v = fmin(v, lane_dpp<kDppRor4>(v));
+    v = fmin(v, lane_dpp<kDppRor2>(v));
+    v = fmin(v, lane_dpp<kDppRor1>(v));
+    return v;
+}
+
+// sum over the 4 lanes of each quad, valid in all of them
+template <class R>
+__device__ inline R quad_sum(R v) {
+    v += lane_dpp<kDppXor1>(v);
+    v += lane_dpp<kDppXor2>(v);
     return v;
 }
 
