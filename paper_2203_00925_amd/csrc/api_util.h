@@ -129,7 +129,7 @@ inline hipError_t capture_graph(State& s, hipGraphExec_t* exec, F enqueue) {
 }
 
 // n RK3 steps without timing events (api.hip)
-hipError_t enqueue_steps(const mifvm::State& s, int n, double dt, hipStream_t q);
+hipError_t enqueue_steps(mifvm::State& s, int n, double dt, hipStream_t q);
 // the matrix-free product's per-cell tables of the current potential BC
 // kinds, built if stale (api.hip)
 int ensure_mf_tables(mifvm::State& s, hipStream_t hs);

@@ -51,12 +51,9 @@ __device__ inline double2 mk2(double x, double y) { return make_double2(x, y); }
 __device__ inline float2 mk2(float x, float y) { return make_float2(x, y); }
 
 template <class R>
-__global__ __launch_bounds__(kBlock) void k_ghost_fill(int64_t nc, int64_t nb,
-                                                        const int32_t* __restrict__ gowner,
-                                                        const int32_t* __restrict__ gtag,
-                                                        const R* __restrict__ gdist, BcTable bc, R* u) {
-    const int64_t g = gtid();
-    if (g >= nb) return;
+__device__ inline void fill_ghost(int64_t g, int64_t nc, const int32_t* __restrict__ gowner,
+                                  const int32_t* __restrict__ gtag, const R* __restrict__ gdist, const BcTable& bc,
+                                  R* u) {
     const int t = gtag[g];
     const int kind = bc.kind[t];
     const R val = bc_value<R>(bc, g);
@@ -66,6 +63,15 @@ __global__ __launch_bounds__(kBlock) void k_ghost_fill(int64_t nc, int64_t nb,
     else if (kind == kNeumann) ug = uo + val * gdist[g];
     else ug = uo;
     u[nc + g] = ug;
+}
+
+template <class R>
+__global__ __launch_bounds__(kBlock) void k_ghost_fill(int64_t nc, int64_t nb,
+                                                        const int32_t* __restrict__ gowner,
+                                                        const int32_t* __restrict__ gtag,
+                                                        const R* __restrict__ gdist, BcTable bc, R* u) {
+    const int64_t g = gtid();
+    if (g < nb) fill_ghost(g, nc, gowner, gtag, gdist, bc, u);
 }
 
 // ---- gradient in star-moment form ------------------------------------------
@@ -642,18 +648,27 @@ __global__ __launch_bounds__(kBlock) void k_conservation(Dev d, const R* __restr
     if (threadIdx.x == 0) d.partial[blockIdx.x] = s;
 }
 
-// one block: reduce n partials into mesh m's scal[slot] (op 0 = sum, 1 = min)
-__global__ __launch_bounds__(1024) void k_finalize(Dev d, int64_t n, int m, int slot, int op) {
+// one block: reduce n partials into mesh m's scal[slot] (op 0 = sum, 1 = min),
+// and into the host's mirror of it (pinned memory, read once the stream has
+// been waited for: no copy behind the kernel)
+__global__ __launch_bounds__(1024) void k_finalize(Dev d, int64_t n, int m, int slot, int op, double* host) {
     __shared__ double lds[16];
     const double v = op == 0 ? reduce_partials_sum(d.partial, n, lds) : reduce_partials_min(d.partial, n, lds);
-    if (threadIdx.x == 0) msc(d, m)[slot] = v;
+    if (threadIdx.x == 0) {
+        msc(d, m)[slot] = v;
+        if (host) host[int64_t(m) * SC_COUNT_ + slot] = v;
+    }
 }
 
-// the time step each mesh's update uses: dt if dt > 0, else its CFL bound
-// times cfl (stored by the last CFL evaluation)
-__global__ void k_set_dt(Dev d, double dt, double cfl) {
-    const int m = int(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (m < d.nm) d.mesh_dt[m] = dt > 0.0 ? dt : cfl * msc(d, m)[SC_DT_INV];
+// What a run of steps starts from: the time step each mesh's update uses (dt
+// if dt > 0, else its CFL bound times cfl, stored by the last CFL evaluation),
+// and the ghosts of u
+template <class R>
+__global__ __launch_bounds__(kBlock) void k_step_begin(Dev d, const R* __restrict__ gdist, BcTable bc, R* u, double dt,
+                                                        double cfl) {
+    const int64_t g = gtid();
+    if (g < d.nm) d.mesh_dt[g] = dt > 0.0 ? dt : cfl * msc(d, int(g))[SC_DT_INV];
+    if (g < d.nb) fill_ghost(g, d.nc, d.gowner, d.gtag, gdist, bc, u);
 }
 
 // ---- launchers ---------------------------------------------------------------
@@ -756,8 +771,10 @@ hipError_t launch_fv_cell_setup(const Dev& d, hipStream_t s) {
     return hipGetLastError();
 }
 
-hipError_t launch_set_dt(const Dev& d, double dt, double cfl, hipStream_t s) {
-    hipLaunchKernelGGL(k_set_dt, dim3((d.nm + 255) / 256), dim3(256), 0, s, d, dt, cfl);
+hipError_t launch_step_begin(const Dev& d, bool fp32, const BcTable& bc, double dt, double cfl, hipStream_t s) {
+    const dim3 g(grid_for(d.nb > d.nm ? d.nb : d.nm)), b(kBlock);
+    if (fp32) hipLaunchKernelGGL(k_step_begin<float>, g, b, 0, s, d, (const float*)d.gdist32, bc, d.u32, dt, cfl);
+    else hipLaunchKernelGGL(k_step_begin<double>, g, b, 0, s, d, (const double*)d.gdist, bc, d.u, dt, cfl);
     return hipGetLastError();
 }
 
@@ -853,23 +870,23 @@ static int blocks_for_range(int64_t n) {
     return int(b < 1024 ? (b < 1 ? 1 : b) : 1024);
 }
 
-hipError_t launch_cfl(const Dev& d, const Mesh& mh, const BcTable& bc, hipStream_t s) {
+hipError_t launch_cfl(const Dev& d, const Mesh& mh, const BcTable& bc, double* host, hipStream_t s) {
     for (int m = 0; m < d.nm; ++m) {
         const int nblk = blocks_for_range(mh.mesh_start[m + 1] - mh.mesh_start[m]);
         hipLaunchKernelGGL(k_cfl, dim3(nblk), dim3(kBlock), 0, s, d, bc, m);
-        hipLaunchKernelGGL(k_finalize, dim3(1), dim3(1024), 0, s, d, int64_t(nblk), m, int(SC_DT_INV), 1);
+        hipLaunchKernelGGL(k_finalize, dim3(1), dim3(1024), 0, s, d, int64_t(nblk), m, int(SC_DT_INV), 1, host);
     }
     return hipGetLastError();
 }
 
-hipError_t launch_conservation(const Dev& d, const Mesh& mh, bool fp32, hipStream_t s) {
+hipError_t launch_conservation(const Dev& d, const Mesh& mh, bool fp32, double* host, hipStream_t s) {
     for (int m = 0; m < d.nm; ++m) {
         const int nblk = blocks_for_range(mh.mesh_start[m + 1] - mh.mesh_start[m]);
         if (fp32)
             hipLaunchKernelGGL(k_conservation<float>, dim3(nblk), dim3(kBlock), 0, s, d, (const float*)d.u32, m);
         else
             hipLaunchKernelGGL(k_conservation<double>, dim3(nblk), dim3(kBlock), 0, s, d, (const double*)d.u, m);
-        hipLaunchKernelGGL(k_finalize, dim3(1), dim3(1024), 0, s, d, int64_t(nblk), m, int(SC_CONS), 0);
+        hipLaunchKernelGGL(k_finalize, dim3(1), dim3(1024), 0, s, d, int64_t(nblk), m, int(SC_CONS), 0, host);
     }
     return hipGetLastError();
 }

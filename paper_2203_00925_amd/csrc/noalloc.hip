@@ -79,7 +79,7 @@ extern "C" int mifvm_conservation_static(mifvm_state* st, double* total_out, voi
     d.partial = ptr;
     d.scal = ptr + kPartials;
     double* total = ptr + kPartials + int64_t(MIFVM_STATIC_MAX_MESHES) * SC_COUNT_;
-    HIPCHK(launch_conservation(d, *s.mesh, s.fp32, hs));
+    HIPCHK(launch_conservation(d, *s.mesh, s.fp32, nullptr, hs));
     hipLaunchKernelGGL(k_sum_meshes, dim3(1), dim3(64), 0, hs, d.scal, int(d.nm), total);
     HIPCHK(hipGetLastError());
     double host = 0.0;

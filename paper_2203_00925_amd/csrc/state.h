@@ -180,6 +180,9 @@ struct State {
     hipGraphExec_t step_exec = nullptr;   // n RK3 steps
     int step_exec_n = 0;
     double step_exec_dt = -1.0;
+    hipGraphExec_t stage_exec = nullptr;  // the stages of one RK3 step (the time step is in device memory)
+    int64_t step_calls = 0;               // of those that may replay it
+    bool waited = false;                  // the last call (a CFL evaluation, a solve) waited for its stream
     // schedule chosen by the autotuner (0 = not tuned)
     int tuned_chunk = 0, tuned_graph = 0, tuned_step_graph = 0;
     bool assembled = false;               // K's stored values, diagonal and c match the BCs
@@ -242,7 +245,8 @@ hipError_t launch_cell_step(const Dev& d, bool fp32, const BcTable& bc, const vo
 hipError_t launch_fv_cell_setup(const Dev& d, hipStream_t s);
 // the matrix-free per-cell tables (mf_kernels.hip)
 hipError_t launch_mf_cell_setup(const Dev& d, const BcTable& bc_pot, hipStream_t s);
-hipError_t launch_set_dt(const Dev& d, double dt, double cfl, hipStream_t s);
+// each mesh's time step and the ghosts of u: what a run of steps starts from
+hipError_t launch_step_begin(const Dev& d, bool fp32, const BcTable& bc, double dt, double cfl, hipStream_t s);
 hipError_t launch_residual_out(const Dev& d, bool fp32, double* res_internal, hipStream_t s);
 hipError_t launch_face_phi(const Dev& d, hipStream_t s);
 hipError_t launch_make_fp32_geometry(const Dev& d, int64_t node_padded, hipStream_t s);
@@ -257,8 +261,9 @@ hipError_t launch_to_internal_typed(const int32_t* perm, int64_t n, int comps, c
                                     void* dst, bool dst_f32, hipStream_t s);
 hipError_t launch_to_user_typed(const int32_t* perm, int64_t n, int comps, const void* src, bool src_f32,
                                 void* dst, bool dst_f32, hipStream_t s);
-hipError_t launch_cfl(const Dev& d, const Mesh& mh, const BcTable& bc, hipStream_t s);
-hipError_t launch_conservation(const Dev& d, const Mesh& mh, bool fp32, hipStream_t s);
+// host: the pinned mirror of the scalars, which receives the result as well (null: none)
+hipError_t launch_cfl(const Dev& d, const Mesh& mh, const BcTable& bc, double* host, hipStream_t s);
+hipError_t launch_conservation(const Dev& d, const Mesh& mh, bool fp32, double* host, hipStream_t s);
 
 // launchers (solve_kernels.hip)
 hipError_t launch_assemble(const Dev& d, const BcTable& bc, int row_max, hipStream_t s);
