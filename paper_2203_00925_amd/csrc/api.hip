@@ -116,6 +116,7 @@ size_t layout(const Mesh& m, char* base, Dev& d) {
     d.uf = carve<double>(base, off, 4 * nc);
     d.u_b = carve<double>(base, off, NX);
     d.u_c = carve<double>(base, off, NX);
+    d.cell_nb = carve<int32_t>(base, off, 4 * nc);
     d.fvc_vid = carve<int32_t>(base, off, 4 * nc);
     d.fvc_w = carve<double>(base, off, 4 * nc);
     d.fvc_r = carve<double>(base, off, 4 * nc);
@@ -159,7 +160,7 @@ size_t layout(const Mesh& m, char* base, Dev& d) {
     d.mf_nidx = carve<int32_t>(base, off, m.node.idx.size() > 0 ? m.node.idx.size() : 1);
     d.n_entries = int64_t(m.node.idx.size());
     d.mfc_vid = carve<int32_t>(base, off, 4 * nc);
-    d.mfc_w = carve<double>(base, off, 4 * nc);
+    d.mfc_w = carve<double>(base, off, 3 * nc);
     d.mfc_r = carve<double>(base, off, 4 * nc);
     d.mfc_w32 = carve<float>(base, off, 4 * nc);
     d.mfc_r32 = carve<float>(base, off, 4 * nc);

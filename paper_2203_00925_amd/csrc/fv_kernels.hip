@@ -30,6 +30,7 @@
 // wavefront are one contiguous 128/256/512-byte segment.
 #include <type_traits>
 
+#include "quad.h"
 #include "reduce.h"
 #include "seg.h"
 #include "state.h"
@@ -307,8 +308,8 @@ __global__ __launch_bounds__(kBlock, 4) void k_grad_cells(Dev d, FvArrays<R> a) 
     // of a face.  With parts: the gradient and limiter arrays, which the face
     // kernel reads.
     if constexpr (!PARTS) {
-#pragma unroll
-        for (int k = 0; k < 4; ++k) a.uf[k * nc + i] = ui + psi * dl[k];
+        const R face[4] = {ui + psi * dl[0], ui + psi * dl[1], ui + psi * dl[2], ui + psi * dl[3]};
+        store_quad(a.uf, nc, i, face);
     } else {
         a.grad[i] = gx;
         a.grad[nc + i] = gy;
@@ -361,9 +362,11 @@ __global__ __launch_bounds__(kBlock) void k_face_flux(Dev d, FvArrays<R> a, BcTa
 // so sum_k s_k (kAC (u_A - u_C) + kBC (u_B - u_C)) = sum_v w_v u_node[v], and
 // s_k kRL (u_R - u_L) = kRL (u_n - u_i) with n the cell across face k.  The
 // convective part is (s_k phi_f) times the upwind side's MUSCL value at the
-// face centroid, which the gradient kernel stores per cell and face: uf[k][i]
-// on the cell's side, uf[j][n] across (j = the face's slot among n's
-// faces).  Both cells of a face take the same upwind value, so its
+// face centroid, which the gradient kernel stores per cell and face: value k
+// of cell i on the cell's side, value j of cell n across (j = the face's slot
+// among n's faces).  A face's vertex weights add up to zero, so the cell's
+// fourth follows from the other three, sum_v w_v u_v = sum_{k<3} w_k (u_k - u_3),
+// and its place holds the cell's volume.  Both cells of a face take the same upwind value, so its
 // convective parts cancel exactly in the sum over cells.  Boundary faces
 // (the cell is always their L side) are evaluated as in k_face_flux.
 
@@ -387,8 +390,10 @@ __global__ __launch_bounds__(kBlock) void k_fv_cell_setup(Dev d) {
         }
     };
     uint32_t slots = 0;
+    int across[4];
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
+        across[k] = d.c2n[k * nc + i];
         const int code = d.c2f[k * nc + i];
         const int f = code >= 0 ? code : ~code;
         const double sg = code >= 0 ? 1.0 : -1.0;
@@ -411,13 +416,16 @@ __global__ __launch_bounds__(kBlock) void k_fv_cell_setup(Dev d) {
         slots |= (in ? j : 0u) << (2 * k);
     }
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        d.fvc_vid[q * nc + i] = vid[q] >= 0 ? vid[q] : vid[0];
-        d.fvc_w[q * nc + i] = w[q];
-        d.fvc_r[q * nc + i] = r[q];
-        d.fvc_w32[q * nc + i] = float(w[q]);
-        d.fvc_r32[q * nc + i] = float(r[q]);
-    }
+    for (int q = 0; q < 4; ++q) vid[q] = vid[q] >= 0 ? vid[q] : vid[0];
+    w[3] = d.vol[i];
+    const float w32[4] = {float(w[0]), float(w[1]), float(w[2]), float(w[3])};
+    const float r32[4] = {float(r[0]), float(r[1]), float(r[2]), float(r[3])};
+    store_quad(d.cell_nb, nc, i, across);
+    store_quad(d.fvc_vid, nc, i, vid);
+    store_quad(d.fvc_w, nc, i, w);
+    store_quad(d.fvc_r, nc, i, r);
+    store_quad(d.fvc_w32, nc, i, w32);
+    store_quad(d.fvc_r32, nc, i, r32);
     d.fvc_slot[i] = uint8_t(slots);
 }
 
@@ -437,16 +445,13 @@ __global__ __launch_bounds__(kBlock) void k_cell_step(Dev d, FvArrays<R> a, BcTa
     int nb[4], vid[4];
     R w[4], r[4], uo[4], po[4];
     const uint32_t sl = d.fvc_slot[i];
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-        nb[k] = d.c2n[k * nc + i];
-        vid[k] = d.fvc_vid[k * nc + i];
-        w[k] = a.cw[k * nc + i];
-        r[k] = a.cr[k * nc + i];
-        uo[k] = a.uf[k * nc + i];
-        po[k] = a.cphi[k * nc + i];                    // outward
-    }
-    const R ui = uin[i], base = a.u[i], vol = a.vol[i], src = a.src[i];
+    load_quad(d.cell_nb, nc, i, nb);
+    load_quad(d.fvc_vid, nc, i, vid);
+    load_quad(a.cw, nc, i, w);
+    load_quad(a.cr, nc, i, r);
+    load_quad(a.uf, nc, i, uo);
+    load_quad(a.cphi, nc, i, po);                      // outward
+    const R ui = uin[i], base = a.u[i], vol = w[3], src = a.src[i];
     const R D = R(d.mesh_D[m]), a_dt = R(alpha * d.mesh_dt[m]);
     R un[4], ux[4], uv[4];
 #pragma unroll
@@ -454,11 +459,11 @@ __global__ __launch_bounds__(kBlock) void k_cell_step(Dev d, FvArrays<R> a, BcTa
         un[k] = uin[nb[k]];                            // a ghost's value behind a boundary face
         uv[k] = a.unode[vid[k]];
         ux[k] = R(0);
-        if (nb[k] < nc && po[k] < R(0)) ux[k] = a.uf[int64_t((sl >> (2 * k)) & 3u) * nc + nb[k]];
+        if (nb[k] < nc && po[k] < R(0)) ux[k] = quad_value(a.uf, nc, nb[k], int((sl >> (2 * k)) & 3u));
     }
     R dif = R(0);
 #pragma unroll
-    for (int k = 0; k < 4; ++k) dif += w[k] * uv[k];
+    for (int k = 0; k < 3; ++k) dif += w[k] * (uv[k] - uv[3]);
 #pragma unroll
     for (int k = 0; k < 4; ++k) dif += r[k] * (un[k] - ui);
     R conv = R(0);
@@ -543,13 +548,16 @@ __global__ __launch_bounds__(kBlock) void k_cell_phi(Dev d) {
     const int64_t i = gtid();
     if (i >= d.nc) return;
     const int64_t nc = d.nc;
+    double po[4];
+    float po32[4];
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
         const int code = d.c2f[k * nc + i];
-        const double po = code >= 0 ? d.phi[code] : -d.phi[~code];
-        d.fvc_phi[k * nc + i] = po;
-        d.fvc_phi32[k * nc + i] = float(po);
+        po[k] = code >= 0 ? d.phi[code] : -d.phi[~code];
+        po32[k] = float(po[k]);
     }
+    store_quad(d.fvc_phi, nc, i, po);
+    store_quad(d.fvc_phi32, nc, i, po32);
 }
 
 // FP32 copies of the static geometry the FP32 kernels read

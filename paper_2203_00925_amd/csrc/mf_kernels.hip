@@ -16,6 +16,7 @@
 
 #include "cg_scalars.h"
 #include "mf_cell.h"
+#include "quad.h"
 #include "reduce.h"
 #include "seg.h"
 #include "state.h"
@@ -154,13 +155,16 @@ __global__ __launch_bounds__(kBlock) void k_mf_cell_setup(Dev d, BcTable bc) {
     // vertex, or vertex 0, with weight 0
     const int v0 = vid[0] >= 0 ? vid[0] : 0;
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        d.mfc_vid[q * nc + i] = vid[q] >= 0 ? vid[q] : v0;
-        d.mfc_w[q * nc + i] = w[q];
-        d.mfc_r[q * nc + i] = r[q];
-        d.mfc_w32[q * nc + i] = float(w[q]);
-        d.mfc_r32[q * nc + i] = float(r[q]);
+    for (int q = 0; q < 4; ++q) vid[q] = vid[q] >= 0 ? vid[q] : v0;
+    store_quad(d.mfc_vid, nc, i, vid);
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {                     // the fourth weight is minus their sum
+        d.mfc_w[mfc_weight<double>(nc, i, q)] = w[q];
+        d.mfc_w32[mfc_weight<float>(nc, i, q)] = float(w[q]);
     }
+    const float r32[4] = {float(r[0]), float(r[1]), float(r[2]), float(r[3])};
+    store_quad(d.mfc_r, nc, i, r);
+    store_quad(d.mfc_r32, nc, i, r32);
 }
 
 __global__ __launch_bounds__(kBlock) void k_mf_cell(Dev d, const double* __restrict__ x,

@@ -82,17 +82,18 @@ struct Dev {
     double *u, *src, *vel, *phi;     // u: nc+nb (ghosts behind), vel 3 x nc
     double *grad, *psi, *unode, *flux;    // grad 3 x nc
     // FP64 step (per cell): the MUSCL value at each of the cell's four face
-    // centroids [4][nc] (gradient kernel -> cell step); the two stage buffers
+    // centroids (quad.h; gradient kernel -> cell step); the two stage buffers
     // of u (nc+nb each: a stage reads one and writes the other, u^n stays in u)
     double *uf, *u_b, *u_c;
-    // per-cell tables of the FP64 step (geometry only): the cell's 4 vertex
-    // ids, their diffusion weights and the kRL weights over its interior
-    // faces ([4][nc] each), and per face k the slot of the same face among
-    // the neighbour's faces (2 bits per face)
-    int32_t* fvc_vid;
+    // per-cell tables of the FP64 step (geometry only, four values each laid
+    // out by quad.h): c2n again, the cell's 4 vertex ids, three of their
+    // diffusion weights and the volume, the kRL weights over its interior
+    // faces, and per face k the slot of the same face among the neighbour's
+    // faces (2 bits per face)
+    int32_t *cell_nb, *fvc_vid;
     double *fvc_w, *fvc_r;
     uint8_t* fvc_slot;
-    double* fvc_phi;                      // [4][nc] outward phi of the cell's faces (with phi)
+    double* fvc_phi;                      // outward phi of the cell's faces (with phi)
     // the same for the FP32 step: face values, stage buffers, weights, phi
     float *uf32, *u_b32, *u_c32, *fvc_w32, *fvc_r32, *fvc_phi32;
     // solver vectors (P lives in x)
@@ -111,7 +112,7 @@ struct Dev {
     // matrix-free operator per cell i (from the faces and the potential's
     // boundary kinds): (K x)_i = -(sum_k w[k] x_v[vid[k]] + sum_k r[k] t_k) over
     // the cell's 4 vertices and 4 faces, t_k = x[c2n[k]] - x_i across an
-    // interior face and x_i on a boundary face ([4][nc] each; FP32 copies)
+    // interior face and x_i on a boundary face (mf_cell.h; FP32 copies)
     int32_t* mfc_vid;
     double *mfc_w, *mfc_r;
     float *mfc_w32, *mfc_r32;
