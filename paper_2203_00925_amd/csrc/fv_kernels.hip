@@ -97,9 +97,9 @@ __global__ __launch_bounds__(kBlock) void k_ghost_fill(int64_t nc, int64_t nb,
 // the entries q, q + 4, ..., six loads of each kind in flight.  Values are
 // taken relative to the list's first entry's.
 template <class R>
-__global__ __launch_bounds__(kBlock) void k_vertex_moments(Dev d, FvArrays<R> a) {
+__global__ __launch_bounds__(kBlock) void k_vertex_moments(Dev d, FvArrays<R> a, BlockOrder order) {
     constexpr int L = 4, B = 6;
-    const int64_t v = xcd_block() * (kBlock / L) + threadIdx.x / L;
+    const int64_t v = order.block() * (kBlock / L) + threadIdx.x / L;
     const int q = threadIdx.x & (L - 1);
     const int64_t vc = v < d.nv ? v : d.nv - 1;
     const int64_t sl = vc >> 6;
@@ -161,7 +161,7 @@ __global__ __launch_bounds__(kBlock) void k_vertex_moments(Dev d, FvArrays<R> a)
 // mean of the four and x_f of three of them, x_f - x_i = (x_i - x_v)/3 for the
 // vertex v across from the face.
 template <class R, bool PARTS>
-__global__ __launch_bounds__(kBlock, 4) void k_grad_cells(Dev d, FvArrays<R> a) {
+__global__ __launch_bounds__(kBlock, 4) void k_grad_cells(Dev d, FvArrays<R> a, BlockOrder order) {
     using V2 = typename Vec2T<R>::T;
     using V4 = typename Vec4T<R>::T;
     extern __shared__ __align__(16) unsigned char sm_raw[];
@@ -176,7 +176,7 @@ __global__ __launch_bounds__(kBlock, 4) void k_grad_cells(Dev d, FvArrays<R> a) 
     R* const vf = reinterpret_cast<R*>(ve + vcap);
     constexpr bool rel = std::is_same<R, float>::value;   // FP32: positions relative to the tile's first cell
     const int64_t nc = d.nc;
-    const int64_t t = xcd_block();
+    const int64_t t = order.block();
     if (t >= d.g_tiles) return;
     const int T = blockDim.x;
     const int64_t i = t * T + threadIdx.x;
@@ -434,8 +434,8 @@ __global__ __launch_bounds__(kBlock) void k_fv_cell_setup(Dev d) {
 // u[i]); then the ghosts behind the cell's boundary faces, from the new value
 template <class R>
 __global__ __launch_bounds__(kBlock) void k_cell_step(Dev d, FvArrays<R> a, BcTable bc, const R* __restrict__ uin,
-                                                      R* uout, double alpha) {
-    const int64_t i = gtid_m();                        // XCD-contiguous block order
+                                                      R* uout, double alpha, BlockOrder order) {
+    const int64_t i = order.block() * kBlock + threadIdx.x;
     if (i >= d.nc) return;
     const int64_t nc = d.nc;
     const int m = mesh_of(d, i);
@@ -732,21 +732,22 @@ FvArrays<R> with_u(FvArrays<R> a, const void* u_in) {
 }
 
 hipError_t launch_vertex_moments(const Dev& d, bool fp32, hipStream_t s, const void* u_in) {
-    const dim3 g(rows_m(d.nv * 4, kBlock)), b(kBlock);
-    if (fp32) hipLaunchKernelGGL(k_vertex_moments<float>, g, b, 0, s, d, with_u(fv32(d), u_in));
-    else hipLaunchKernelGGL(k_vertex_moments<double>, g, b, 0, s, d, with_u(fv64(d), u_in));
+    const BlockOrder o = stream_order(d.nv * 4, kBlock);
+    const dim3 g(o.grid), b(kBlock);
+    if (fp32) hipLaunchKernelGGL(k_vertex_moments<float>, g, b, 0, s, d, with_u(fv32(d), u_in), o);
+    else hipLaunchKernelGGL(k_vertex_moments<double>, g, b, 0, s, d, with_u(fv64(d), u_in), o);
     return hipGetLastError();
 }
 
 template <class R>
 void launch_grad_t(const Dev& d, const FvArrays<R>& a, bool parts, hipStream_t s) {
     const dim3 b(d.g_rows);
-    // grid padded to a multiple of 8 for the XCD-contiguous tile order
-    const dim3 gx(unsigned((d.g_tiles + kXcds - 1) / kXcds * kXcds));
+    const BlockOrder o = stream_order(d.g_tiles, 1);
+    const dim3 gx(o.grid);
     if (parts)
-        hipLaunchKernelGGL((k_grad_cells<R, true>), gx, b, grad_lds_bytes<R>(d), s, d, a);
+        hipLaunchKernelGGL((k_grad_cells<R, true>), gx, b, grad_lds_bytes<R>(d), s, d, a, o);
     else
-        hipLaunchKernelGGL((k_grad_cells<R, false>), gx, b, grad_lds_bytes<R>(d), s, d, a);
+        hipLaunchKernelGGL((k_grad_cells<R, false>), gx, b, grad_lds_bytes<R>(d), s, d, a, o);
 }
 
 hipError_t launch_grad_limiter(const Dev& d, bool fp32, hipStream_t s, bool parts, const void* u_in) {
@@ -764,12 +765,13 @@ hipError_t launch_face_flux(const Dev& d, bool fp32, const BcTable& bc, hipStrea
 
 hipError_t launch_cell_step(const Dev& d, bool fp32, const BcTable& bc, const void* u_in, void* u_out,
                             double alpha, hipStream_t s) {
+    const BlockOrder o = stream_order(d.nc, kBlock);
     if (fp32)
-        hipLaunchKernelGGL(k_cell_step<float>, dim3(rows_m(d.nc, kBlock)), dim3(kBlock), 0, s, d, fv32(d), bc,
-                           static_cast<const float*>(u_in), static_cast<float*>(u_out), alpha);
+        hipLaunchKernelGGL(k_cell_step<float>, dim3(o.grid), dim3(kBlock), 0, s, d, fv32(d), bc,
+                           static_cast<const float*>(u_in), static_cast<float*>(u_out), alpha, o);
     else
-        hipLaunchKernelGGL(k_cell_step<double>, dim3(rows_m(d.nc, kBlock)), dim3(kBlock), 0, s, d, fv64(d), bc,
-                           static_cast<const double*>(u_in), static_cast<double*>(u_out), alpha);
+        hipLaunchKernelGGL(k_cell_step<double>, dim3(o.grid), dim3(kBlock), 0, s, d, fv64(d), bc,
+                           static_cast<const double*>(u_in), static_cast<double*>(u_out), alpha, o);
     return hipGetLastError();
 }
 
