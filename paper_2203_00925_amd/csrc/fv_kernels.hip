@@ -366,28 +366,24 @@ __global__ __launch_bounds__(kBlock) void k_face_flux(Dev d, FvArrays<R> a, BcTa
 // of cell i on the cell's side, value j of cell n across (j = the face's slot
 // among n's faces).  A face's vertex weights add up to zero, so the cell's
 // fourth follows from the other three, sum_v w_v u_v = sum_{k<3} w_k (u_k - u_3),
-// and its place holds the cell's volume.  Both cells of a face take the same upwind value, so its
-// convective parts cancel exactly in the sum over cells.  Boundary faces
-// (the cell is always their L side) are evaluated as in k_face_flux.
+// and its place holds the cell's volume.  Both cells of a face take the same
+// upwind value, so its convective parts cancel exactly in the sum over cells.
+// Boundary faces (the cell is always their L side) are evaluated as in
+// k_face_flux.
 
 // the tables: geometry only, built once per state
 __global__ __launch_bounds__(kBlock) void k_fv_cell_setup(Dev d) {
     const int64_t i = gtid();
     if (i >= d.nc) return;
     const int64_t nc = d.nc;
-    int vid[4] = {-1, -1, -1, -1};
+    // the cell's vertices, k across from face k
+    const uint4 cl = d.g_cell[i];
+    const int32_t* __restrict__ tv = d.gv_idx + d.gv_off[i / d.g_rows];
+    const int vid[4] = {tv[cl.z & 0xffff], tv[cl.z >> 16], tv[cl.w & 0xffff], tv[cl.w >> 16]};
     double w[4] = {0.0, 0.0, 0.0, 0.0}, r[4] = {0.0, 0.0, 0.0, 0.0};
-    auto add = [&](int v, double c) {                 // the vertex's slot (first seen, first slot)
-        bool done = false;
+    auto add = [&](int v, double c) {
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const bool hit = !done && (vid[q] == v || vid[q] < 0);
-            if (hit) {
-                vid[q] = v;
-                w[q] += c;
-            }
-            done = done || hit;
-        }
+        for (int q = 0; q < 4; ++q) w[q] += vid[q] == v ? c : 0.0;
     };
     uint32_t slots = 0;
     int across[4];
@@ -398,8 +394,6 @@ __global__ __launch_bounds__(kBlock) void k_fv_cell_setup(Dev d) {
         const int f = code >= 0 ? code : ~code;
         const double sg = code >= 0 ? 1.0 : -1.0;
         const bool in = f < d.nfi;
-        // a boundary face only places its vertices (weight 0): every vertex
-        // of the cell gets a slot
         const double on = in ? sg : 0.0;
         const double kac = d.kAC[f], kbc = d.kBC[f];
         add(d.fA[f], on * kac);
@@ -415,13 +409,10 @@ __global__ __launch_bounds__(kBlock) void k_fv_cell_setup(Dev d) {
         }
         slots |= (in ? j : 0u) << (2 * k);
     }
-#pragma unroll
-    for (int q = 0; q < 4; ++q) vid[q] = vid[q] >= 0 ? vid[q] : vid[0];
     w[3] = d.vol[i];
     const float w32[4] = {float(w[0]), float(w[1]), float(w[2]), float(w[3])};
     const float r32[4] = {float(r[0]), float(r[1]), float(r[2]), float(r[3])};
     store_quad(d.cell_nb, nc, i, across);
-    store_quad(d.fvc_vid, nc, i, vid);
     store_quad(d.fvc_w, nc, i, w);
     store_quad(d.fvc_r, nc, i, r);
     store_quad(d.fvc_w32, nc, i, w32);
@@ -431,36 +422,80 @@ __global__ __launch_bounds__(kBlock) void k_fv_cell_setup(Dev d) {
 
 // u_out[i] = u[i] + alpha dt Res(u_in)_i (u holds u^n; u_in and u_out are
 // other buffers, or u_out = u on the last stage, whose cell i alone reads
-// u[i]); then the ghosts behind the cell's boundary faces, from the new value
+// u[i]); then the ghosts behind the cell's boundary faces, from the new value.
+//
+// One block per gradient tile.  The kernel is bound by its gathers' line
+// accesses (with one gather per neighbour, vertex and upwind face value they
+// were nine tenths of them), so the tile's own values, which 85% of its cells'
+// neighbours are, and the vertex values its cells touch (0.49 per cell instead
+// of 4) go through LDS; a neighbour outside the tile is gathered, and lanes
+// without one read their own cell's line.
 template <class R>
 __global__ __launch_bounds__(kBlock) void k_cell_step(Dev d, FvArrays<R> a, BcTable bc, const R* __restrict__ uin,
                                                       R* uout, double alpha, BlockOrder order) {
-    const int64_t i = order.block() * kBlock + threadIdx.x;
-    if (i >= d.nc) return;
+    extern __shared__ __align__(16) unsigned char sm_raw[];
+    const int T = d.g_rows;
+    R* const su = reinterpret_cast<R*>(sm_raw);            // [T] u
+    R* const sf = su + T;                                  // [4][T] face values
+    R* const sv = sf + 4 * T;                              // vertex values
     const int64_t nc = d.nc;
+    const int64_t t = order.block();
+    if (t >= d.g_tiles) return;
+    const int64_t t0 = t * T, row = t0 + threadIdx.x;
+    const bool cell = row < nc;
+    const int64_t i = cell ? row : nc - 1;
+    const int64_t w0 = d.gv_off[t];
+    const int wn = int(d.gv_off[t + 1] - w0);
     const int m = mesh_of(d, i);
-    // the cell's tables go out first (coalesced), then the gathers they
-    // address; the neighbour's face value only on lanes where it is the
-    // upwind side (the gathers' address work is what bounds this kernel)
-    int nb[4], vid[4];
+    // the cell's tables go out first (coalesced), then the gathers they address
+    int wv = d.gv_idx[w0 + (int(threadIdx.x) < wn ? int(threadIdx.x) : 0)];
+    int nb[4];
     R w[4], r[4], uo[4], po[4];
     const uint32_t sl = d.fvc_slot[i];
+    const uint2 cv = reinterpret_cast<const uint2*>(d.g_cell)[2 * i + 1];   // its vertices
     load_quad(d.cell_nb, nc, i, nb);
-    load_quad(d.fvc_vid, nc, i, vid);
+    load_quad(a.uf, nc, i, uo);
+    const R ui = uin[i];
+    load_quad(a.cphi, nc, i, po);                          // outward
     load_quad(a.cw, nc, i, w);
     load_quad(a.cr, nc, i, r);
-    load_quad(a.uf, nc, i, uo);
-    load_quad(a.cphi, nc, i, po);                      // outward
-    const R ui = uin[i], base = a.u[i], vol = w[3], src = a.src[i];
+    const R base = a.u[i], vol = w[3], src = a.src[i];
     const R D = R(d.mesh_D[m]), a_dt = R(alpha * d.mesh_dt[m]);
+    const R wval = a.unode[wv];
     R un[4], ux[4], uv[4];
+    int in_tile[4];                                        // the neighbour's place in the tile, or -1
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
-        un[k] = uin[nb[k]];                            // a ghost's value behind a boundary face
-        uv[k] = a.unode[vid[k]];
-        ux[k] = R(0);
-        if (nb[k] < nc && po[k] < R(0)) ux[k] = quad_value(a.uf, nc, nb[k], int((sl >> (2 * k)) & 3u));
+        const int64_t l = nb[k] - t0;
+        in_tile[k] = l >= 0 && l < T && nb[k] < nc ? int(l) : -1;
+        const bool far = in_tile[k] < 0;
+        un[k] = uin[far ? int64_t(nb[k]) : i];             // a ghost's value behind a boundary face
+        const bool across = far && nb[k] < nc && po[k] < R(0);
+        ux[k] = quad_value(a.uf, nc, across ? int64_t(nb[k]) : i, across ? int((sl >> (2 * k)) & 3u) : 0);
     }
+    su[threadIdx.x] = ui;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) sf[k * T + threadIdx.x] = uo[k];
+    if (int(threadIdx.x) < wn) sv[threadIdx.x] = wval;
+    for (int v = T + threadIdx.x; v < wn; v += T) {
+        wv = d.gv_idx[w0 + v];
+        sv[v] = a.unode[wv];
+    }
+    __syncthreads();
+    if (!cell) return;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        const int l = in_tile[k] < 0 ? int(threadIdx.x) : in_tile[k];
+        const R u_l = su[l], f_l = sf[int((sl >> (2 * k)) & 3u) * T + l];
+        if (in_tile[k] >= 0) {
+            un[k] = u_l;
+            ux[k] = f_l;
+        }
+    }
+    uv[0] = sv[cv.x & 0xffff];
+    uv[1] = sv[cv.x >> 16];
+    uv[2] = sv[cv.y & 0xffff];
+    uv[3] = sv[cv.y >> 16];
     R dif = R(0);
 #pragma unroll
     for (int k = 0; k < 3; ++k) dif += w[k] * (uv[k] - uv[3]);
@@ -709,6 +744,12 @@ size_t grad_lds_bytes(const Dev& d) {
     return (size_t(2 * d.g_max + 5 * d.gv_max) * 2 + d.gv_max) * sizeof(R);
 }
 
+// the cell step's: five values per cell of a tile, one per vertex (at most 18 KB)
+template <class R>
+size_t step_lds_bytes(const Dev& d) {
+    return size_t(5 * d.g_rows + d.gv_max) * sizeof(R);
+}
+
 template <class R, bool PARTS>
 hipError_t allow_lds(const Dev& d) {
     const size_t lds = grad_lds_bytes<R>(d);
@@ -765,12 +806,13 @@ hipError_t launch_face_flux(const Dev& d, bool fp32, const BcTable& bc, hipStrea
 
 hipError_t launch_cell_step(const Dev& d, bool fp32, const BcTable& bc, const void* u_in, void* u_out,
                             double alpha, hipStream_t s) {
-    const BlockOrder o = stream_order(d.nc, kBlock);
+    const BlockOrder o = stream_order(d.g_tiles, 1);
+    const dim3 g(o.grid), b(d.g_rows);
     if (fp32)
-        hipLaunchKernelGGL(k_cell_step<float>, dim3(o.grid), dim3(kBlock), 0, s, d, fv32(d), bc,
+        hipLaunchKernelGGL(k_cell_step<float>, g, b, step_lds_bytes<float>(d), s, d, fv32(d), bc,
                            static_cast<const float*>(u_in), static_cast<float*>(u_out), alpha, o);
     else
-        hipLaunchKernelGGL(k_cell_step<double>, dim3(o.grid), dim3(kBlock), 0, s, d, fv64(d), bc,
+        hipLaunchKernelGGL(k_cell_step<double>, g, b, step_lds_bytes<double>(d), s, d, fv64(d), bc,
                            static_cast<const double*>(u_in), static_cast<double*>(u_out), alpha, o);
     return hipGetLastError();
 }

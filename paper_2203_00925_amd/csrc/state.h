@@ -90,7 +90,7 @@ struct Dev {
     // diffusion weights and the volume, the kRL weights over its interior
     // faces, and per face k the slot of the same face among the neighbour's
     // faces (2 bits per face)
-    int32_t *cell_nb, *fvc_vid;
+    int32_t* cell_nb;
     double *fvc_w, *fvc_r;
     uint8_t* fvc_slot;
     double* fvc_phi;                      // outward phi of the cell's faces (with phi)
