@@ -117,6 +117,7 @@ size_t layout(const Mesh& m, char* base, Dev& d) {
     d.u_b = carve<double>(base, off, NX);
     d.u_c = carve<double>(base, off, NX);
     d.cell_nb = carve<int32_t>(base, off, 4 * nc);
+    d.cell_cv = carve<uint2>(base, off, nc);
     d.fvc_w = carve<double>(base, off, 4 * nc);
     d.fvc_r = carve<double>(base, off, 4 * nc);
     d.fvc_slot = carve<uint8_t>(base, off, nc);

@@ -413,6 +413,7 @@ __global__ __launch_bounds__(kBlock) void k_fv_cell_setup(Dev d) {
     const float w32[4] = {float(w[0]), float(w[1]), float(w[2]), float(w[3])};
     const float r32[4] = {float(r[0]), float(r[1]), float(r[2]), float(r[3])};
     store_quad(d.cell_nb, nc, i, across);
+    d.cell_cv[i] = make_uint2(cl.z, cl.w);
     store_quad(d.fvc_w, nc, i, w);
     store_quad(d.fvc_r, nc, i, r);
     store_quad(d.fvc_w32, nc, i, w32);
@@ -452,7 +453,7 @@ __global__ __launch_bounds__(kBlock) void k_cell_step(Dev d, FvArrays<R> a, BcTa
     int nb[4];
     R w[4], r[4], uo[4], po[4];
     const uint32_t sl = d.fvc_slot[i];
-    const uint2 cv = reinterpret_cast<const uint2*>(d.g_cell)[2 * i + 1];   // its vertices
+    const uint2 cv = d.cell_cv[i];                         // its vertices
     load_quad(d.cell_nb, nc, i, nb);
     load_quad(a.uf, nc, i, uo);
     const R ui = uin[i];

@@ -91,6 +91,7 @@ struct Dev {
     // faces, and per face k the slot of the same face among the neighbour's
     // faces (2 bits per face)
     int32_t* cell_nb;
+    uint2* cell_cv;
     double *fvc_w, *fvc_r;
     uint8_t* fvc_slot;
     double* fvc_phi;                      // outward phi of the cell's faces (with phi)
