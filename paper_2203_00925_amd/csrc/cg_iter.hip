@@ -75,6 +75,73 @@ __global__ __launch_bounds__(kBlock) void k_cg_product(Dev d) {
     if (threadIdx.x == 0) d.partial[lb] = v[0];
 }
 
+// The same for one mesh in gradient tiles of 256 cells, FP64 and FP32: the
+// tile's own p, which 85% of its cells' neighbours are, and the vertex values
+// its cells touch (0.49 per cell instead of 4, named by 16-bit local numbers)
+// go through LDS; a neighbour outside is gathered, and lanes without one read
+// their own cell's line.
+template <class R>
+__global__ __launch_bounds__(kBlock) void k_cg_product_tiles(Dev d) {
+    extern __shared__ __align__(16) unsigned char sp_raw[];
+    __shared__ double lds[kMaxWaves];
+    R* const sx = reinterpret_cast<R*>(sp_raw);            // [256] p
+    R* const sv = sx + kBlock;                             // vertex values
+    const int64_t lb = xcd_block();
+    if (lb >= d.cg_pblk) return;
+    double* sc = d.scal;
+    if (lb == 0 && threadIdx.x == 0) commit(sc);
+    if (sc[SC_N_DONE] != 0.0) return;
+    const int64_t nc = d.nc;
+    const R* __restrict__ p = CgVec<R>::p(d);
+    const R* __restrict__ pv = reinterpret_cast<const R*>(d.mf_xv);
+    R* __restrict__ q = CgVec<R>::q(d);
+    double v[1] = {0.0};
+    const int64_t r1 = (lb + 1) * d.cg_prows;
+    for (int64_t t0 = lb * d.cg_prows; t0 < r1 && t0 < nc; t0 += kBlock) {
+        const int64_t t = t0 / kBlock, row = t0 + threadIdx.x, i = row < nc ? row : nc - 1;
+        const int64_t w0 = d.gv_off[t];
+        const int wn = int(d.gv_off[t + 1] - w0);
+        const int wv = d.gv_idx[w0 + (int(threadIdx.x) < wn ? int(threadIdx.x) : 0)];
+        int nb[4];
+        R w[3], r[4];
+        const uint2 cv = d.cell_cv[i];
+        load_quad(d.cell_nb, nc, i, nb);
+        load_weights(MfCell<R>::w(d), nc, i, w);
+        load_quad(MfCell<R>::r(d), nc, i, r);
+        const R xi = p[i], wval = pv[wv];
+        R xn[4];
+        int in_tile[4];                                    // the neighbour's place in the tile, or -1
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const int64_t l = nb[k] - t0;
+            const bool bnd = nb[k] >= nc;                  // a boundary face takes x_i
+            in_tile[k] = l >= 0 && l < kBlock && !bnd ? int(l) : -1;
+            xn[k] = p[in_tile[k] < 0 && !bnd ? int64_t(nb[k]) : i];
+        }
+        if (t0 != lb * d.cg_prows) __syncthreads();        // the last tile's readers
+        sx[threadIdx.x] = xi;
+        if (int(threadIdx.x) < wn) sv[threadIdx.x] = wval;
+        for (int u = kBlock + threadIdx.x; u < wn; u += kBlock) sv[u] = pv[d.gv_idx[w0 + u]];
+        __syncthreads();
+        const R x0 = sv[cv.x & 0xffff], x1 = sv[cv.x >> 16], x2 = sv[cv.y & 0xffff], x3 = sv[cv.y >> 16];
+        R acc = w[0] * (x0 - x3);
+        acc += w[1] * (x1 - x3);
+        acc += w[2] * (x2 - x3);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const R xl = sx[in_tile[k] < 0 ? int(threadIdx.x) : in_tile[k]];
+            const R x = in_tile[k] < 0 ? xn[k] : xl;
+            acc += r[k] * (nb[k] < nc ? x - xi : x);
+        }
+        if (row < nc) {
+            q[i] = -acc;
+            v[0] -= double(xi) * double(acc);
+        }
+    }
+    block_sums<1>(v, lds);
+    if (threadIdx.x == 0) d.partial[lb] = v[0];
+}
+
 // The same on the stored matrix (one mesh): a block takes `tiles` consecutive
 // cell tiles, each tile's halo of p staged in LDS and addressed by 16-bit
 // local indices; the entries of a row in stored order.
@@ -135,9 +202,9 @@ __global__ __launch_bounds__(512) void k_cg_residual(Dev d, int np) {
     if (lb >= d.cg_nblk) return;
     const Seg s = cg_seg(d, lb);
     const R* __restrict__ q = CgVec<R>::q(d);
+    R* __restrict__ z = CgVec<R>::z(d);
     const R* __restrict__ dinv = CgVec<R>::dinv(d);
     R* __restrict__ r = CgVec<R>::r(d);
-    R* __restrict__ z = CgVec<R>::z(d);
     const int T = blockDim.x;
     // the first row's loads go out before the scalars are known
     int64_t i = s.r0 + threadIdx.x;
@@ -157,7 +224,7 @@ __global__ __launch_bounds__(512) void k_cg_residual(Dev d, int np) {
     for (; i < s.r1; i += T) {
         const int64_t n = i + T;
         c = n < last ? n : last;
-        const R rn = r[c], qn = q[c], dn = dinv[c];    // the next row's, in flight
+        const R rn = r[c], qn = q[c], dn = dinv[c];       // the next row's, in flight
         const R rc = ri - a * qi;
         const R zc = di * rc;
         r[i] = rc;
@@ -332,6 +399,13 @@ namespace {
 int stored_tiles(const Dev& d) { return int((d.ntiles + kCgMaxProductBlocks - 1) / kCgMaxProductBlocks); }
 }  // namespace
 
+namespace {
+// The product by tiles: 131k cells and more (two tiles a CU).  Below, its
+// barrier costs more than its gathers save: 48k cells 4.50 ms against 4.39; above,
+// 162k 9.84 against 10.04, 4.4M 361 against 372, refined 384k 16.4 against 17.2.
+bool tiled_product(const Dev& d) { return d.nm == 1 && d.g_rows == kBlock && d.g_tiles >= 512; }
+}  // namespace
+
 int cg_product_parts(const Dev& d, bool stored) {
     return stored ? int((d.ntiles + stored_tiles(d) - 1) / stored_tiles(d)) : int(d.cg_pblk);
 }
@@ -346,6 +420,9 @@ hipError_t cg_part(const Dev& d, bool stored, int part, hipStream_t s) {
     if (part == 0 && stored)
         hipLaunchKernelGGL(k_cg_product_stored<R>, dim3(nst), dim3(d.tile_rows), size_t(d.halo_max) * sizeof(R), s, d,
                            tiles);
+    else if (part == 0 && tiled_product(d))
+        hipLaunchKernelGGL(k_cg_product_tiles<R>, dim3(pad8(d.cg_pblk)), dim3(kBlock),
+                           size_t(kBlock + d.gv_max) * sizeof(R), s, d);
     else if (part == 0)
         hipLaunchKernelGGL(k_cg_product<R>, dim3(pad8(d.cg_pblk)), dim3(kBlock), 0, s, d);
     else if (part == 1)

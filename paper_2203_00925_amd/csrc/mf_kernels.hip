@@ -124,19 +124,14 @@ __global__ __launch_bounds__(kBlock) void k_mf_cell_setup(Dev d, BcTable bc) {
     const int64_t i = gtid_m();
     if (i >= d.nc) return;
     const int64_t nc = d.nc;
-    int vid[4] = {-1, -1, -1, -1};
+    // the cell's vertices, k across from face k
+    const uint4 cl = d.g_cell[i];
+    const int32_t* __restrict__ tv = d.gv_idx + d.gv_off[i / d.g_rows];
+    const int vid[4] = {tv[cl.z & 0xffff], tv[cl.z >> 16], tv[cl.w & 0xffff], tv[cl.w >> 16]};
     double w[4] = {0.0, 0.0, 0.0, 0.0}, r[4] = {0.0, 0.0, 0.0, 0.0};
-    auto add = [&](int v, double c) {                 // the vertex's slot (first seen, first slot)
-        bool done = false;
+    auto add = [&](int v, double c) {
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const bool hit = !done && (vid[q] == v || vid[q] < 0);
-            if (hit) {
-                vid[q] = v;
-                w[q] += c;
-            }
-            done = done || hit;
-        }
+        for (int q = 0; q < 4; ++q) w[q] += vid[q] == v ? c : 0.0;
     };
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
@@ -151,11 +146,6 @@ __global__ __launch_bounds__(kBlock) void k_mf_cell_setup(Dev d, BcTable bc) {
         add(d.fC[f], sg * (-(kac + kbc)));
         r[k] = bnd ? -2.0 * krl : krl;
     }
-    // unused slots (a cell none of whose faces is in K) point at a used
-    // vertex, or vertex 0, with weight 0
-    const int v0 = vid[0] >= 0 ? vid[0] : 0;
-#pragma unroll
-    for (int q = 0; q < 4; ++q) vid[q] = vid[q] >= 0 ? vid[q] : v0;
     store_quad(d.mfc_vid, nc, i, vid);
 #pragma unroll
     for (int q = 0; q < 3; ++q) {                     // the fourth weight is minus their sum
