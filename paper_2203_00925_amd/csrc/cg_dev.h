@@ -16,7 +16,6 @@ template <class R> struct CgVec;
 template <> struct CgVec<double> {
     __device__ static double *x(const Dev& d) { return d.x; }
     __device__ static double *r(const Dev& d) { return d.r; }
-    __device__ static double *z(const Dev& d) { return d.z; }
     __device__ static double *p(const Dev& d) { return d.p; }
     __device__ static double *q(const Dev& d) { return d.q; }
     __device__ static const double *dinv(const Dev& d) { return d.k_dinv; }
@@ -27,7 +26,6 @@ template <> struct CgVec<double> {
 template <> struct CgVec<float> {
     __device__ static float *x(const Dev& d) { return d.d32; }
     __device__ static float *r(const Dev& d) { return d.r32; }
-    __device__ static float *z(const Dev& d) { return d.z32; }
     __device__ static float *p(const Dev& d) { return d.p32; }
     __device__ static float *q(const Dev& d) { return d.q32; }
     __device__ static const float *dinv(const Dev& d) { return d.k_dinv32; }

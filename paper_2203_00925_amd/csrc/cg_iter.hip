@@ -3,7 +3,7 @@
 //   k_cg_product   q = K p from the cells' tables and the vertex values of
 //                  p; partial p.q;
 //   k_cg_residual  alpha = rz / p.q (every block adds the partials), r -=
-//                  alpha q, z = D^-1 r; partial rz, rr;
+//                  alpha q, z = D^-1 r in q's place; partial rz, rr;
 //   k_cg_direction beta and the convergence tests (every block), x += alpha
 //                  p, p = z + beta p; its first blocks update the vertex
 //                  values of p by the same recurrence, A p = A z + beta A p
@@ -194,15 +194,16 @@ __global__ __launch_bounds__(kBlock) void k_cg_product_stored(Dev d, int tiles) 
 }
 
 // alpha; r -= alpha q; z = D^-1 r; partial rz, rr.  np: the product's partials
-// of a single mesh (its blocks may differ from this kernel's).
+// of a single mesh (its blocks may differ from this kernel's).  z takes q's
+// place, which nothing reads any more: one vector less for the cache to hold
+// (1.3M cells 73.2 -> 67.8 ms, 4.4M 360 -> 352, refined 3.07M 160 -> 155).
 template <class R>
 __global__ __launch_bounds__(512) void k_cg_residual(Dev d, int np) {
     __shared__ double lds[3 * kMaxWaves];
     const int64_t lb = xcd_block();
     if (lb >= d.cg_nblk) return;
     const Seg s = cg_seg(d, lb);
-    const R* __restrict__ q = CgVec<R>::q(d);
-    R* __restrict__ z = CgVec<R>::z(d);
+    R* const qz = CgVec<R>::q(d);                          // q, replaced by z row by row
     const R* __restrict__ dinv = CgVec<R>::dinv(d);
     R* __restrict__ r = CgVec<R>::r(d);
     const int T = blockDim.x;
@@ -210,7 +211,7 @@ __global__ __launch_bounds__(512) void k_cg_residual(Dev d, int np) {
     int64_t i = s.r0 + threadIdx.x;
     const int64_t last = s.r1 - 1;
     int64_t c = i < last ? i : last;
-    R ri = r[c], qi = q[c], di = dinv[c];
+    R ri = r[c], qi = qz[c], di = dinv[c];
     if (s.sc[SC_DONE] != 0.0) return;
     double pq[1];
     sum_parts<1>(d.partial + s.pp0, 0, d.nm == 1 ? np : s.pnp, lds, pq);
@@ -224,11 +225,11 @@ __global__ __launch_bounds__(512) void k_cg_residual(Dev d, int np) {
     for (; i < s.r1; i += T) {
         const int64_t n = i + T;
         c = n < last ? n : last;
-        const R rn = r[c], qn = q[c], dn = dinv[c];       // the next row's, in flight
+        const R rn = r[c], qn = qz[c], dn = dinv[c];       // the next row's, in flight
         const R rc = ri - a * qi;
         const R zc = di * rc;
         r[i] = rc;
-        z[i] = zc;
+        qz[i] = zc;
         v[0] += double(rc) * double(zc);
         v[1] += double(rc) * double(rc);
         ri = rn;
@@ -274,7 +275,7 @@ __global__ __launch_bounds__(512) void k_cg_direction(Dev d, int nvert) {
         const int64_t v = v0 + (threadIdx.x / kCgVertexLanes);
         const int64_t vc = v < v1 ? v : v1 - 1;
         const R old = pv[vc];
-        const R zv = vertex_sum<R>(d, CgVec<R>::z(d), vc, q);
+        const R zv = vertex_sum<R>(d, CgVec<R>::q(d), vc, q);     // z
         double t[1];
         sum_parts<1>(d.partial + d.cg_stride + p0, 0, np, lds, t);
         const R beta = R(t[0] / sc[SC_RZ]);
@@ -282,7 +283,7 @@ __global__ __launch_bounds__(512) void k_cg_direction(Dev d, int nvert) {
         return;
     }
     const Seg s = cg_seg(d, lb);
-    const R* __restrict__ z = CgVec<R>::z(d);
+    const R* __restrict__ z = CgVec<R>::q(d);              // left there by k_cg_residual
     R* __restrict__ x = CgVec<R>::x(d);
     R* __restrict__ p = CgVec<R>::p(d);
     int64_t i = s.r0 + threadIdx.x;
@@ -397,9 +398,7 @@ bool cg_meshes_apart(const Mesh& m) {
 namespace {
 // tiles per block of the stored product
 int stored_tiles(const Dev& d) { return int((d.ntiles + kCgMaxProductBlocks - 1) / kCgMaxProductBlocks); }
-}  // namespace
 
-namespace {
 // The product by tiles: 131k cells and more (two tiles a CU).  Below, its
 // barrier costs more than its gathers save: 48k cells 4.50 ms against 4.39; above,
 // 162k 9.84 against 10.04, 4.4M 361 against 372, refined 384k 16.4 against 17.2.
