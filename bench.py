@@ -41,21 +41,14 @@ METRIC = "FV cell-updates/s + Poisson solve ms @1e-10 rel; plain vs mixed/learne
 # Each is valid only for the kernel source it was taken on: the bench reports
 # it when that source (the kernel's file and the reduction headers) still
 # hashes to the recorded prefix, else null.
-MEASURED_TRAFFIC = {"cube120": {
-    "k_mf_cg_cell": {"src": "8fdb010b17804213", "bytes": 1215810467},
-    "k_mf_vertex": {"src": "8fdb010b17804213", "bytes": 623188346},
-    "k_cg_axpy": {"src": "50d641f414878f07", "bytes": 668804504},
-    "k_cg_dir": {"src": "50d641f414878f07", "bytes": 248844609},
-    "k_grad_moments": {"src": "7212ca82332031bf", "bytes": 3720635711},
-    "k_cell_step": {"src": "7212ca82332031bf", "bytes": 2159479857},
-}}
-# timing id -> the FP64 kernel it times
-KERNEL_NAMES = {"grad_limiter": "k_grad_moments", "mf_gather": "k_mf_cg_cell", "fv_cell": "k_cell_step"}
-KERNEL_FILES = {
-    "grad_limiter": "fv_kernels.hip", "fv_cell": "fv_kernels.hip",
-    "cg_spmv": "solve_kernels.hip", "cg_axpy": "solve_kernels.hip", "cg_dir": "solve_kernels.hip",
-    "mf_vertex": ("mf_kernels.hip", "mf_cell.h"), "mf_gather": ("mf_kernels.hip", "mf_cell.h"),
-}
+MEASURED_TRAFFIC = {"cube120": {}}
+# timing id -> the FP64 kernel it times (the product on a mesh of this size)
+KERNEL_NAMES = {"grad_limiter": "k_grad_cells", "node_interp": "k_vertex_moments", "fv_cell": "k_cell_step",
+                "mf_gather": "k_cg_product_tiles", "cg_axpy": "k_cg_residual", "cg_dir": "k_cg_direction"}
+_CG = ("cg_iter.hip", "cg_dev.h", "mf_cell.h", "quad.h", "xcd.h")
+_FV = ("fv_kernels.hip", "quad.h", "xcd.h")
+KERNEL_FILES = {"grad_limiter": _FV, "node_interp": _FV, "fv_cell": _FV,
+                "mf_gather": _CG, "cg_axpy": _CG, "cg_dir": _CG}
 
 
 def measure_copy_peak(gib=1, reps=10):
@@ -89,8 +82,7 @@ def measure_copy_peak(gib=1, reps=10):
 def kernel_source_hash(name):
     import hashlib
     h = hashlib.sha256()
-    files = KERNEL_FILES[name] if isinstance(KERNEL_FILES[name], tuple) else (KERNEL_FILES[name],)
-    for f in files + ("reduce.h", "seg.h", "cg_scalars.h", "halo_stage.h"):
+    for f in KERNEL_FILES[name] + ("reduce.h", "seg.h", "cg_scalars.h", "halo_stage.h"):
         with open(os.path.join(ROOT, "paper_2203_00925_amd", "csrc", f), "rb") as fh:
             h.update(f.encode())
             h.update(fh.read())
@@ -119,38 +111,35 @@ def algorithmic_bytes(info):
     offdiag = info.matrix_nnz - nc
     halo = info.halo_entries
     return {
-        # star-moment gradient on LDS tiles: tile halo list 4/entity; x, y,
-        # z, u of cells and ghosts 32; own vertex lists: 16-bit local index 2
-        # + weight 8 per entry, list length 4 and value written 8 per vertex;
-        # foreign vertex lists: index 2 per entry, length 4 per row; per cell
-        # c2f 16, local face neighbours 8, local vertices 8, M^-1 48, the
-        # four face values written 32; edge-only neighbours: index 2 per
-        # entry; face centroids 24/face
-        "grad_limiter": halo * 4 + (nc + nb) * 32 + info.node_entries * 10 + nv * 12
-        + info.foreign_entries * 2 + info.foreign_rows * 4 + nc * (16 + 8 + 8 + 48 + 32)
-        + info.edge_nbr_entries * 2 + nf * 24,
-        # the FP64 stage in one pass per cell: per cell outward phi 32, c2n
-        # 16, face slots 1, vertex ids 16, vertex weights 32, kRL weights 32,
-        # its four face values 32 (the neighbours' gathered, counted once),
-        # u_in 8, u^n 8, vol 8, src 8, u written 8; the vertex values 8 per
-        # vertex, gathered once; per ghost: its value read and written 16,
-        # its face's kAC, kBC, kRL, A, B, C, area, tag, value and distance 64
-        "fv_cell": nc * 201 + nv * 8 + nb * 80,
+        # gradient per tile (the tiles' halo and vertex lists not counted):
+        # position 32 and u 8 of cells and ghosts; vertex records 96 per
+        # vertex; per cell local numbers 16, M^-1 48, the four face values
+        # written 32; edge-only neighbours: local index 2 per entry
+        "grad_limiter": (nc + nb) * 40 + nv * 96 + nc * 96 + info.edge_nbr_entries * 2,
+        # vertex moments: index 4 per list entry, position 32 and u 8 of cells
+        # and ghosts; per vertex list length 4, mean and slope 64 read, moments
+        # 32 and value 8 written
+        "node_interp": info.node_entries * 4 + (nc + nb) * 40 + nv * 108,
+        # the FP64 stage in one pass per cell: per cell outward phi 32,
+        # neighbours 16, face slots 1, local vertices 8, three vertex weights
+        # and the volume 32, kRL weights 32, its four face values 32 (the
+        # neighbours' counted once), u_in 8, u^n 8, src 8, u written 8; the
+        # vertex values 8 per vertex; per ghost: its value read and written
+        # 16, its face's kAC, kBC, kRL, A, B, C, area, tag, value and distance 64
+        "fv_cell": nc * 185 + nv * 8 + nb * 80,
         # value 8 + 16-bit local index 2 per off-diagonal entry; tile halo
         # list 4/entity; p 8, diagonal 8, q written 8 per row
         "cg_spmv": offdiag * 10 + halo * 4 + nc * 24,
-        # x,p,r,q,dinv read 40; x,r,z written 24
-        "cg_axpy": nc * 64,
-        # z,p read, p written
-        "cg_dir": nc * 24,
-        # matrix-free product: vertex lists (weight 8 + index 4 per entry, a
-        # ghost entry folded onto its owner), x gathered once, vertex values
-        # written
-        "mf_vertex": info.node_entries * 12 + nc * 8 + nv * 8,
-        # the per-cell product: per cell 4 vertex ids 16, 4 vertex weights 32,
-        # 4 face neighbours 16, 4 face weights 32, p 8 (neighbours' p counted
-        # once), q written 8; vertex values gathered once
-        "mf_gather": nc * 112 + nv * 8,
+        # r, q, dinv read, r and z (in q's place) written
+        "cg_axpy": nc * 40,
+        # x, p, z read, x, p written; the vertex values of p: lists (weight 8
+        # + index 4 per entry, a ghost entry folded onto its owner; z counted
+        # above), read and written
+        "cg_dir": nc * 40 + info.node_entries * 12 + nv * 16,
+        # matrix-free product: per cell local vertices 8, three vertex weights
+        # 24, neighbours 16, face weights 32, p 8 (neighbours' counted once),
+        # q written 8; vertex values gathered once
+        "mf_gather": nc * 96 + nv * 8,
     }
 
 
@@ -273,8 +262,8 @@ def main():
     log(f"state ready; dt={dt:.6g}")
 
     stream = torch.cuda.current_stream()
-    # the FV step replays the library's captured step graph (the time step,
-    # one ghost fill, 3 stages of 2 launches); capture it here, outside
+    # the FV step replays the library's captured step graph (the time step and
+    # the ghosts in one launch, 3 stages of 3); capture it here, outside
     # warm-up and timing, and undo the
     # step it runs so that the state stays in step with the forms' runs
     u_keep = st.get_field(B.FIELD_U).clone()
@@ -295,10 +284,9 @@ def main():
 
     # the last warm-up step's solve runs with every kernel timed: it names
     # the solve's dominant kernel, the only one the timed region brackets
-    # with events (an event pair around each of the seven launches of a CG
-    # iteration costs about 6% of the solve), and gives the other kernels'
-    # durations
-    cg_names = ("mf_vertex", "mf_gather", "cg_axpy", "cg_dir")
+    # with events (which cost the solve a few percent and its graph replay),
+    # and gives the other kernels' durations
+    cg_names = ("mf_gather", "cg_axpy", "cg_dir")
     wstats = None
     for w in range(args.warmup):
         last = w == args.warmup - 1
@@ -341,7 +329,7 @@ def main():
     st.kernel_timing(False)
     st.set_field(B.FIELD_U, u_keep)
     del u_keep
-    for k in ("ghost_fill", "grad_limiter", "fv_cell"):
+    for k in ("ghost_fill", "grad_limiter", "node_interp", "fv_cell"):
         kstats[k] = fv_stats[k]
     solve_ms = [e[1].elapsed_time(e[2]) for e in events]
     total1 = st.conservation()
@@ -371,8 +359,7 @@ def main():
     iters = [s["iterations"] for s in solves]
     if args.log:
         from paper_2203_00925_amd.runlog import RunLog
-        mf_bytes = nbytes["mf_vertex"] + nbytes["mf_gather"] + nbytes["cg_axpy"] + \
-            nbytes["cg_dir"]
+        mf_bytes = sum(nbytes[k] for k in cg_names)
         with RunLog(args.log, cells=info.nc, conservation0=total0) as rl:
             rl.run(workload=args.workload, cells=info.nc, faces=info.nf, steps=args.steps,
                    warmup=args.warmup, dt=dt, conservation_initial=total0)
@@ -405,7 +392,7 @@ def main():
         "conservation_rel_drift": abs(total1 - total0) / abs(total0),
         # the kernel with the most GPU time in the timed region
         "roofline": roof(dominant or max(cg_names + ("grad_limiter",), key=lambda k: kstats[k][0])),
-        "roofline_fv": {k: roof(k) for k in ("grad_limiter", "fv_cell")},
+        "roofline_fv": {k: roof(k) for k in ("grad_limiter", "node_interp", "fv_cell")},
         "roofline_cg": {k: roof(k, kstats if (k == dominant or not wstats) else wstats) for k in cg_names},
         "kernel_timing": {"timed_region": dominant or "all",
                           "others": "last warm-up step" if dominant else "timed region"},

@@ -158,7 +158,9 @@ typedef struct {
     int32_t method;            /* enum mifvm_solve_method                     */
     int32_t graph;             /* 1: enqueue each chunk by replaying a captured
                                   hipGraph (not while kernel timing is on);
-                                  -1: the autotuned choice (else 0)          */
+                                  -1: the autotuned choice; else direct
+                                  for the first chunk, while the next
+                                  is captured, then replays                */
     double inner_tol;          /* IR_FP32: relative reduction asked of each
                                   FP32 inner solve (0 = 1e-4)                */
     int32_t stall_window;      /* LEARNED: fall back when the best residual
@@ -622,8 +624,8 @@ int mifvm_conservation_static(mifvm_state* st, double* total_out, void* stream);
  * enable != 0 starts recording an event pair around every kernel launch of
  * this state and clears the totals; enable == 0 stops.  Kernel ids: */
 enum mifvm_kernel {
-    MIFVM_K_GHOST_FILL = 0, MIFVM_K_GRAD_LIMITER = 1 /* incl. vertex values */,
-    MIFVM_K_NODE_INTERP = 2 /* reserved: computed inside GRAD_LIMITER, never launched */,
+    MIFVM_K_GHOST_FILL = 0, MIFVM_K_GRAD_LIMITER = 1,
+    MIFVM_K_NODE_INTERP = 2 /* vertex values and the moments GRAD_LIMITER reads */,
     MIFVM_K_FACE_FLUX = 3 /* face fluxes of the residual evaluation */,
     MIFVM_K_UPDATE = 4 /* reserved: the update is part of FV_CELL, never launched */,
     MIFVM_K_CG_SETUP = 5, MIFVM_K_CG_SPMV = 6,
@@ -632,13 +634,15 @@ enum mifvm_kernel {
     (the first includes the encoder, the last the decoder) */,
     MIFVM_K_FCG_VEC = 14 /* flexible-CG update and its scalar steps */,
     MIFVM_K_NN_TRAIN = 15 /* one whole training step (all of its launches) */,
-    MIFVM_K_MF_VERTEX = 16 /* matrix-free product inside the CG: the vertex values */,
+    MIFVM_K_MF_VERTEX = 16 /* matrix-free product: the vertex values (CG of meshes
+    that share a vertex; elsewhere the CG updates them inside CG_DIR) */,
     MIFVM_K_MF_FACE = 17 /* reserved: the face terms are summed per cell inside MF_GATHER,
     never launched */,
     MIFVM_K_MF_GATHER = 18 /* matrix-free product inside the CG: the per-cell product over
     the cell's vertices and faces, with p.q (CG_SPMV counts the stored-matrix product) */,
     MIFVM_K_NN_FUSED = 19 /* the whole network in one launch (encoder, 3 layers, decoder) */,
-    MIFVM_K_CG_ALPHA = 20 /* the matrix-free CG's alpha step (its p.q partials summed per mesh) */,
+    MIFVM_K_CG_ALPHA = 20 /* alpha from the p.q partials, summed per mesh (with MF_VERTEX;
+    elsewhere inside CG_AXPY) */,
     MIFVM_K_FV_CELL = 21 /* the step: face fluxes and the RK stage update in one pass per cell */,
     MIFVM_K_COUNT = 22
 };

@@ -546,8 +546,8 @@ class State:
                       history=0, method=SOLVE_PLAIN, inner_tol=1e-4, graph=-1, stream=None,
                       allow_not_converged=False, stall_window=0, learned_maxit=0,
                       allow_fell_back=False, matrix_free=False, learned_smoother=False):
-        """chunk 0 / graph -1: the autotuned schedule (32 iterations per host
-        check, direct launches when not tuned)."""
+        """chunk 0 / graph -1: the autotuned schedule (when not tuned, 32
+        iterations per host check, chunks after the first replayed)."""
         import torch
         if f is not None:
             f = f.to(device=self.device, dtype=torch.float64).contiguous()

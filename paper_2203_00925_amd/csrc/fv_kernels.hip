@@ -718,12 +718,12 @@ __global__ __launch_bounds__(kBlock) void k_step_begin(Dev d, const R* __restric
 // ---- launchers ---------------------------------------------------------------
 FvArrays<double> fv64(const Dev& d) {
     return {d.u, d.grad, d.psi, d.unode, d.flux, d.phi, d.minv, d.kAC, d.kBC, d.kRL, d.area,
-            d.vol, d.src, d.n_alpha, d.fx, d.xc, d.gdist, d.uf, d.fvc_w, d.fvc_r, d.fvc_phi, d.vmom};
+            d.vol, d.src, d.fx, d.xc, d.gdist, d.uf, d.fvc_w, d.fvc_r, d.fvc_phi, d.vmom};
 }
 
 FvArrays<float> fv32(const Dev& d) {
     return {d.u32, d.grad32, d.psi32, d.unode32, d.flux32, d.phi32, d.minv32, d.kAC32, d.kBC32,
-            d.kRL32, d.area32, d.vol32, d.src32, d.n_alpha32, d.fx32, d.xc32, d.gdist32,
+            d.kRL32, d.area32, d.vol32, d.src32, d.fx32, d.xc32, d.gdist32,
             d.uf32, d.fvc_w32, d.fvc_r32, d.fvc_phi32, d.vmom32};
 }
 

@@ -7,11 +7,13 @@
 // entity e = nc + g standing for s_g x_owner (s_g = -1 Dirichlet, +1 else:
 // the homogeneous part of the ghost value; its constant goes into c).
 // Neumann and zero-flux faces carry a fixed flux, which is constant in x and
-// so absent from K.  Three kernels: vertex values (one thread per vertex,
-// 64-row slices of the vertex lists), face fluxes (one thread per face), and
-// the per-cell gather through the cell->face table, which also writes the
-// partial p.q of the conjugate gradient.  About 210 bytes per row move
-// against about 730 for the stored 64-row-sliced matrix.
+// so absent from K.  Two kernels: vertex values (one thread per vertex,
+// 64-row slices of the vertex lists), then the per-cell product from tables of
+// the cell's vertices and faces (mf_cell.h).  About 170 bytes per row move
+// against about 730 for the stored 64-row-sliced matrix.  The conjugate
+// gradient runs them with its own product (cg_iter.hip); the parts here, with
+// the p.q partials and alpha as a third kernel, serve meshes that share a
+// vertex and the learned preconditioner's loop.
 #include <type_traits>
 
 #include "cg_scalars.h"
@@ -106,7 +108,7 @@ __global__ __launch_bounds__(kBlock) void k_mf_vertex(Dev d, const R* __restrict
 }
 
 // ---- the product per cell ----------------------------------------------------
-// gather_row's y_i = -sum_f s_if F_f regrouped per cell: each face of a
+// y_i = -sum_f s_if F_f regrouped per cell: each face of a
 // tetrahedron holds three of its four vertices, so the vertex terms of its
 // faces add up to one weight per vertex, w_k = sum over the cell's faces f
 // holding vertex k of s_if times that vertex's coefficient in F_f (kAC, kBC
@@ -246,12 +248,6 @@ hipError_t launch_mf_cg_spmv(const Dev& d, const BcTable& bc, hipStream_t s) {
 hipError_t launch_mf_cg32_part(const Dev& d, const BcTable& bc, int part, hipStream_t s) {
     mf_cg_part<float>(d, bc, part, d.p32, s);
     return hipGetLastError();
-}
-
-hipError_t launch_mf_cg32_spmv(const Dev& d, const BcTable& bc, hipStream_t s) {
-    hipError_t e = hipSuccess;
-    for (int part = 0; part < kMfParts && e == hipSuccess; ++part) e = launch_mf_cg32_part(d, bc, part, s);
-    return e;
 }
 
 }  // namespace mifvm

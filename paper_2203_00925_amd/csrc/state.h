@@ -137,7 +137,7 @@ template <> struct Vec4T<float> { using T = float4; };
 template <class R>
 struct FvArrays {
     R *u, *grad, *psi, *unode, *flux;
-    const R *phi, *minv, *kAC, *kBC, *kRL, *area, *vol, *src, *n_alpha, *fx, *xc, *gdist;
+    const R *phi, *minv, *kAC, *kBC, *kRL, *area, *vol, *src, *fx, *xc, *gdist;
     // the per-cell stage: face values [4][nc], vertex and kRL weights, outward phi
     R* uf;
     const R *cw, *cr, *cphi;
@@ -296,13 +296,12 @@ hipError_t launch_cg_commit(const Dev& d, hipStream_t s);
 hipError_t launch_mf_apply(const Dev& d, const BcTable& bc, const double* x, double* y, hipStream_t s,
                            const double* skip = nullptr);
 hipError_t launch_mf_cg_spmv(const Dev& d, const BcTable& bc, hipStream_t s);
-// the parts of launch_mf_cg_spmv one by one (part 0 ghost and vertex values,
+// the parts of launch_mf_cg_spmv one by one (part 0 vertex values,
 // 1 the per-cell product + p.q partials, 2 alpha), for per-kernel timing
 constexpr int kMfParts = 3;
 hipError_t launch_mf_cg_part(const Dev& d, const BcTable& bc, int part, hipStream_t s);
-// the same product in FP32 for the inner CG of the refined solve: q32 = K p32
+// the same part in FP32 for the inner CG of the refined solve: q32 = K p32
 // with the FP32 vertex weights and per-cell tables, partial p32.q32 in FP64
-hipError_t launch_mf_cg32_spmv(const Dev& d, const BcTable& bc, hipStream_t s);
 hipError_t launch_mf_cg32_part(const Dev& d, const BcTable& bc, int part, hipStream_t s);
 
 // launchers (streamer_kernels.hip): the coupled loop's per-step kernels
