@@ -81,13 +81,12 @@ __global__ __launch_bounds__(kBlock) void k_cg_product(Dev d) {
 // go through LDS; a neighbour outside is gathered, and lanes without one read
 // their own cell's line.
 template <class R>
-__global__ __launch_bounds__(kBlock) void k_cg_product_tiles(Dev d) {
+__global__ __launch_bounds__(kBlock) void k_cg_product_tiles(Dev d, BlockOrder order) {
     extern __shared__ __align__(16) unsigned char sp_raw[];
     __shared__ double lds[kMaxWaves];
     R* const sx = reinterpret_cast<R*>(sp_raw);            // [256] p
     R* const sv = sx + kBlock;                             // vertex values
-    const int64_t lb = xcd_block();
-    if (lb >= d.cg_pblk) return;
+    const int64_t lb = order.block();
     double* sc = d.scal;
     if (lb == 0 && threadIdx.x == 0) commit(sc);
     if (sc[SC_N_DONE] != 0.0) return;
@@ -96,9 +95,8 @@ __global__ __launch_bounds__(kBlock) void k_cg_product_tiles(Dev d) {
     const R* __restrict__ pv = reinterpret_cast<const R*>(d.mf_xv);
     R* __restrict__ q = CgVec<R>::q(d);
     double v[1] = {0.0};
-    const int64_t r1 = (lb + 1) * d.cg_prows;
-    for (int64_t t0 = lb * d.cg_prows; t0 < r1 && t0 < nc; t0 += kBlock) {
-        const int64_t t = t0 / kBlock, row = t0 + threadIdx.x, i = row < nc ? row : nc - 1;
+    for (int64_t t = lb; t < d.g_tiles; t += order.grid) {
+        const int64_t t0 = t * kBlock, row = t0 + threadIdx.x, i = row < nc ? row : nc - 1;
         const int64_t w0 = d.gv_off[t];
         const int wn = int(d.gv_off[t + 1] - w0);
         const int wv = d.gv_idx[w0 + (int(threadIdx.x) < wn ? int(threadIdx.x) : 0)];
@@ -118,7 +116,7 @@ __global__ __launch_bounds__(kBlock) void k_cg_product_tiles(Dev d) {
             in_tile[k] = l >= 0 && l < kBlock && !bnd ? int(l) : -1;
             xn[k] = p[in_tile[k] < 0 && !bnd ? int64_t(nb[k]) : i];
         }
-        if (t0 != lb * d.cg_prows) __syncthreads();        // the last tile's readers
+        if (t != lb) __syncthreads();        // the last tile's readers
         sx[threadIdx.x] = xi;
         if (int(threadIdx.x) < wn) sv[threadIdx.x] = wval;
         for (int u = kBlock + threadIdx.x; u < wn; u += kBlock) sv[u] = pv[d.gv_idx[w0 + u]];
@@ -403,10 +401,23 @@ int stored_tiles(const Dev& d) { return int((d.ntiles + kCgMaxProductBlocks - 1)
 // barrier costs more than its gathers save: 48k cells 4.50 ms against 4.39; above,
 // 162k 9.84 against 10.04, 4.4M 361 against 372, refined 384k 16.4 against 17.2.
 bool tiled_product(const Dev& d) { return d.nm == 1 && d.g_rows == kBlock && d.g_tiles >= 512; }
+// Its blocks take a tile a round: one round and contiguous eighths to 8,192
+// tiles, then as few rounds as that many partials allow, each over neighbouring
+// tiles in the step kernels' windows.  (A block's tiles in sequence instead put
+// the blocks at work so far apart that a neighbour outside the tile left the
+// L2: 3.07M cells refined 159 ms against 154, 4.4M 354 against 349.  Windows in
+// the one round: 1.3M 69 against 67 ms.)
+BlockOrder tile_order(const Dev& d) {
+    const int64_t rounds = (d.g_tiles + kCgMaxProductBlocks - 1) / kCgMaxProductBlocks;
+    if (rounds > 1) return stream_order((d.g_tiles + rounds - 1) / rounds, 1);
+    const unsigned g = pad8(d.g_tiles);
+    return {g, 28u, g / kXcds};
+}
 }  // namespace
 
 int cg_product_parts(const Dev& d, bool stored) {
-    return stored ? int((d.ntiles + stored_tiles(d) - 1) / stored_tiles(d)) : int(d.cg_pblk);
+    if (stored) return int((d.ntiles + stored_tiles(d) - 1) / stored_tiles(d));
+    return tiled_product(d) ? int(tile_order(d).grid) : int(d.cg_pblk);
 }
 
 namespace {
@@ -420,8 +431,8 @@ hipError_t cg_part(const Dev& d, bool stored, int part, hipStream_t s) {
         hipLaunchKernelGGL(k_cg_product_stored<R>, dim3(nst), dim3(d.tile_rows), size_t(d.halo_max) * sizeof(R), s, d,
                            tiles);
     else if (part == 0 && tiled_product(d))
-        hipLaunchKernelGGL(k_cg_product_tiles<R>, dim3(pad8(d.cg_pblk)), dim3(kBlock),
-                           size_t(kBlock + d.gv_max) * sizeof(R), s, d);
+        hipLaunchKernelGGL(k_cg_product_tiles<R>, dim3(tile_order(d).grid), dim3(kBlock),
+                           size_t(kBlock + d.gv_max) * sizeof(R), s, d, tile_order(d));
     else if (part == 0)
         hipLaunchKernelGGL(k_cg_product<R>, dim3(pad8(d.cg_pblk)), dim3(kBlock), 0, s, d);
     else if (part == 1)
