@@ -339,9 +339,18 @@ CgPlan cg_plan(const Mesh& m) {
     const size_t nm = m.mesh_start.size() - 1;
     int64_t most = 0;
     for (size_t k = 0; k < nm; ++k) most = std::max(most, m.mesh_start[k + 1] - m.mesh_start[k]);
-    const int64_t share = (most + kCgMaxBlocks - 1) / kCgMaxBlocks;
+    // A block's rows: about kCgMaxBlocks blocks for the whole state, at least
+    // 256 for its largest mesh (the last to finish) and no more than
+    // kCgMaxBlocks for any mesh, whose partials every block of the next kernel
+    // adds.  256 threads and more rows each: 384k cells in threads of one row
+    // 20.7 ms, of two 19.6; 1.3M refined 49.4 and 47.6; eight meshes of 0.5M
+    // cells 31.3 and 29.8, forty of 2.9M 106.6 and 99.8.  Above eight rows 512
+    // threads: 4.4M 355 ms, with 256 360.  Of 512 blocks and 1,024 neither is
+    // better; 2,048: 384k 21.0, 1.3M refined 52.4.
+    const int64_t share = std::max((most + kCgMaxBlocks - 1) / kCgMaxBlocks,
+                                   std::min((m.nc + kCgMaxBlocks - 1) / kCgMaxBlocks, (most + 255) / 256));
     if (share > 256) {                     // rows a thread, then threads in whole wavefronts
-        const int64_t per = (share + 511) / 512;
+        const int64_t widest = share > 2048 ? 512 : 256, per = (share + widest - 1) / widest;
         c.threads = int32_t(((share + per - 1) / per + 63) / 64 * 64);
         c.rows = int32_t(c.threads * per);
     }
