@@ -43,7 +43,7 @@ METRIC = "FV cell-updates/s + Poisson solve ms @1e-10 rel; plain vs mixed/learne
 # hashes to the recorded prefix, else null.
 MEASURED_TRAFFIC = {"cube120": {}}
 # timing id -> the FP64 kernel it times (the product on a mesh of this size)
-KERNEL_NAMES = {"grad_limiter": "k_grad_cells", "node_interp": "k_vertex_moments", "fv_cell": "k_cell_step",
+KERNEL_NAMES = {"grad_limiter": "k_grad_cells", "node_interp": "k_vertex_moments_tiles", "fv_cell": "k_cell_step",
                 "mf_gather": "k_cg_product_tiles", "cg_axpy": "k_cg_residual", "cg_dir": "k_cg_direction"}
 _CG = ("cg_iter.hip", "cg_dev.h", "mf_cell.h", "quad.h", "xcd.h")
 _FV = ("fv_kernels.hip", "quad.h", "xcd.h")
@@ -116,10 +116,10 @@ def algorithmic_bytes(info):
         # vertex; per cell local numbers 16, M^-1 48, the four face values
         # written 32; edge-only neighbours: local index 2 per entry
         "grad_limiter": (nc + nb) * 40 + nv * 96 + nc * 96 + info.edge_nbr_entries * 2,
-        # vertex moments: index 4 per list entry, position 32 and u 8 of cells
-        # and ghosts; per vertex list length 4, mean and slope 64 read, moments
+        # vertex moments by slices (their halos not counted): local index 2 per
+        # list entry, position 32 and u 8 of cells and ghosts; per vertex list length 4, mean and slope 64 read, moments
         # 32 and value 8 written
-        "node_interp": info.node_entries * 4 + (nc + nb) * 40 + nv * 108,
+        "node_interp": info.node_entries * 2 + (nc + nb) * 40 + nv * 108,
         # the FP64 stage in one pass per cell: per cell outward phi 32,
         # neighbours 16, face slots 1, local vertices 8, three vertex weights
         # and the volume 32, kRL weights 32, its four face values 32 (the

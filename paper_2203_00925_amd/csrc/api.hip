@@ -74,6 +74,10 @@ size_t layout(const Mesh& m, char* base, Dev& d) {
     d.g_self = carve<int32_t>(base, off, m.g_self.size());
     d.gv_off = carve<int64_t>(base, off, m.gv_off.size());
     d.gv_idx = carve<int32_t>(base, off, m.gv_idx.size());
+    d.nh_max = m.nh_max;
+    d.nh_off = carve<int64_t>(base, off, m.nh_off.size());
+    d.nh_idx = carve<int32_t>(base, off, m.nh_idx.size());
+    d.nl_idx = carve<uint16_t>(base, off, m.nl_idx.size());
     d.g_cell = carve<uint4>(base, off, nc);
     d.ge_off = carve<int64_t>(base, off, m.ge_off.size());
     d.ge_idx = carve<uint4>(base, off, m.ge_idx.size() / 8 + 1);
@@ -413,6 +417,7 @@ int mifvm_state_create(const mifvm_mesh* mesh, const mifvm_params* params, void*
     UP(d.n_off, m.node.off); UP(d.n_w, m.node.width); UP(d.n_idx, m.node.idx); UP(d.n_alpha, m.node.val);
     UP(d.n_len, m.n_len);
     UP(d.g_off, m.g_off); UP(d.g_idx, m.g_idx); UP(d.g_self, m.g_self);
+    UP(d.nh_off, m.nh_off); UP(d.nh_idx, m.nh_idx); UP(d.nl_idx, m.nl_idx);
     UP(d.gv_off, m.gv_off); UP(d.gv_idx, m.gv_idx); UP(d.ge_off, m.ge_off);
     UPB(d.g_cell, m.g_cell); UPB(d.ge_idx, m.ge_idx);
     UPB(d.vpos, m.vpos); UPB(d.vmean, m.vmean); UPB(d.vslope, m.vslope);

@@ -147,6 +147,101 @@ __global__ __launch_bounds__(kBlock) void k_vertex_moments(Dev d, FvArrays<R> a,
     a.unode[v] = ub + (R(sb.x) * cx + R(sb.y) * cy + R(sb.z) * cz);
 }
 
+// The same per slice of 64 vertices, one block each, with the entities their
+// lists name staged in LDS: the direct gathers are bound by line accesses (24
+// positions and values a vertex, two loads and one each), and a slice's
+// entities, sorted, are half as many and mostly neighbours in memory.  The same
+// sums in the same order.
+template <class R>
+__global__ __launch_bounds__(kBlock) void k_vertex_moments_tiles(Dev d, FvArrays<R> a, BlockOrder order) {
+    constexpr int L = 4, B = 6, H = 4;
+    extern __shared__ __align__(16) unsigned char sm_raw[];
+    double2* const hxy = reinterpret_cast<double2*>(sm_raw);
+    double* const hz = reinterpret_cast<double*>(hxy + d.nh_max);
+    R* const hv = reinterpret_cast<R*>(hz + d.nh_max);
+    const int64_t sl = order.block();
+    if (sl * 64 >= d.nv) return;
+    const int T = kBlock;
+    const int64_t h0 = d.nh_off[sl];
+    const int hn = int(d.nh_off[sl + 1] - h0);
+    const int64_t v = sl * 64 + threadIdx.x / L;
+    const int q = threadIdx.x & (L - 1);
+    const int64_t vc = v < d.nv ? v : d.nv - 1;
+    const int64_t base = d.n_off[sl] + (vc & 63);
+    int he[H];
+#pragma unroll
+    for (int j = 0; j < H; ++j) {
+        const int h = j * T + threadIdx.x;
+        he[j] = d.nh_idx[h0 + (h < hn ? h : 0)];
+    }
+    const int n = d.n_len[vc];
+    const double4* __restrict__ P = d.xyz4;
+    const R* __restrict__ u = a.u;
+    double4 hp[H];
+    R hu[H];
+#pragma unroll
+    for (int j = 0; j < H; ++j) {
+        hp[j] = P[he[j]];
+        hu[j] = u[he[j]];
+    }
+    const double4 xb = d.vmean[vc], sb = d.vslope[vc];
+    int l[B];
+#pragma unroll
+    for (int j = 0; j < B; ++j) {
+        const int k = j * L + q;
+        l[j] = d.nl_idx[base + int64_t(k < n ? k : 0) * 64];
+    }
+#pragma unroll
+    for (int j = 0; j < H; ++j) {
+        const int h = j * T + threadIdx.x;
+        if (h < hn) {
+            hxy[h] = make_double2(hp[j].x, hp[j].y);
+            hz[h] = hp[j].z;
+            hv[h] = hu[j];
+        }
+    }
+    for (int h = H * T + threadIdx.x; h < hn; h += T) {
+        const int e = d.nh_idx[h0 + h];
+        const double4 p = P[e];
+        hxy[h] = make_double2(p.x, p.y);
+        hz[h] = p.z;
+        hv[h] = u[e];
+    }
+    __syncthreads();
+    R cx = R(0), cy = R(0), cz = R(0), su = R(0), u0 = R(0);
+    for (int k0 = 0; k0 < n; k0 += B * L) {               // uniform over the 4 lanes
+        if (k0 > 0) {
+#pragma unroll
+            for (int j = 0; j < B; ++j) {
+                const int k = k0 + j * L + q;
+                l[j] = d.nl_idx[base + int64_t(k < n ? k : 0) * 64];
+            }
+        }
+        if (k0 == 0) u0 = __shfl(hv[l[0]], int(threadIdx.x & 63 & ~(L - 1)), 64);
+#pragma unroll
+        for (int j = 0; j < B; ++j) {
+            const bool in = k0 + j * L + q < n;
+            const double2 p = hxy[l[j]];
+            const R du = in ? hv[l[j]] - u0 : R(0);
+            cx += R(p.x - xb.x) * du;
+            cy += R(p.y - xb.y) * du;
+            cz += R(hz[l[j]] - xb.z) * du;
+            su += du;
+        }
+    }
+#pragma unroll
+    for (int o = 1; o < L; o <<= 1) {
+        cx += __shfl_xor(cx, o, 64);
+        cy += __shfl_xor(cy, o, 64);
+        cz += __shfl_xor(cz, o, 64);
+        su += __shfl_xor(su, o, 64);
+    }
+    if (q != 0 || v >= d.nv) return;
+    const R ub = u0 + su / R(n);
+    a.vmom[v] = mk4(cx, cy, cz, ub);
+    a.unode[v] = ub + (R(sb.x) * cx + R(sb.y) * cy + R(sb.z) * cz);
+}
+
 // One block per tile of d.g_rows cells.  The tile's halo (its cells and the
 // entities sharing an edge or a face with one, 2.9 per cell) is staged in LDS
 // as two arrays of 16-byte items, (x, y) and (z, u), and the records of the
@@ -776,6 +871,17 @@ FvArrays<R> with_u(FvArrays<R> a, const void* u_in) {
 hipError_t launch_vertex_moments(const Dev& d, bool fp32, hipStream_t s, const void* u_in) {
     const BlockOrder o = stream_order(d.nv * 4, kBlock);
     const dim3 g(o.grid), b(kBlock);
+    // By slices from 512 of them (two a CU); on fewer the barrier costs more
+    // than the gathers save.  27k vertices, six steps: 455 us by slices, 449
+    // direct; 55k, four steps: 452 and 457; 531k, two steps: 1,802 and 1,921 (FP32
+    // 1,351 and 1,444).  Lists that name more than 64 KB of entities a slice
+    // stay with the direct form.
+    const size_t lds = size_t(d.nh_max) * (24 + (fp32 ? 4 : 8));
+    if (d.nh_max > 0 && lds <= 65536 && d.nv >= 64 * 512) {
+        if (fp32) hipLaunchKernelGGL(k_vertex_moments_tiles<float>, g, b, lds, s, d, with_u(fv32(d), u_in), o);
+        else hipLaunchKernelGGL(k_vertex_moments_tiles<double>, g, b, lds, s, d, with_u(fv64(d), u_in), o);
+        return hipGetLastError();
+    }
     if (fp32) hipLaunchKernelGGL(k_vertex_moments<float>, g, b, 0, s, d, with_u(fv32(d), u_in), o);
     else hipLaunchKernelGGL(k_vertex_moments<double>, g, b, 0, s, d, with_u(fv64(d), u_in), o);
     return hipGetLastError();

@@ -791,6 +791,42 @@ int preprocess(const double* xyz, int64_t nv, const int32_t* tets, int64_t nc,
         }
     }
     mark("gradient tiles");
+    // -- 16. halos of the vertex lists' slices ---------------------------------------
+    {
+        const int64_t ns = (nv + 63) / 64;
+        M.nh_off.assign(ns + 1, 0);
+        M.nh_idx.clear();
+        M.nh_idx.reserve(size_t(nc) * 5 / 2);
+        M.nl_idx.assign(M.node.idx.size(), 0);
+        M.nh_max = 0;
+        std::fill(seen.begin(), seen.end(), -1);
+        std::vector<int32_t> buf;
+        for (int64_t s = 0; s < ns; ++s) {
+            const int64_t v0 = s * 64, v1 = std::min(nv, v0 + 64);
+            buf.clear();
+            for (int64_t e = M.nptr[v0]; e < M.nptr[v1]; ++e)
+                if (seen[M.nidx[e]] != s) {
+                    seen[M.nidx[e]] = s;
+                    buf.push_back(M.nidx[e]);
+                }
+            std::sort(buf.begin(), buf.end());
+            for (size_t h = 0; h < buf.size(); ++h) g2l[buf[h]] = int32_t(h);
+            for (int64_t v = v0; v < v1; ++v)
+                for (int64_t k = 0; k < M.nptr[v + 1] - M.nptr[v]; ++k)
+                    M.nl_idx[M.node.off[s] + k * 64 + (v & 63)] = (uint16_t)g2l[M.nidx[M.nptr[v] + k]];
+            M.nh_idx.insert(M.nh_idx.end(), buf.begin(), buf.end());
+            M.nh_off[s + 1] = (int64_t)M.nh_idx.size();
+            M.nh_max = std::max<int32_t>(M.nh_max, (int32_t)buf.size());
+            for (int32_t e : buf) g2l[e] = -1;
+        }
+        if (M.nh_max > 65536) {
+            M.nh_max = 0;
+            M.nh_off.clear();
+            M.nh_idx.clear();
+            M.nl_idx.clear();
+        }
+    }
+    mark("vertex slices");
     // every local index must name the same entity as the global one
     bool ok = true;
     for (int64_t r = 0; ok && r < nc; ++r) {
@@ -810,6 +846,11 @@ int preprocess(const double* xyz, int64_t nv, const int32_t* tets, int64_t nc,
             ok = int64_t(M.ge_idx[at]) < gn && M.g_idx[g0 + M.ge_idx[at]] == M.eidx[M.eptr[r] + k];
         }
     }
+    for (int64_t v = 0; ok && M.nh_max > 0 && v < nv; ++v)
+        for (int64_t k = 0; ok && k < M.n_len[v]; ++k) {
+            const int64_t at = M.node.off[v >> 6] + k * 64 + (v & 63), h0 = M.nh_off[v >> 6];
+            ok = h0 + M.nl_idx[at] < M.nh_off[(v >> 6) + 1] && M.nh_idx[h0 + M.nl_idx[at]] == M.node.idx[at];
+        }
     if (!ok) { err = "internal error: tile-local index mismatch"; return E_MESH; }
     mark("verification");
     return 0;

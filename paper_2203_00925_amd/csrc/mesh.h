@@ -86,6 +86,13 @@ struct Mesh {
     int32_t g_rows = 256, g_max = 0, gv_max = 0;
     std::vector<int64_t> g_off, gv_off;
     std::vector<int32_t> g_idx, g_self, gv_idx;
+    // halos of the 64-row slices of the vertex lists: the entities they name
+    // (sorted), and each list entry's place among them (node's slots; empty,
+    // nh_max 0, where a slice names more than 65,536)
+    int32_t nh_max = 0;
+    std::vector<int64_t> nh_off;
+    std::vector<int32_t> nh_idx;
+    std::vector<uint16_t> nl_idx;
     std::vector<uint16_t> g_cell;
     std::vector<int64_t> ge_off;
     std::vector<uint16_t> ge_idx;

@@ -73,6 +73,10 @@ struct Dev {
     int64_t g_tiles;
     int64_t *g_off, *gv_off, *ge_off;
     int32_t *g_idx, *g_self, *gv_idx;
+    int32_t nh_max;                       // halos of the vertex lists' slices (0: none)
+    int64_t* nh_off;
+    int32_t* nh_idx;
+    uint16_t* nl_idx;
     uint4 *g_cell, *ge_idx;
     double4 *vpos, *vmean, *vslope, *vmom;
     float4* vmom32;
