@@ -455,8 +455,6 @@ __global__ __launch_bounds__(512) void k_amg_direction(Dev d, int nvert) {
     }
 }
 
-unsigned pad8(int64_t n) { return unsigned((n + kXcds - 1) / kXcds * kXcds); }
-
 // Where a level's result goes: the rows of the finer level that make up each
 // of its rows.
 struct Fine {

@@ -330,8 +330,6 @@ __global__ __launch_bounds__(512) void k_cg_open_vertices(Dev d) {
     if (q == 0 && v < d.nv) reinterpret_cast<R*>(d.mf_xv)[v] = s;
 }
 
-unsigned pad8(int64_t n) { return unsigned((n + kXcds - 1) / kXcds * kXcds); }
-
 }  // namespace
 
 CgPlan cg_plan(const Mesh& m) {

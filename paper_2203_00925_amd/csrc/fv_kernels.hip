@@ -96,9 +96,37 @@ __global__ __launch_bounds__(kBlock) void k_ghost_fill(int64_t nc, int64_t nb,
 // (C, ub) and u_v of one vertex, summed by 4 neighbouring lanes: lane q takes
 // the entries q, q + 4, ..., six loads of each kind in flight.  Values are
 // taken relative to the list's first entry's.
+constexpr int kMomentLanes = 4, kMomentBatch = 6;
+
+template <class R>
+struct ListSums {                         // one lane's part
+    R cx = R(0), cy = R(0), cz = R(0), su = R(0);
+
+    __device__ void add(double x, double y, double z, R du, const double4& xb) {
+        cx += R(x - xb.x) * du;
+        cy += R(y - xb.y) * du;
+        cz += R(z - xb.z) * du;
+        su += du;
+    }
+    // the lanes' parts together; lane 0 of an existing vertex writes
+    __device__ void finish(const FvArrays<R>& a, int64_t v, bool write, int n, R u0, const double4& sb) {
+#pragma unroll
+        for (int o = 1; o < kMomentLanes; o <<= 1) {
+            cx += __shfl_xor(cx, o, 64);
+            cy += __shfl_xor(cy, o, 64);
+            cz += __shfl_xor(cz, o, 64);
+            su += __shfl_xor(su, o, 64);
+        }
+        if (!write) return;
+        const R ub = u0 + su / R(n);
+        a.vmom[v] = mk4(cx, cy, cz, ub);
+        a.unode[v] = ub + (R(sb.x) * cx + R(sb.y) * cy + R(sb.z) * cz);
+    }
+};
+
 template <class R>
 __global__ __launch_bounds__(kBlock) void k_vertex_moments(Dev d, FvArrays<R> a, BlockOrder order) {
-    constexpr int L = 4, B = 6;
+    constexpr int L = kMomentLanes, B = kMomentBatch;
     const int64_t v = order.block() * (kBlock / L) + threadIdx.x / L;
     const int q = threadIdx.x & (L - 1);
     const int64_t vc = v < d.nv ? v : d.nv - 1;
@@ -108,7 +136,8 @@ __global__ __launch_bounds__(kBlock) void k_vertex_moments(Dev d, FvArrays<R> a,
     const double4 xb = d.vmean[vc], sb = d.vslope[vc];
     const double4* __restrict__ P = d.xyz4;
     const R* __restrict__ u = a.u;
-    R cx = R(0), cy = R(0), cz = R(0), su = R(0), u0 = R(0);
+    ListSums<R> sums;
+    R u0 = R(0);
     for (int k0 = 0; k0 < n; k0 += B * L) {               // uniform over the 4 lanes
         int e[B];
 #pragma unroll
@@ -127,24 +156,10 @@ __global__ __launch_bounds__(kBlock) void k_vertex_moments(Dev d, FvArrays<R> a,
 #pragma unroll
         for (int j = 0; j < B; ++j) {
             const bool in = k0 + j * L + q < n;
-            const R du = in ? ue[j] - u0 : R(0);
-            cx += R(pe[j].x - xb.x) * du;
-            cy += R(pe[j].y - xb.y) * du;
-            cz += R(pe[j].z - xb.z) * du;
-            su += du;
+            sums.add(pe[j].x, pe[j].y, pe[j].z, in ? ue[j] - u0 : R(0), xb);
         }
     }
-#pragma unroll
-    for (int o = 1; o < L; o <<= 1) {
-        cx += __shfl_xor(cx, o, 64);
-        cy += __shfl_xor(cy, o, 64);
-        cz += __shfl_xor(cz, o, 64);
-        su += __shfl_xor(su, o, 64);
-    }
-    if (q != 0 || v >= d.nv) return;
-    const R ub = u0 + su / R(n);
-    a.vmom[v] = mk4(cx, cy, cz, ub);
-    a.unode[v] = ub + (R(sb.x) * cx + R(sb.y) * cy + R(sb.z) * cz);
+    sums.finish(a, v, q == 0 && v < d.nv, n, u0, sb);
 }
 
 // The same per slice of 64 vertices, one block each, with the entities their
@@ -154,7 +169,7 @@ __global__ __launch_bounds__(kBlock) void k_vertex_moments(Dev d, FvArrays<R> a,
 // sums in the same order.
 template <class R>
 __global__ __launch_bounds__(kBlock) void k_vertex_moments_tiles(Dev d, FvArrays<R> a, BlockOrder order) {
-    constexpr int L = 4, B = 6, H = 4;
+    constexpr int L = kMomentLanes, B = kMomentBatch, H = 4;
     extern __shared__ __align__(16) unsigned char sm_raw[];
     double2* const hxy = reinterpret_cast<double2*>(sm_raw);
     double* const hz = reinterpret_cast<double*>(hxy + d.nh_max);
@@ -208,7 +223,8 @@ __global__ __launch_bounds__(kBlock) void k_vertex_moments_tiles(Dev d, FvArrays
         hv[h] = u[e];
     }
     __syncthreads();
-    R cx = R(0), cy = R(0), cz = R(0), su = R(0), u0 = R(0);
+    ListSums<R> sums;
+    R u0 = R(0);
     for (int k0 = 0; k0 < n; k0 += B * L) {               // uniform over the 4 lanes
         if (k0 > 0) {
 #pragma unroll
@@ -222,24 +238,10 @@ __global__ __launch_bounds__(kBlock) void k_vertex_moments_tiles(Dev d, FvArrays
         for (int j = 0; j < B; ++j) {
             const bool in = k0 + j * L + q < n;
             const double2 p = hxy[l[j]];
-            const R du = in ? hv[l[j]] - u0 : R(0);
-            cx += R(p.x - xb.x) * du;
-            cy += R(p.y - xb.y) * du;
-            cz += R(hz[l[j]] - xb.z) * du;
-            su += du;
+            sums.add(p.x, p.y, hz[l[j]], in ? hv[l[j]] - u0 : R(0), xb);
         }
     }
-#pragma unroll
-    for (int o = 1; o < L; o <<= 1) {
-        cx += __shfl_xor(cx, o, 64);
-        cy += __shfl_xor(cy, o, 64);
-        cz += __shfl_xor(cz, o, 64);
-        su += __shfl_xor(su, o, 64);
-    }
-    if (q != 0 || v >= d.nv) return;
-    const R ub = u0 + su / R(n);
-    a.vmom[v] = mk4(cx, cy, cz, ub);
-    a.unode[v] = ub + (R(sb.x) * cx + R(sb.y) * cy + R(sb.z) * cz);
+    sums.finish(a, v, q == 0 && v < d.nv, n, u0, sb);
 }
 
 // One block per tile of d.g_rows cells.  The tile's halo (its cells and the

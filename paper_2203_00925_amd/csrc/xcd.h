@@ -18,11 +18,9 @@ __device__ inline int64_t xcd_block() {
     return int64_t(blockIdx.x % kXcds) * per + blockIdx.x / kXcds;
 }
 __device__ inline int64_t gtid_m() { return xcd_block() * blockDim.x + threadIdx.x; }
-// grid of blocks of `block` threads covering n rows, padded to a multiple of 8
-inline unsigned rows_m(int64_t n, int block) {
-    const int64_t b = (n + block - 1) / block;
-    return unsigned((b + kXcds - 1) / kXcds * kXcds);
-}
+// a grid of n blocks padded to a multiple of 8; one of blocks of `block` threads covering n rows
+inline unsigned pad8(int64_t n) { return unsigned((n + kXcds - 1) / kXcds * kXcds); }
+inline unsigned rows_m(int64_t n, int block) { return pad8((n + block - 1) / block); }
 
 // The same for a step's kernels, which read some dozen arrays once: above
 // 4,096 blocks (1M cells; below, the arrays stay in the caches from one kernel
@@ -46,7 +44,7 @@ inline BlockOrder stream_order(int64_t rows, int rows_per_block) {
     const int64_t n = (rows + rows_per_block - 1) / rows_per_block;
     constexpr unsigned W = 32;
     if (n > 4096) return {unsigned((n + kXcds * W - 1) / (kXcds * W) * (kXcds * W)), 5u, W};
-    const unsigned g = unsigned((n + kXcds - 1) / kXcds * kXcds);
+    const unsigned g = pad8(n);
     return {g, 28u, g / kXcds};
 }
 
