@@ -24,7 +24,7 @@ HIP_SOURCES = ["api.hip", "nn_api.hip", "fv_kernels.hip", "solve_kernels.hip", "
                "batch_api.hip"]
 CXX_SOURCES = ["mesh.cpp", "amg.cpp"]
 HEADERS = ["mesh.h", "state.h", "reduce.h", "seg.h", "cg_scalars.h", "api_util.h", "nn.h", "gmres.h",
-           "amg.h", "amg_dev.h", "batch.h", "cg_dev.h", "cg_iter.h", "fcg_monitor.h", "halo_stage.h",
+           "amg.h", "amg_dev.h", "batch.h", "cg_dev.h", "chunks.h", "cg_iter.h", "fcg_monitor.h", "halo_stage.h",
            "mf_cell.h", "quad.h", "xcd.h"]
 
 

@@ -83,6 +83,7 @@ size_t layout(const Mesh& m, char* base, Dev& d) {
     d.ge_idx = carve<uint4>(base, off, m.ge_idx.size() / 8 + 1);
     d.vpos = carve<double4>(base, off, nv);
     d.vmean = carve<double4>(base, off, nv);
+    d.voff = carve<double4>(base, off, nv);
     d.vslope = carve<double4>(base, off, nv);
     d.vmom = carve<double4>(base, off, nv);
     d.vmom32 = carve<float4>(base, off, nv);
@@ -420,7 +421,7 @@ int mifvm_state_create(const mifvm_mesh* mesh, const mifvm_params* params, void*
     UP(d.nh_off, m.nh_off); UP(d.nh_idx, m.nh_idx); UP(d.nl_idx, m.nl_idx);
     UP(d.gv_off, m.gv_off); UP(d.gv_idx, m.gv_idx); UP(d.ge_off, m.ge_off);
     UPB(d.g_cell, m.g_cell); UPB(d.ge_idx, m.ge_idx);
-    UPB(d.vpos, m.vpos); UPB(d.vmean, m.vmean); UPB(d.vslope, m.vslope);
+    UPB(d.vpos, m.vpos); UPB(d.vmean, m.vmean); UPB(d.voff, m.voff); UPB(d.vslope, m.vslope);
     UP(d.k_off, m.kmat.off); UP(d.k_w, m.kmat.width); UP(d.k_col, m.kmat.idx); UP(d.k_len, m.klen);
     UP(d.cell_perm, m.cell_perm); UP(d.vert_perm, m.vert_perm);
     UP(d.h_off, m.h_off); UP(d.h_idx, m.h_idx); UP(d.h_self, m.h_self);

@@ -108,19 +108,25 @@ struct ListSums {                         // one lane's part
         cz += R(z - xb.z) * du;
         su += du;
     }
-    // the lanes' parts together; lane 0 of an existing vertex writes
-    __device__ void finish(const FvArrays<R>& a, int64_t v, bool write, int n, R u0, const double4& sb) {
+    // The lanes' parts together; lane 0 of an existing vertex writes.  The
+    // differences to the rounded xb add up to l, not to zero: C - l (ub - u0)
+    // is the centred moment.
+    __device__ void finish(const FvArrays<R>& a, int64_t v, bool write, R n, R u0, const double4& xb,
+                           const double4& sb) {
 #pragma unroll
         for (int o = 1; o < kMomentLanes; o <<= 1) {
+            su += __shfl_xor(su, o, 64);
             cx += __shfl_xor(cx, o, 64);
             cy += __shfl_xor(cy, o, 64);
             cz += __shfl_xor(cz, o, 64);
-            su += __shfl_xor(su, o, 64);
         }
         if (!write) return;
-        const R ub = u0 + su / R(n);
-        a.vmom[v] = mk4(cx, cy, cz, ub);
-        a.unode[v] = ub + (R(sb.x) * cx + R(sb.y) * cy + R(sb.z) * cz);
+        const R lx = R(__int_as_float(__double2loint(xb.w))), ly = R(__int_as_float(__double2hiint(xb.w)));
+        const R lz = R(sb.w);
+        const R bl = R(sb.x) * lx + R(sb.y) * ly + R(sb.z) * lz, bc = R(sb.x) * cx + R(sb.y) * cy + R(sb.z) * cz;
+        const R mean = su / n, ub = u0 + mean;
+        a.unode[v] = ub + (bc - bl * mean);
+        a.vmom[v] = mk4(cx - lx * mean, cy - ly * mean, cz - lz * mean, ub);
     }
 };
 
@@ -159,7 +165,7 @@ __global__ __launch_bounds__(kBlock) void k_vertex_moments(Dev d, FvArrays<R> a,
             sums.add(pe[j].x, pe[j].y, pe[j].z, in ? ue[j] - u0 : R(0), xb);
         }
     }
-    sums.finish(a, v, q == 0 && v < d.nv, n, u0, sb);
+    sums.finish(a, v, q == 0 && v < d.nv, R(n), u0, xb, sb);
 }
 
 // The same per slice of 64 vertices, one block each, with the entities their
@@ -241,7 +247,7 @@ __global__ __launch_bounds__(kBlock) void k_vertex_moments_tiles(Dev d, FvArrays
             sums.add(p.x, p.y, hz[l[j]], in ? hv[l[j]] - u0 : R(0), xb);
         }
     }
-    sums.finish(a, v, q == 0 && v < d.nv, n, u0, sb);
+    sums.finish(a, v, q == 0 && v < d.nv, R(n), u0, xb, sb);
 }
 
 // One block per tile of d.g_rows cells.  The tile's halo (its cells and the
@@ -265,7 +271,7 @@ __global__ __launch_bounds__(kBlock, 4) void k_grad_cells(Dev d, FvArrays<R> a, 
     const int hc = d.g_max, vcap = d.gv_max;
     V2* const xy = reinterpret_cast<V2*>(sm_raw);         // halo
     V2* const zu = xy + hc;
-    V2* const va = zu + hc;                               // vertices: (xb_x, xb_y), (xb_z, n),
+    V2* const va = zu + hc;                               // vertices: xb - x_v (x, y), (z, n),
     V2* const vb = va + vcap;
     V2* const vc = vb + vcap;                             // (C_x, C_y), (C_z, ub),
     V2* const vd = vc + vcap;
@@ -307,16 +313,16 @@ __global__ __launch_bounds__(kBlock, 4) void k_grad_cells(Dev d, FvArrays<R> a, 
         hp[j] = P[he[j]];
         hu[j] = u[he[j]];
     }
-    auto put_vertex = [&](int w, const double4& xb, const double4& xv, const V4& mo) {
-        va[w] = mk2(R(xb.x - ref.x), R(xb.y - ref.y));
-        vb[w] = mk2(R(xb.z - ref.z), R(xb.w));
+    auto put_vertex = [&](int w, const double4& off, const double4& xv, const V4& mo) {
+        va[w] = mk2(R(off.x), R(off.y));
+        vb[w] = mk2(R(off.z), R(off.w));
         vc[w] = mk2(mo.x, mo.y);
         vd[w] = mk2(mo.z, mo.w);
         ve[w] = mk2(R(xv.x - ref.x), R(xv.y - ref.y));
         vf[w] = R(xv.z - ref.z);
     };
     {
-        const double4 xb = d.vmean[wv], xv = d.vpos[wv];
+        const double4 off = d.voff[wv], xv = d.vpos[wv];
         const V4 mo = a.vmom[wv];
 #pragma unroll
         for (int j = 0; j < HB; ++j) {
@@ -326,7 +332,7 @@ __global__ __launch_bounds__(kBlock, 4) void k_grad_cells(Dev d, FvArrays<R> a, 
                 zu[h] = mk2(R(hp[j].z - ref.z), hu[j]);
             }
         }
-        if (int(threadIdx.x) < wn) put_vertex(threadIdx.x, xb, xv, mo);
+        if (int(threadIdx.x) < wn) put_vertex(threadIdx.x, off, xv, mo);
     }
     const R* __restrict__ m = a.minv;
     const R m0 = m[ic], m1 = m[nc + ic], m2 = m[2 * nc + ic];
@@ -339,7 +345,7 @@ __global__ __launch_bounds__(kBlock, 4) void k_grad_cells(Dev d, FvArrays<R> a, 
     }
     for (int w = T + threadIdx.x; w < wn; w += T) {
         wv = d.gv_idx[w0 + w];
-        put_vertex(w, d.vmean[wv], d.vpos[wv], a.vmom[wv]);
+        put_vertex(w, d.voff[wv], d.vpos[wv], a.vmom[wv]);
     }
     __syncthreads();
     if (!cell) return;
@@ -354,12 +360,12 @@ __global__ __launch_bounds__(kBlock, 4) void k_grad_cells(Dev d, FvArrays<R> a, 
         const int l = int(vl[k >> 1] >> (16 * (k & 1))) & 0xffff;
         const V2 A = va[l], Bv = vb[l], C = vc[l], Dv = vd[l], E = ve[l];
         const R nd = Bv.y * (Dv.y - ui);
-        jx += C.x + (A.x - xi) * nd;
-        jy += C.y + (A.y - yi) * nd;
-        jz += Dv.x + (Bv.x - zi) * nd;
         ox[k] = xi - E.x;
         oy[k] = yi - E.y;
         oz[k] = zi - vf[l];
+        jx += C.x + (A.x - ox[k]) * nd;                   // xb - x_i
+        jy += C.y + (A.y - oy[k]) * nd;
+        jz += Dv.x + (Bv.x - oz[k]) * nd;
     }
     R umax = ui, umin = ui;
 #pragma unroll

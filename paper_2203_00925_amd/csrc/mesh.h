@@ -71,11 +71,13 @@ struct Mesh {
     // edge (m = 2, listed here) and the 4 face neighbours (m = 3, c2n).
     std::vector<int64_t> eptr; std::vector<int32_t> eidx;   // edge-only neighbours, CSR
     int32_t enbr_max = 0;
-    // per vertex (4 doubles each): its position, its list's mean position and
-    // length, and the slope b of its least-squares weights
-    // alpha_e = 1/n + b . (x_e - mean)
+    // per vertex (4 doubles each): its position; its list's mean position,
+    // rounded; the mean less the position, and the list's length; the slope b of
+    // its least-squares weights alpha_e = 1/n + b . (x_e - mean).
+    // The sum of x_e - (rounded mean) over the list: x and y as two floats in
+    // the mean's fourth place, z in the slope's.
     std::vector<int32_t> n_len;       // nv: vertex list lengths
-    std::vector<double> vpos, vmean, vslope;
+    std::vector<double> vpos, vmean, voff, vslope;
     // Gradient tiles of g_rows consecutive cells: the halo (sorted; the cells
     // and the entities sharing an edge or a face with one), the vertices the
     // cells touch (sorted), and the local indices a cell reads: g_cell[8 i]

@@ -78,7 +78,7 @@ struct Dev {
     int32_t* nh_idx;
     uint16_t* nl_idx;
     uint4 *g_cell, *ge_idx;
-    double4 *vpos, *vmean, *vslope, *vmom;
+    double4 *vpos, *vmean, *voff, *vslope, *vmom;
     float4* vmom32;
     // renumbering
     int32_t *cell_perm, *vert_perm;       // internal -> user
