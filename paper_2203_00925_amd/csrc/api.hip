@@ -800,26 +800,20 @@ int mifvm_residual(mifvm_state* st, double* d_res, double* d_grad, double* d_psi
     hipStream_t hs = S(stream);
     int rc = residual_parts(s, hs);
     if (rc) return rc;
-    if (d_res) {
-        HIPCHK(launch_residual_out(d, s.fp32, d.tmp, hs));
-        HIPCHK(launch_to_user(d.cell_perm, d.nc, d.nc, d.nc, 1, d.tmp, d_res, hs));
-    }
+    if (d_res || d_grad || d_psi) HIPCHK(launch_residual_out(d, s.fp32, d_res, d_grad, d_psi, hs));
     // FP32 parts are widened into the scratch buffer before being reordered
-    auto out = [&](const double* a64, const float* a32, int64_t n, int comps, const int32_t* perm,
-                   double* dst) -> int {
+    auto out = [&](const double* a64, const float* a32, int64_t n, const int32_t* perm, double* dst) -> int {
         const double* src = a64;
         if (s.fp32) {
-            HIPCHK(launch_cast_to_f64(n * comps, a32, d.tmp, hs));
+            HIPCHK(launch_cast_to_f64(n, a32, d.tmp, hs));
             src = d.tmp;
         }
-        if (perm) HIPCHK(launch_to_user(perm, n, n, n, comps, src, dst, hs));
-        else HIPCHK(hipMemcpyAsync(dst, src, n * comps * sizeof(double), hipMemcpyDeviceToDevice, hs));
+        if (perm) HIPCHK(launch_to_user(perm, n, n, n, 1, src, dst, hs));
+        else HIPCHK(hipMemcpyAsync(dst, src, n * sizeof(double), hipMemcpyDeviceToDevice, hs));
         return MIFVM_OK;
     };
-    if (d_grad && (rc = out(d.grad, d.grad32, d.nc, 3, d.cell_perm, d_grad))) return rc;
-    if (d_psi && (rc = out(d.psi, d.psi32, d.nc, 1, d.cell_perm, d_psi))) return rc;
-    if (d_unode && (rc = out(d.unode, d.unode32, d.nv, 1, d.vert_perm, d_unode))) return rc;
-    if (d_flux && (rc = out(d.flux, d.flux32, d.nf, 1, nullptr, d_flux))) return rc;
+    if (d_unode && (rc = out(d.unode, d.unode32, d.nv, d.vert_perm, d_unode))) return rc;
+    if (d_flux && (rc = out(d.flux, d.flux32, d.nf, nullptr, d_flux))) return rc;
     return MIFVM_OK;
 }
 

@@ -253,7 +253,9 @@ hipError_t launch_fv_cell_setup(const Dev& d, hipStream_t s);
 hipError_t launch_mf_cell_setup(const Dev& d, const BcTable& bc_pot, hipStream_t s);
 // each mesh's time step and the ghosts of u: what a run of steps starts from
 hipError_t launch_step_begin(const Dev& d, bool fp32, const BcTable& bc, double dt, double cfl, hipStream_t s);
-hipError_t launch_residual_out(const Dev& d, bool fp32, double* res_internal, hipStream_t s);
+// in the caller's order: the residual from the face fluxes, the gradient and
+// the limiter (each unless null)
+hipError_t launch_residual_out(const Dev& d, bool fp32, double* res, double* grad, double* psi, hipStream_t s);
 hipError_t launch_face_phi(const Dev& d, hipStream_t s);
 hipError_t launch_make_fp32_geometry(const Dev& d, int64_t node_padded, hipStream_t s);
 hipError_t launch_cast_to_f32(int64_t n, const double* src, float* dst, hipStream_t s);
