@@ -575,7 +575,7 @@ hipError_t launch_amg_open(const Dev& d, const BcTable& bc_pot, const AmgDev& a,
     hipLaunchKernelGGL(k_amg_p0, dim3(unsigned(nb)), dim3(kBlock), 0, s, d);
     hipLaunchKernelGGL(k_amg_rz_fin, dim3(1), dim3(1024), 0, s, d, nb);
     e = hipGetLastError();
-    return e == hipSuccess && matrix_free ? launch_cg_open_vertices(d, false, s) : e;
+    return e == hipSuccess && matrix_free ? launch_cg_open_vertices(d, s) : e;
 }
 
 hipError_t launch_amg_iteration(const Dev& d, const BcTable&, const AmgDev& a, bool matrix_free,

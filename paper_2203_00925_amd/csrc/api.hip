@@ -256,11 +256,6 @@ hipError_t enqueue_cg_chunk(State& s, int method, int n, hipStream_t q) {
     if (e == hipSuccess && three_kernel_cg(s)) e = launch_cg_commit(s.d, q);
     return e;
 }
-
-// what a matrix-free loop needs once it is opened: the vertex values of p
-hipError_t cg_opened(State& s, int method, hipStream_t q) {
-    return s.mf && three_kernel_cg(s) ? launch_cg_open_vertices(s.d, method != MIFVM_SOLVE_PLAIN, q) : hipSuccess;
-}
 }  // namespace
 
 extern "C" {
@@ -1084,6 +1079,7 @@ int solve_impl(mifvm_state* st, const double* d_f, const double* f_internal, con
         }
         return MIFVM_OK;
     };
+    const bool vertices = matrix_free && three_kernel_cg(s);   // the loop reads the vertex values of p
     int restarts = learned.restarts, outer = 0;
     if (method == MIFVM_SOLVE_FGMRES) {
         const GmDev& g = *s.gm;
@@ -1144,8 +1140,7 @@ int solve_impl(mifvm_state* st, const double* d_f, const double* f_internal, con
                 hipError_t e = launch_mf_apply(d, s.bc[1], d.x, d.tmp, hs);
                 if (e != hipSuccess) return e;
             }
-            hipError_t e = launch_cg_setup(d, tol, limit, restart, fresh, hs, matrix_free ? d.tmp : nullptr);
-            return e == hipSuccess ? cg_opened(s, run_method, hs) : e;
+            return launch_cg_setup(d, tol, limit, restart, fresh, vertices, matrix_free ? d.tmp : nullptr, hs);
         };
         HIPCHK(timed(tm, MIFVM_K_CG_SETUP, hs, [&] { return setup(budget, true); }));
         if ((rc = pull())) return rc;
@@ -1172,9 +1167,8 @@ int solve_impl(mifvm_state* st, const double* d_f, const double* f_internal, con
                     hipError_t e = launch_mf_apply(d, s.bc[1], d.x, d.tmp, hs);
                     if (e != hipSuccess) return e;
                 }
-                hipError_t e =
-                    launch_ir_residual(d, tol, tol_in, maxit, restart, fresh, matrix_free ? d.tmp : nullptr, hs);
-                return e == hipSuccess ? cg_opened(s, run_method, hs) : e;
+                return launch_ir_residual(d, tol, tol_in, maxit, restart, fresh, vertices,
+                                          matrix_free ? d.tmp : nullptr, hs);
             }));
             fresh = false;
             if ((rc = pull())) return rc;

@@ -126,4 +126,16 @@ __device__ inline R vertex_sum(const Dev& d, const R* __restrict__ z, int64_t v,
     return quad_sum(s);
 }
 
+// the vertex values of p that block b of a grid writes when a matrix-free loop opens
+template <class R>
+__device__ inline void open_vertices(const Dev& d, int64_t b) {
+    const int64_t v = b * (blockDim.x / kCgVertexLanes) + threadIdx.x / kCgVertexLanes;
+    const int q = threadIdx.x & (kCgVertexLanes - 1);
+    const R s = vertex_sum<R>(d, CgVec<R>::p(d), v < d.nv ? v : d.nv - 1, q);
+    if (q == 0 && v < d.nv) reinterpret_cast<R*>(d.mf_xv)[v] = s;
+}
+inline unsigned vertex_blocks(const Dev& d, int threads) {
+    return unsigned((d.nv * kCgVertexLanes + threads - 1) / threads);
+}
+
 }  // namespace mifvm

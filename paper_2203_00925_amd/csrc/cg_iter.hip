@@ -320,15 +320,8 @@ __global__ __launch_bounds__(512) void k_cg_direction(Dev d, int nvert) {
     }
 }
 
-// vertex values of p when the loop opens (p = z of the true residual)
-template <class R>
-__global__ __launch_bounds__(512) void k_cg_open_vertices(Dev d) {
-    const int64_t v = xcd_block() * (blockDim.x / kCgVertexLanes) + threadIdx.x / kCgVertexLanes;
-    const int q = threadIdx.x & (kCgVertexLanes - 1);
-    const int64_t vc = v < d.nv ? v : d.nv - 1;
-    const R s = vertex_sum<R>(d, CgVec<R>::p(d), vc, q);
-    if (q == 0 && v < d.nv) reinterpret_cast<R*>(d.mf_xv)[v] = s;
-}
+// vertex values of p when the multigrid's loop opens
+__global__ __launch_bounds__(256) void k_cg_open_vertices(Dev d) { open_vertices<double>(d, xcd_block()); }
 
 }  // namespace
 
@@ -454,9 +447,8 @@ hipError_t launch_cg_part(const Dev& d, bool fp32, bool stored, int part, hipStr
     return fp32 ? cg_part<float>(d, stored, part, s) : cg_part<double>(d, stored, part, s);
 }
 
-hipError_t launch_cg_open_vertices(const Dev& d, bool fp32, hipStream_t s) {
-    if (fp32) hipLaunchKernelGGL(k_cg_open_vertices<float>, dim3(rows_m(d.nv * kCgVertexLanes, 256)), dim3(256), 0, s, d);
-    else hipLaunchKernelGGL(k_cg_open_vertices<double>, dim3(rows_m(d.nv * kCgVertexLanes, 256)), dim3(256), 0, s, d);
+hipError_t launch_cg_open_vertices(const Dev& d, hipStream_t s) {
+    hipLaunchKernelGGL(k_cg_open_vertices, dim3(pad8(vertex_blocks(d, 256))), dim3(256), 0, s, d);
     return hipGetLastError();
 }
 

@@ -3,6 +3,7 @@
 // copy and vectors, FP64 accumulation of every dot product), while the true
 // residual r = b - K x and the update x += d stay in FP64.  The FP64 outer
 // residual also serves as the restart of the inner CG.
+#include "cg_dev.h"
 #include "cg_scalars.h"
 #include "reduce.h"
 #include "seg.h"
@@ -67,10 +68,15 @@ __global__ __launch_bounds__(kBlock) void k_ir_residual(Dev d, const double* __r
 // One block per mesh.  fresh: a new solve (sets the outer tolerance, limits
 // and count).  The inner solve runs until ||r32|| <= max(tol_in ||r32_0||,
 // tol ||b|| / 2), the iteration limit, or a restart; the outer loop ends
-// when the FP64 true residual meets tol.
+// when the FP64 true residual meets tol.  Blocks behind those of the meshes:
+// the vertex values of p32 (as in k_cg_setup_fin).
 __global__ __launch_bounds__(1024) void k_ir_residual_fin(Dev d, int64_t nparts, double tol, double tol_in,
                                                           int maxit, int restart, int fresh) {
     __shared__ double lds[16];
+    if (int(blockIdx.x) >= d.nm) {
+        open_vertices<float>(d, int64_t(blockIdx.x) - d.nm);
+        return;
+    }
     const int m = blockIdx.x;
     double t[4];
     seg_sums<4>(d, 0, m, nparts, kBlock, lds, t);
@@ -187,11 +193,11 @@ hipError_t launch_cast_matrix(const Dev& d, int64_t padded, hipStream_t s) {
 }
 
 hipError_t launch_ir_residual(const Dev& d, double tol, double tol_in, int maxit, int restart, bool fresh,
-                              const double* kx, hipStream_t s) {
+                              bool vertices, const double* kx, hipStream_t s) {
     const int nb = rows_grid(d.nc);
     hipLaunchKernelGGL(k_ir_residual, dim3(nb), dim3(kBlock), 0, s, d, kx);
-    hipLaunchKernelGGL(k_ir_residual_fin, dim3(d.nm), dim3(1024), 0, s, d, int64_t(nb), tol, tol_in, maxit,
-                       restart, fresh ? 1 : 0);
+    hipLaunchKernelGGL(k_ir_residual_fin, dim3(d.nm + (vertices ? vertex_blocks(d, 1024) : 0u)), dim3(1024), 0, s, d,
+                       int64_t(nb), tol, tol_in, maxit, restart, fresh ? 1 : 0);
     return hipGetLastError();
 }
 

@@ -4,6 +4,7 @@
 // in device memory (alpha, beta and the convergence test are computed by the
 // last block of the kernel that produces their partial sums; later kernels
 // of an enqueued chunk return at once when the solve has finished).
+#include "cg_dev.h"
 #include "cg_scalars.h"
 #include "reduce.h"
 #include "seg.h"
@@ -254,10 +255,17 @@ __global__ __launch_bounds__(kBlock) void k_cg_setup(Dev d, const double* __rest
 
 // One block per mesh.  fresh != 0: a new solve (sets tolerance, limits,
 // count); otherwise a reopen after a true-residual check or a restart keeps
-// them.
+// them.  Blocks behind those form the vertex values of p, where the iteration
+// wants them (cg_iter.hip): both need only k_cg_setup, and a launch of their own
+// was half of the time of a solve that is converged on entry (3,072 cells 70
+// us, with this 43).
 __global__ __launch_bounds__(1024) void k_cg_setup_fin(Dev d, int64_t nparts, double tol, int maxit,
                                                        int restart, int fresh) {
     __shared__ double lds[16];
+    if (int(blockIdx.x) >= d.nm) {
+        open_vertices<double>(d, int64_t(blockIdx.x) - d.nm);
+        return;
+    }
     const int m = blockIdx.x;
     const double trz = seg_sum(d, 0, m, nparts, kBlock, lds);
     const double trr = seg_sum(d, 1, m, nparts, kBlock, lds);
@@ -381,11 +389,11 @@ hipError_t launch_rhs(const Dev& d, const double* f, hipStream_t s) {
     return hipGetLastError();
 }
 
-hipError_t launch_cg_setup(const Dev& d, double tol, int maxit, int restart, bool fresh, hipStream_t s,
-                           const double* kx) {
+hipError_t launch_cg_setup(const Dev& d, double tol, int maxit, int restart, bool fresh, bool vertices,
+                           const double* kx, hipStream_t s) {
     const int nb = grid_rows(d.nc);
     hipLaunchKernelGGL(k_cg_setup, dim3(nb), dim3(kBlock), 0, s, d, kx);
-    hipLaunchKernelGGL(k_cg_setup_fin, dim3(d.nm), dim3(1024), 0, s, d, int64_t(nb), tol, maxit, restart,
+    hipLaunchKernelGGL(k_cg_setup_fin, dim3(d.nm + (vertices ? vertex_blocks(d, 1024) : 0u)), dim3(1024), 0, s, d, int64_t(nb), tol, maxit, restart,
                        fresh ? 1 : 0);
     return hipGetLastError();
 }

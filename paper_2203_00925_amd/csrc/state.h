@@ -279,9 +279,10 @@ hipError_t launch_assemble(const Dev& d, const BcTable& bc, int row_max, hipStre
 hipError_t launch_assemble_consts(const Dev& d, const BcTable& bc, hipStream_t s);
 hipError_t launch_spmv_plain(const Dev& d, const double* x, double* y, hipStream_t s);
 hipError_t launch_rhs(const Dev& d, const double* f_internal, hipStream_t s);
-// kx: K x computed by the caller (matrix-free), or null for the stored K
-hipError_t launch_cg_setup(const Dev& d, double tol, int maxit, int restart, bool fresh, hipStream_t s,
-                           const double* kx = nullptr);
+// kx: K x computed by the caller (matrix-free), or null for the stored K;
+// vertices: leave the vertex values of p in mf_xv (the three-kernel iteration)
+hipError_t launch_cg_setup(const Dev& d, double tol, int maxit, int restart, bool fresh, bool vertices,
+                           const double* kx, hipStream_t s);
 hipError_t launch_cg_spmv(const Dev& d, hipStream_t s);
 hipError_t launch_cg_axpy(const Dev& d, hipStream_t s);
 hipError_t launch_cg_dir(const Dev& d, hipStream_t s);
@@ -289,12 +290,12 @@ hipError_t launch_cg_dir(const Dev& d, hipStream_t s);
 // launchers (cg_iter.hip): the parts of one CG iteration in order (0 the
 // product, 1 the residual, 2 the direction), FP64 or the FP32 inner form, on
 // the stored matrix (one mesh) or matrix-free; the vertex values of p before
-// the first matrix-free iteration of an opened loop; the scalars after the
-// last iteration of a chunk
+// the first matrix-free iteration of the multigrid's opened loop; the scalars
+// after the last iteration of a chunk
 constexpr int kCgParts = 3;
 hipError_t launch_cg_part(const Dev& d, bool fp32, bool stored, int part, hipStream_t s);
 int cg_product_parts(const Dev& d, bool stored);   // partials the product of a single mesh leaves
-hipError_t launch_cg_open_vertices(const Dev& d, bool fp32, hipStream_t s);
+hipError_t launch_cg_open_vertices(const Dev& d, hipStream_t s);
 hipError_t launch_cg_commit(const Dev& d, hipStream_t s);
 
 // launchers (mf_kernels.hip): y = K x from the discretisation (no stored matrix)
@@ -320,9 +321,9 @@ hipError_t launch_norm_l2(const Dev& d, const double* a, const double* e, hipStr
 
 // launchers (ir_kernels.hip): FP32 inner CG inside FP64 iterative refinement
 hipError_t launch_cast_matrix(const Dev& d, int64_t padded, hipStream_t s);
-// kx: K x computed by the caller (matrix-free), or null for the stored K
+// kx, vertices: as for launch_cg_setup
 hipError_t launch_ir_residual(const Dev& d, double tol, double tol_in, int maxit, int restart, bool fresh,
-                              const double* kx, hipStream_t s);
+                              bool vertices, const double* kx, hipStream_t s);
 hipError_t launch_cg32_spmv(const Dev& d, hipStream_t s);
 hipError_t launch_cg32_axpy(const Dev& d, hipStream_t s);
 hipError_t launch_cg32_dir(const Dev& d, hipStream_t s);
