@@ -713,30 +713,35 @@ hipError_t enqueue_stages(State& s, bool timing, hipStream_t q) {
     return e;
 }
 
-// Whether a step call replays its first step's stages as a graph: when the
-// call before it on this state waited for the stream (a CFL evaluation or a
-// solve before every step), so that nothing hides the host's time for nine launches.  3k
-// cells 107 -> 75 us a CFL evaluation and step, 118k 117 -> 107, 236k 148 ->
-// 148; steps queued one after the other are up to 8% faster launched.  Not
-// while kernels are timed or the caller captures the stream, and not the first
-// time (a capture takes 0.1 ms).
-bool step_replay(State& s, hipStream_t hs) {
-    constexpr int64_t kReplayCells = int64_t(1) << 17;
+// How many of a call's steps replay their stages as a graph.  All of them to
+// 96k cells: nine kernels launched one by one cost the host, or the gaps between
+// them, more than their work (a step and a wait, FP64: 3k cells launched 84.6
+// us, replayed 66.6; 64k 84.4 and 72.5; a hundred steps, 83k 6,190 and 6,066),
+// above, launches are faster (118k, a hundred steps: 7,044 and 7,329).  To 131k
+// cells the first step of a call whose predecessor on this state waited for
+// the stream (a CFL evaluation or a solve before every step), so that nothing
+// hides the host's time (118k 117 -> 107, 236k 148 -> 148).  Not while kernels
+// are timed or the caller captures the stream, nor in a state's first call
+// unless it is long (a capture takes 0.1 ms, a replayed step saves 5 us).
+int steps_replayed(State& s, int n_steps, hipStream_t hs) {
+    constexpr int64_t kReplayCells = 3 << 15, kReplayWaited = 1 << 17;
+    constexpr int kLongCall = 32;
     const bool waited = s.waited;
     s.waited = false;
-    if (!waited || s.timer.on || s.d.nc > kReplayCells || s.step_calls++ == 0) return false;
+    const int n = s.d.nc <= kReplayCells ? n_steps : waited && s.d.nc <= kReplayWaited ? 1 : 0;
+    if (n == 0 || s.timer.on || (s.step_calls++ == 0 && n < kLongCall)) return 0;
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(hs, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) {
         (void)hipGetLastError();
-        return false;
+        return 0;
     }
     if (!s.stage_exec &&
         capture_graph(s, &s.stage_exec, [&](hipStream_t q) { return enqueue_stages(s, false, q); }) != hipSuccess) {
         (void)hipGetLastError();
         s.stage_exec = nullptr;
-        return false;
+        return 0;
     }
-    return true;
+    return n;
 }
 }  // namespace
 
@@ -750,9 +755,9 @@ int mifvm_step(mifvm_state* st, int32_t n_steps, double dt, void* stream) {
     // the ghosts are filled once; every update then sets those of its cells
     HIPCHK(timed(s.timer, MIFVM_K_GHOST_FILL, hs,
                  [&] { return launch_step_begin(s.d, s.fp32, s.bc[0], dt, s.cfl, hs); }));
-    const bool replay = step_replay(s, hs);
+    const int replayed = steps_replayed(s, n_steps, hs);
     for (int n = 0; n < n_steps; ++n) {
-        if (n == 0 && replay) HIPCHK(hipGraphLaunch(s.stage_exec, hs));
+        if (n < replayed) HIPCHK(hipGraphLaunch(s.stage_exec, hs));
         else HIPCHK(enqueue_stages(s, true, hs));
     }
     return MIFVM_OK;

@@ -1,6 +1,8 @@
 """What a call costs beside another that does the same work: calls that are
 bound by launches and graph captures, compared by their times in turn (the
 smallest of several medians)."""
+import ctypes as C
+import threading
 import time
 
 import numpy as np
@@ -67,3 +69,70 @@ def test_converged_matrix_free_solve_costs_its_residual(method):
     assert free()["iterations"] == 0 and stored()["iterations"] == 0
     a, b = times(free, stored)
     assert a < 1.25 * b
+
+
+@pytest.mark.parametrize("precision", [B.FP64, B.FP32])
+def test_small_steps_cost_what_the_captured_step_does(precision):
+    """Nine launches a step bound a small mesh; a step that is waited for comes
+    within a fifth of the caller's own graph of it (3,072 cells)."""
+    st, _ = state(precision=precision)
+    step, graph = times(lambda: st.step(1, 1e-6), lambda: st.step_graph(1, 1e-6))
+    assert step < 1.2 * graph
+
+
+# 93,750 cells: every step replayed; 105,456: the first one after a wait; 384
+@pytest.mark.parametrize("precision", [B.FP64, B.FP32])
+@pytest.mark.parametrize("n", [4, 25, 26])
+def test_replayed_steps_equal_direct_launches(n, precision):
+    """Bitwise, over calls of one step, of several, and a long first one, with a
+    change of the walls between them (timed kernels are launched directly)."""
+    print(f"[gpu] replayed steps n={n} precision={precision}", flush=True)
+    (a, _), (b, _) = state(n, precision=precision), state(n, precision=precision)
+    b.kernel_timing(True)
+    for rep, steps in enumerate((40, 1, 3, 1, 1, 2)):
+        if rep == 4:
+            for st in (a, b):
+                st.set_bcs(B.VAR_SCALAR, [NEUMANN] * 6, [0.1] * 6)
+        if rep % 2:
+            assert a.cfl_dt(0.4) == b.cfl_dt(0.4)
+        for st in (a, b):
+            st.step(steps, 1e-4 / n)
+        assert torch.equal(a.get_field(B.FIELD_U), b.get_field(B.FIELD_U))
+
+
+def test_steps_beside_another_threads_capture():
+    """One thread captures a stream of its own while another steps: the capture
+    stays valid, the steps are right."""
+    with open("/proc/self/maps") as f:
+        h = C.CDLL(next(line.split()[-1] for line in f if "libamdhip64" in line))
+    (a, _), (b, _) = state(), state()
+    s, x = torch.cuda.Stream(), torch.ones(64, device="cuda")
+    torch.cuda.synchronize()
+    begun, done, errors = threading.Event(), threading.Event(), []
+
+    def steps():
+        begun.wait(30)
+        try:
+            torch.cuda.set_device(0)
+            for _ in range(4):
+                a.step(1, 1e-5)
+        except Exception as e:              # checked in the main thread
+            errors.append(e)
+        done.set()
+
+    t = threading.Thread(target=steps)
+    t.start()
+    q, g, n = C.c_void_p(s.cuda_stream), C.c_void_p(), C.c_size_t()
+    assert h.hipStreamBeginCapture(q, 0) == 0          # global
+    begun.set()
+    assert done.wait(30)
+    with torch.cuda.stream(s):
+        x.add_(1)
+    rc = h.hipStreamEndCapture(q, C.byref(g))
+    t.join(30)
+    assert rc == 0 and not errors, (rc, errors)
+    assert h.hipGraphGetNodes(g, None, C.byref(n)) == 0 and n.value == 1
+    assert h.hipGraphDestroy(g) == 0
+    for _ in range(4):
+        b.step(1, 1e-5)
+    assert torch.equal(a.get_field(B.FIELD_U), b.get_field(B.FIELD_U))
