@@ -377,8 +377,8 @@ int mifvm_fgmres_attach(mifvm_state* st, int32_t m, void* d_ws, size_t ws_bytes)
 
 /* ---- captured replays and the autotuner -----------------------------------
  * mifvm_step_graph: as mifvm_step, but the n_steps x 3 stages are captured
- * once into a hipGraph (per (n_steps, dt, CFL factor of the last
- * mifvm_cfl_dt)) and replayed on `stream`; mifvm_set_bc and
+ * once into hipGraphs (per n_steps; the calls that capture launch directly)
+ * and replayed on `stream`, whatever dt; mifvm_set_bc and
  * mifvm_poisson_assemble drop every captured graph.
  * mifvm_autotune: times the CG schedule (chunk 8/16/32/64, direct launches
  * or graph replay) on short solves of the current system (f = U; P is

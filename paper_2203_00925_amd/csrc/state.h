@@ -172,7 +172,6 @@ struct State {
     Dev d{};
     BcTable bc[2]{};                      // SCALAR, POTENTIAL
     double bc_tag_value[2][kMaxTags]{};   // the last per-tag value set (host record)
-    double step_exec_cfl = -1.0;          // CFL factor captured in step_exec
     int64_t graph_gen = 0;                // bumped whenever the captured graphs are dropped
     double diffusivity = 0.0;
     bool fp32 = false;                    // reduced-precision form of the step
@@ -183,10 +182,13 @@ struct State {
     hipStream_t cap_stream = nullptr;     // library-owned, used only to capture
     hipGraphExec_t cg_exec = nullptr;     // one chunk of CG iterations
     int cg_exec_chunk = 0, cg_exec_method = -1;
-    hipGraphExec_t step_exec = nullptr;   // n RK3 steps
+    hipGraphExec_t step_exec = nullptr;   // n RK3 steps of one dt (and CFL factor, where dt = 0)
     int step_exec_n = 0;
-    double step_exec_dt = -1.0;
-    hipGraphExec_t stage_exec = nullptr;  // the stages of one RK3 step (the time step is in device memory)
+    double step_exec_dt = -1.0, step_exec_cfl = 0.0;
+    hipGraphExec_t stages_exec = nullptr; // the stages of n steps (the time step is in device memory)
+    int stages_exec_n = 0;
+    double step_dt = -1.0, step_cfl = 0.0;   // the last call's
+    hipGraphExec_t stage_exec = nullptr;  // the stages of one step (mifvm_step)
     int64_t step_calls = 0;               // of those that may replay it
     bool waited = false;                  // the last call (a CFL evaluation, a solve) waited for its stream
     // schedule chosen by the autotuner (0 = not tuned)

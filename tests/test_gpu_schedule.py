@@ -136,3 +136,26 @@ def test_steps_beside_another_threads_capture():
     for _ in range(4):
         b.step(1, 1e-5)
     assert torch.equal(a.get_field(B.FIELD_U), b.get_field(B.FIELD_U))
+
+
+@pytest.mark.parametrize("precision", [B.FP64, B.FP32])
+def test_captured_steps_serve_every_time_step(precision):
+    """A new dt costs what a repeated one does (in the graph, it was captured
+    again: half as much more), and the result is the direct steps'."""
+    (a, _), (b, _) = state(precision=precision), state(precision=precision)
+    b.kernel_timing(True)                  # direct
+    dts = [1e-5, 2e-5, 0.0, 2e-5, 3e-5, 0.0]
+    for k, dt in enumerate(dts):
+        if dt == 0.0:
+            assert a.cfl_dt(0.1 + 0.1 * k) == b.cfl_dt(0.1 + 0.1 * k)
+        a.step_graph(3, dt)
+        b.step(3, dt)
+        assert torch.equal(a.get_field(B.FIELD_U), b.get_field(B.FIELD_U))
+    count = [0]
+
+    def new():
+        count[0] += 1
+        a.step_graph(10, 1e-6 * (1 + 1e-6 * count[0]))
+
+    fresh, same = times(new, lambda: a.step_graph(10, 1e-6))
+    assert fresh < 1.2 * same
