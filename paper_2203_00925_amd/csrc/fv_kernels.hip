@@ -354,15 +354,20 @@ __global__ __launch_bounds__(kBlock, 4) void k_grad_cells(Dev d, FvArrays<R> a, 
     const R xi = sxy.x, yi = sxy.y, zi = szu.x, ui = szu.y;
     const uint32_t fl[2] = {cl.x, cl.y}, vl[2] = {cl.z, cl.w};
     R jx = R(0), jy = R(0), jz = R(0);
-    R ox[4], oy[4], oz[4];                                // x_i - x_v
+    R ox[4], oy[4], oz[4];                                // x_i - x_v, formed ahead of the sums that wait for them
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
         const int l = int(vl[k >> 1] >> (16 * (k & 1))) & 0xffff;
-        const V2 A = va[l], Bv = vb[l], C = vc[l], Dv = vd[l], E = ve[l];
-        const R nd = Bv.y * (Dv.y - ui);
+        const V2 E = ve[l];
         ox[k] = xi - E.x;
         oy[k] = yi - E.y;
         oz[k] = zi - vf[l];
+    }
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        const int l = int(vl[k >> 1] >> (16 * (k & 1))) & 0xffff;
+        const V2 A = va[l], Bv = vb[l], C = vc[l], Dv = vd[l];
+        const R nd = Bv.y * (Dv.y - ui);
         jx += C.x + (A.x - ox[k]) * nd;                   // xb - x_i
         jy += C.y + (A.y - oy[k]) * nd;
         jz += Dv.x + (Bv.x - oz[k]) * nd;
