@@ -282,8 +282,9 @@ void mifvm_state_destroy(mifvm_state* st);
  * value is written to every ghost of the tag in device memory (the call
  * synchronises the device before and after).  It takes effect at the next
  * step (SCALAR) or solve (POTENTIAL; a stored matrix must be assembled
- * again).  Captured graphs (mifvm_step_graph, graph-replayed solves) are
- * dropped and captured again at their next use.                           */
+ * again).  Another kind drops the captured graphs (mifvm_step_graph,
+ * graph-replayed solves), which are captured again at their next use;
+ * another value alone keeps them.                                         */
 int mifvm_set_bc(mifvm_state* st, int32_t var, int32_t tag, int32_t kind, double value);
 /* Per-face values for one tag of one variable, for data that varies along
  * a boundary (Dirichlet data at each face's foot point, a Neumann flux per
@@ -340,7 +341,7 @@ int mifvm_mesh_values(const mifvm_state* st, int32_t what, double* out, int32_t 
  * Assemble K and the ghost-constant vector c of K P = -mu*f + c, from the
  * POTENTIAL boundary conditions (rows without the 1/mu_i factor, sign
  * flipped so that the diagonal is positive).  E_STATE for a mesh
- * preprocessed with no_matrix.  Drops captured graphs.  Asynchronous.      */
+ * preprocessed with no_matrix.  Asynchronous.                              */
 int mifvm_poisson_assemble(mifvm_state* st, void* stream);
 /* d_y = K d_x, both user order.                                            */
 int mifvm_poisson_apply(mifvm_state* st, const double* d_x, double* d_y, void* stream);
@@ -378,8 +379,8 @@ int mifvm_fgmres_attach(mifvm_state* st, int32_t m, void* d_ws, size_t ws_bytes)
 /* ---- captured replays and the autotuner -----------------------------------
  * mifvm_step_graph: as mifvm_step, but the n_steps x 3 stages are captured
  * once into hipGraphs (per n_steps; the calls that capture launch directly)
- * and replayed on `stream`, whatever dt; mifvm_set_bc and
- * mifvm_poisson_assemble drop every captured graph.
+ * and replayed on `stream`, whatever dt; a kind that mifvm_set_bc changes
+ * drops every captured graph.
  * mifvm_autotune: times the CG schedule (chunk 8/16/32/64, direct launches
  * or graph replay) on short solves of the current system (f = U; P is
  * restored afterwards) and one step direct vs replayed (U restored); keeps

@@ -533,13 +533,16 @@ int mifvm_set_bc(mifvm_state* st, int32_t var, int32_t tag, int32_t kind, double
     HIPCHK(hipDeviceSynchronize());
     HIPCHK(launch_set_bc_values(s.d, var, tag, value, nullptr, nullptr));
     HIPCHK(hipDeviceSynchronize());
+    // captured launches and the matrix-free tables hold the kinds; the values
+    // they read from device memory
+    const bool other = s.bc[var].kind[tag] != kind;
     s.bc[var].kind[tag] = kind;
     s.bc_tag_value[var][tag] = value;
-    drop_graphs(s);                           // captured launches hold the kinds by value
+    if (other) drop_graphs(s);
     if (var == MIFVM_VAR_POTENTIAL) {
         s.assembled = false;
         s.consts_ready = false;
-        s.mfc_ready = false;
+        if (other) s.mfc_ready = false;
     }
     return MIFVM_OK;
 }
@@ -931,7 +934,6 @@ int mifvm_poisson_assemble(mifvm_state* st, void* stream) {
     s.consts_ready = true;
     s.k32_ready = false;
     s.kt_ready = false;
-    drop_graphs(s);
     return MIFVM_OK;
 }
 

@@ -221,8 +221,8 @@ struct State {
     int amg_exec_key = 0;
 };
 
-// destroy every captured graph (their launch arguments hold boundary kinds,
-// the CFL factor and chunk sizes by value); the next use captures again
+// destroy every captured graph (their launch arguments hold the boundary kinds
+// by value); the next use captures again
 void drop_graphs(State& s);
 // value of every ghost of `tag` for variable var: `value`, or, when vals is
 // not null, vals[caller's boundary triangle of the ghost]
