@@ -159,8 +159,8 @@ typedef struct {
     int32_t graph;             /* 1: enqueue each chunk by replaying a captured
                                   hipGraph (not while kernel timing is on);
                                   -1: the autotuned choice; else direct
-                                  for the first chunk, while the next
-                                  is captured, then replays                */
+                                  launches until a graph is captured
+                                  behind a chunk, then replays             */
     double inner_tol;          /* IR_FP32: relative reduction asked of each
                                   FP32 inner solve (0 = 1e-4)                */
     int32_t stall_window;      /* LEARNED: fall back when the best residual

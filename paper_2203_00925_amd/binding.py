@@ -547,7 +547,8 @@ class State:
                       allow_not_converged=False, stall_window=0, learned_maxit=0,
                       allow_fell_back=False, matrix_free=False, learned_smoother=False):
         """chunk 0 / graph -1: the autotuned schedule (when not tuned, 32
-        iterations per host check, chunks after the first replayed)."""
+        iterations per host check, launched until a graph is captured behind
+        one, then replayed)."""
         import torch
         if f is not None:
             f = f.to(device=self.device, dtype=torch.float64).contiguous()

@@ -180,8 +180,14 @@ struct State {
     std::vector<double> last_rel;
     // captured launch sequences (hipGraph), replayed on the caller's stream
     hipStream_t cap_stream = nullptr;     // library-owned, used only to capture
-    hipGraphExec_t cg_exec = nullptr;     // one chunk of CG iterations
-    int cg_exec_chunk = 0, cg_exec_method = -1;
+    // one chunk of CG iterations, a graph each for the plain and the FP32 inner
+    // form, on the stored matrix and matrix-free: its iterations, those a chunk
+    // of the last such solve had, and how many chunks that took
+    struct CgGraph {
+        hipGraphExec_t exec = nullptr;
+        int chunk = 0, asked = 0, took = 0;
+    };
+    CgGraph cg_graph[4];
     hipGraphExec_t step_exec = nullptr;   // n RK3 steps of one dt (and CFL factor, where dt = 0)
     int step_exec_n = 0;
     double step_exec_dt = -1.0, step_exec_cfl = 0.0;

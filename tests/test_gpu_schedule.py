@@ -227,3 +227,49 @@ def test_boundary_changes_reach_replayed_work(kind):
         st.step_graph(2, 1e-5) if st is a else st.step(2, 1e-5)
         st.step(1, 1e-5)
     assert torch.equal(a.get_field(B.FIELD_U), fresh.get_field(B.FIELD_U))
+
+
+def test_solves_in_turn_keep_their_graphs():
+    """Plain and refined solves, matrix-free and stored, taking turns with
+    chunks of 512 iterations: each keeps its graph, so a turn costs what its
+    solves cost one after the other."""
+    st, f = state()
+    st.poisson_assemble()
+    zero = torch.zeros_like(f)
+    forms = [dict(method=m, matrix_free=free) for m in (B.SOLVE_PLAIN, B.SOLVE_IR_FP32) for free in (True, False)]
+
+    def solve(kw):
+        st.set_field(B.FIELD_P, zero)
+        st.poisson_solve(f, tol=1e-3, chunk=512, graph=1, **kw)
+
+    def twice(kw):
+        solve(kw)
+        solve(kw)
+
+    turns = lambda: [solve(kw) for kw in forms + forms]
+    runs = lambda: [twice(kw) for kw in forms]
+    turns()
+    a, b = times(turns, runs, reps=3, rounds=3)
+    assert a < 1.2 * b
+
+
+def test_solve_within_one_chunk_makes_no_graph():
+    """A limit that leaves no second chunk: the first call of a new state costs
+    what the second does (the capture was half as long as its 20 iterations)."""
+    firsts, seconds = [], []
+    mesh = B.Mesh.from_cube(cube(8, 1008))
+    f = torch.from_numpy(np.random.default_rng(5).normal(size=mesh.info.nc)).cuda()
+    for _ in range(15):
+        st = B.State(mesh)
+        st.set_bcs(B.VAR_POTENTIAL, KINDS, VALS)
+        st.poisson_rhs(f)
+        for out in (firsts, seconds):
+            st.set_field(B.FIELD_P, torch.zeros_like(f))
+            torch.cuda.synchronize()
+            t = time.perf_counter()
+            st.poisson_solve(f, tol=1e-9, maxit=20, matrix_free=True, allow_not_converged=True)
+            torch.cuda.synchronize()
+            out.append((time.perf_counter() - t) * 1e6)
+    a, b = float(np.median(firsts)), float(np.median(seconds))
+    print(f"[gpu] {a:.0f} us, {b:.0f} us", flush=True)
+    assert a < 1.2 * b
