@@ -32,7 +32,7 @@ struct mifvm_batch {
     int grid = 0, item_rows = 0, policy = 0, vb = 8, chunk = 32;
     hipGraphExec_t exec = nullptr;            // captured run
     int exec_steps = 0, exec_every = 0, exec_maxit = 0, exec_restart = 0;
-    double exec_tol = 0.0;
+    double exec_tol = 0.0, exec_cfl = 0.0;
     int64_t exec_gen = -1;
 };
 
@@ -447,7 +447,7 @@ int mifvm_batch_run(mifvm_batch* h, int32_t n_steps, const mifvm_batch_solve_opt
         return report_launches(h, it, rel, info, t0, solves);
     }
     if (!h->exec || h->exec_steps != n_steps || h->exec_every != every || h->exec_tol != tol ||
-        h->exec_maxit != maxit || h->exec_restart != restart || h->exec_gen != s.graph_gen) {
+        h->exec_maxit != maxit || h->exec_restart != restart || h->exec_cfl != s.cfl || h->exec_gen != s.graph_gen) {
         HIPCHK(capture_graph(s, &h->exec, [&](hipStream_t q) -> hipError_t {
             bool first = true;
             for (int k = 0; k < n_steps; ++k) {
@@ -465,6 +465,7 @@ int mifvm_batch_run(mifvm_batch* h, int32_t n_steps, const mifvm_batch_solve_opt
         h->exec_tol = tol;
         h->exec_maxit = maxit;
         h->exec_restart = restart;
+        h->exec_cfl = s.cfl;                  // an argument of the captured steps
         h->exec_gen = s.graph_gen;
     }
     HIPCHK(hipGraphLaunch(h->exec, hs));

@@ -273,3 +273,25 @@ def test_solve_within_one_chunk_makes_no_graph():
     a, b = float(np.median(firsts)), float(np.median(seconds))
     print(f"[gpu] {a:.0f} us, {b:.0f} us", flush=True)
     assert a < 1.2 * b
+
+
+@pytest.mark.parametrize("policy", [B.BQ_XCD, B.BQ_LAUNCHES])
+def test_batch_run_takes_the_last_cfl_factor(policy):
+    """A run captured under one CFL factor steps by the next one after another
+    CFL evaluation: bitwise the steps themselves."""
+    print(f"[gpu] batch run after another CFL factor, policy {policy}", flush=True)
+    ms = [cube(n, 1000 + n) for n in (4, 5)]
+    mesh = B.Mesh.from_batch(ms)
+    a, b = B.State(mesh, diffusivity=1e-3), B.State(mesh, diffusivity=1e-3)
+    vel = np.concatenate([synth.rotating_velocity(m) for m in ms]).T.ravel()
+    for st in (a, b):
+        st.set_bcs(B.VAR_POTENTIAL, [DIRICHLET] * 6)
+        st.set_field(B.FIELD_VEL, torch.from_numpy(np.ascontiguousarray(vel)))
+        st.set_field(B.FIELD_U, torch.from_numpy(np.concatenate([synth.gaussian_field(m) for m in ms])))
+    batch = B.Batch(a, policy=policy)
+    for cfl in (0.4, 0.1, 0.3):
+        a.cfl_dt(cfl)
+        b.cfl_dt(cfl)
+        batch.run(1, tol=1e-8)
+        b.step(1, 0.0)
+        assert torch.equal(a.get_field(B.FIELD_U), b.get_field(B.FIELD_U))
