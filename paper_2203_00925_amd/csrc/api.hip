@@ -106,9 +106,10 @@ size_t layout(const Mesh& m, char* base, Dev& d) {
     d.tile_rows = m.tile_rows;
     d.halo_max = m.halo_max;
     d.ntiles = (int64_t)m.h_self.size();
-    d.h_off = carve<int64_t>(base, off, m.h_off.size());
-    d.h_idx = carve<int32_t>(base, off, m.h_idx.size());
-    d.h_self = carve<int32_t>(base, off, m.h_self.size());
+    const bool halos = !m.kmat.off.empty();                // the stored products' alone
+    d.h_off = carve<int64_t>(base, off, halos ? m.h_off.size() : 0);
+    d.h_idx = carve<int32_t>(base, off, halos ? m.h_idx.size() : 0);
+    d.h_self = carve<int32_t>(base, off, halos ? m.h_self.size() : 0);
     d.k_lidx = carve<uint16_t>(base, off, m.k_lidx.size());
     d.cell_perm = carve<int32_t>(base, off, nc);
     d.vert_perm = carve<int32_t>(base, off, nv);
@@ -417,7 +418,9 @@ int mifvm_state_create(const mifvm_mesh* mesh, const mifvm_params* params, void*
     UPB(d.vpos, m.vpos); UPB(d.vmean, m.vmean); UPB(d.voff, m.voff); UPB(d.vslope, m.vslope);
     UP(d.k_off, m.kmat.off); UP(d.k_w, m.kmat.width); UP(d.k_col, m.kmat.idx); UP(d.k_len, m.klen);
     UP(d.cell_perm, m.cell_perm); UP(d.vert_perm, m.vert_perm);
-    UP(d.h_off, m.h_off); UP(d.h_idx, m.h_idx); UP(d.h_self, m.h_self);
+    if (!m.kmat.off.empty()) {
+        UP(d.h_off, m.h_off); UP(d.h_idx, m.h_idx); UP(d.h_self, m.h_self);
+    }
     UP(d.mesh_start, m.mesh_start);
     {
         const CgPlan cg = cg_plan(m);

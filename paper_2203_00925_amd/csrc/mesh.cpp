@@ -873,6 +873,13 @@ int preprocess(const double* xyz, int64_t nv, const int32_t* tets, int64_t nc,
         for (int k = 0; ok && k < 4; ++k)
             ok = int64_t(M.g_cell[8 * r + k]) < gn && M.g_idx[g0 + M.g_cell[8 * r + k]] == M.c2n[k * nc + r] &&
                  int64_t(M.g_cell[8 * r + 4 + k]) < M.gv_off[g + 1] - M.gv_off[g];
+        // its vertices: with face k's three, all four of the cell
+        int64_t all = 0;
+        for (int k = 0; k < 4; ++k) all += vold2new[cell_verts[new2old[r]][k]];
+        for (int k = 0; ok && k < 4; ++k) {
+            const int32_t code = M.c2f[k * nc + r], f = code >= 0 ? code : ~code;
+            ok = M.gv_idx[M.gv_off[g] + M.g_cell[8 * r + 4 + k]] == all - M.fA[f] - M.fB[f] - M.fC[f];
+        }
         for (int64_t k = 0; ok && k < M.eptr[r + 1] - M.eptr[r]; ++k) {
             const int64_t at = 8 * (M.ge_off[r >> 6] + (k >> 3) * 64 + (r & 63)) + (k & 7);
             ok = int64_t(M.ge_idx[at]) < gn && M.g_idx[g0 + M.ge_idx[at]] == M.eidx[M.eptr[r] + k];

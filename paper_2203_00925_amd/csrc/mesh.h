@@ -60,7 +60,7 @@ struct Mesh {
     // corresponding 64-row slices.
     int32_t tile_rows = 256;
     int32_t halo_max = 0;
-    std::vector<int64_t> h_off;       // ntiles + 1
+    std::vector<int64_t> h_off;       // ntiles + 1 (on the device with a matrix only)
     std::vector<int32_t> h_idx;       // halo entities
     std::vector<int32_t> h_self;      // ntiles: local index of the tile's first cell
     std::vector<uint16_t> k_lidx;     // like kmat.idx, local
