@@ -42,12 +42,12 @@ METRIC = "FV cell-updates/s + Poisson solve ms @1e-10 rel; plain vs mixed/learne
 # it when that source (the kernel's file and the reduction headers) still
 # hashes to the recorded prefix, else null.
 MEASURED_TRAFFIC = {"cube120": {
-    "k_cg_product_tiles": {"src": "bc066d6c4d1174dd", "bytes": 1155842457},
-    "k_cg_residual": {"src": "bc066d6c4d1174dd", "bytes": 415684608},
-    "k_cg_direction": {"src": "bc066d6c4d1174dd", "bytes": 1052607180},
-    "k_vertex_moments_tiles": {"src": "2f5d52e9b5f6f4ea", "bytes": 989898854},
-    "k_grad_cells": {"src": "2f5d52e9b5f6f4ea", "bytes": 2604359475},
-    "k_cell_step": {"src": "2f5d52e9b5f6f4ea", "bytes": 2158360473},
+    "k_cg_product_tiles": {"src": "e69d83f6e2940465", "bytes": 1156493107},
+    "k_cg_residual": {"src": "e69d83f6e2940465", "bytes": 415690752},
+    "k_cg_direction": {"src": "e69d83f6e2940465", "bytes": 1052611686},
+    "k_vertex_moments_tiles": {"src": "c99280cdb9b9a1cc", "bytes": 989946777},
+    "k_grad_cells": {"src": "c99280cdb9b9a1cc", "bytes": 2603799552},
+    "k_cell_step": {"src": "c99280cdb9b9a1cc", "bytes": 2159079526},
 }}
 # timing id -> the FP64 kernel it times (the product on a mesh of this size)
 KERNEL_NAMES = {"grad_limiter": "k_grad_cells", "node_interp": "k_vertex_moments_tiles", "fv_cell": "k_cell_step",

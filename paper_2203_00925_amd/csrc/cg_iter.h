@@ -10,9 +10,10 @@ namespace mifvm {
 
 // A block works on rows of one mesh only and writes one partial per dot
 // product; every block of the next kernel adds all the partials of its mesh
-// itself.  The vector kernels take up to 1024 blocks a mesh (four a CU, so
-// that the CUs stay even: 844 blocks made a product of 1.3M rows 18% slower
-// than 5,063), several rows a thread where a mesh has more than 1024 * 256.
+// itself.  The vector kernels take about 1024 blocks for the whole state (four
+// a CU, so that the CUs stay even: 844 blocks made a product of 1.3M rows 18%
+// slower than 5,063) and no more for any mesh, several rows a thread where 256
+// each do not reach (cg_plan).
 // The product's gathers want many short blocks instead: one row a thread up
 // to 8192 blocks (their partials, 64 KB, come from L2 for all but the first
 // block of an XCD).

@@ -14,9 +14,9 @@
 //                   faces, summed, and the stage update.
 // The residual evaluation that returns the face fluxes runs the face kernel
 // k_face_flux (one thread per face) after the gradient kernel instead.
-// Ghost values (behind boundary faces) are materialised by k_ghost_fill
-// before a run of steps and by k_cell_step after every stage, so every
-// gather is a plain indexed load.
+// Ghost values (behind boundary faces) are materialised by k_step_begin
+// before a run of steps (k_ghost_fill elsewhere) and by k_cell_step after every
+// stage, so every gather is a plain indexed load.
 //
 // Every kernel is instantiated for FP64 (the method as stated) and FP32 (the
 // reduced-precision form: state, gradients, fluxes and geometry copies in

@@ -1,9 +1,11 @@
 // Poisson system of the discretisation (Sec. 2.2, eqs. (7), (laplace)):
 // on-device assembly into 64-row slices, the sparse product, and the
 // Jacobi-preconditioned conjugate-gradient iteration with every scalar kept
-// in device memory (alpha, beta and the convergence test are computed by the
-// last block of the kernel that produces their partial sums; later kernels
-// of an enqueued chunk return at once when the solve has finished).
+// in device memory (alpha, beta and the convergence test are computed by a
+// kernel of one block per mesh behind the one that leaves their partial sums;
+// later kernels of an enqueued chunk return at once when the solve has
+// finished).  Where no vertex lies in two meshes, matrix-free, and on the stored
+// matrix of one mesh, cg_iter.hip has the iteration.
 #include "cg_dev.h"
 #include "cg_scalars.h"
 #include "reduce.h"

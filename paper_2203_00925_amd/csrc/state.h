@@ -142,7 +142,7 @@ template <class R>
 struct FvArrays {
     R *u, *grad, *psi, *unode, *flux;
     const R *phi, *minv, *kAC, *kBC, *kRL, *area, *vol, *src, *fx, *xc, *gdist;
-    // the per-cell stage: face values [4][nc], vertex and kRL weights, outward phi
+    // the per-cell stage (quad.h): face values, vertex and kRL weights, outward phi
     R* uf;
     const R *cw, *cr, *cphi;
     typename Vec4T<R>::T* vmom;           // [nv] moments of the vertex lists

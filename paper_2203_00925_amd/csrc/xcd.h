@@ -23,13 +23,14 @@ inline unsigned pad8(int64_t n) { return unsigned((n + kXcds - 1) / kXcds * kXcd
 inline unsigned rows_m(int64_t n, int block) { return pad8((n + block - 1) / block); }
 
 // The same for a step's kernels, which read some dozen arrays once: above
-// 4,096 blocks (1M cells; below, the arrays stay in the caches from one kernel
-// to the next) the XCDs take windows of 32 blocks each in turn.  Eight distant
-// streams per array cost the HBM a tenth of its rate (eleven arrays of 3.1M
-// 16-byte items: 5.31 TB/s in eighths, 5.88 in plain order), and a window of
-// 8,192 rows keeps nearly all of their neighbours in its L2.  Two steps at
-// 3.07M cells: eighths 2,067 us, windows of 8 blocks 2,015, of 32 2,011, of 128
-// 2,050; four at 304k cells: eighths 478, windows of 32 498.
+// 4,096 blocks (1M cells, or 262k vertices of the moments) the XCDs take
+// windows of 32 blocks each in turn.  Eight distant streams per array cost the
+// HBM a tenth of its rate (eleven arrays of 3.1M 16-byte items: 5.31 TB/s in
+// eighths, 5.88 in plain order), and a window of 8,192 rows keeps nearly all of
+// their neighbours in its L2.  Measured on both sides of the line, not at it:
+// two steps at 3.07M cells (12,000 blocks) eighths 2,067 us, windows of 8
+// blocks 2,015, of 32 2,011, of 128 2,050; four at 304k (1,187 blocks) eighths
+// 478, windows of 32 498.
 // The order is an argument: a choice between the two in the kernel is a branch
 // before its first load (48k cells, ten steps: 459 us against 442).
 struct BlockOrder {
