@@ -271,10 +271,12 @@ def main():
     stream = torch.cuda.current_stream()
     # the FV step replays the library's captured step graph (the time step and
     # the ghosts in one launch, 3 stages of 3); capture it here, outside
-    # warm-up and timing, and undo the
-    # step it runs so that the state stays in step with the forms' runs
+    # warm-up and timing, replay it once (a graph's first replay takes longer),
+    # and undo the steps this runs so that the state stays in step with the
+    # forms' runs
     u_keep = st.get_field(B.FIELD_U).clone()
-    st.step_graph(1, dt)
+    for _ in range(2):
+        st.step_graph(1, dt)
     st.set_field(B.FIELD_U, u_keep)
     del u_keep
 
@@ -690,7 +692,8 @@ def run_small_form():
     st.poisson_assemble()
     dt = st.cfl_dt(pf.cfl)
     u0 = st.get_field(B.FIELD_U).clone()
-    st.step_graph(10, dt)                               # capture (and one untimed run)
+    for _ in range(2):                                  # capture, and one untimed replay
+        st.step_graph(10, dt)
     st.set_field(B.FIELD_U, u0)
     stream = torch.cuda.current_stream()
     e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
@@ -921,7 +924,8 @@ def run_batch(args, steps=None, warmup=None):
     nc = M.info.nc
     # the FV steps alone (captured step graph), restored afterwards
     u_keep = st.get_field(B.FIELD_U).clone()
-    st.step_graph(steps, 0.0)                        # capture outside the timing
+    for _ in range(2):                               # capture and one replay outside the timing
+        st.step_graph(steps, 0.0)
     st.set_field(B.FIELD_U, u_keep)
     e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
     torch.cuda.synchronize()
