@@ -2,6 +2,7 @@
 #pragma once
 #include <algorithm>
 #include <cstdint>
+#include <exception>
 #include <system_error>
 #include <thread>
 #include <vector>
@@ -18,19 +19,29 @@ inline int setup_threads(int64_t n) {
 // f(k, lo, hi) for the nt contiguous chunks [lo, hi) of [0, n), chunk k on
 // its own thread (chunk 0 on the caller's, and those that get no thread);
 // every row is handled by exactly one call, so results do not depend on nt.
-// f does not throw.
+// What a call throws is thrown here, once all have ended.
 template <class F>
 void for_chunks(int64_t n, int nt, F&& f) {
+    std::vector<std::exception_ptr> thrown(size_t(nt), nullptr);
+    auto run = [&f, &thrown, n, nt](int k) {
+        try {
+            f(k, n * k / nt, n * (k + 1) / nt);
+        } catch (...) {
+            thrown[k] = std::current_exception();
+        }
+    };
     std::vector<std::thread> th;
     th.reserve(size_t(nt));
     int k = 1;
     try {
-        for (; k < nt; ++k) th.emplace_back([&f, n, nt, k] { f(k, n * k / nt, n * (k + 1) / nt); });
+        for (; k < nt; ++k) th.emplace_back(run, k);
     } catch (const std::system_error&) {
     }
-    f(0, 0, n / nt);
-    for (; k < nt; ++k) f(k, n * k / nt, n * (k + 1) / nt);
+    run(0);
+    for (; k < nt; ++k) run(k);
     for (auto& t : th) t.join();
+    for (auto& e : thrown)
+        if (e) std::rethrow_exception(e);
 }
 
 }  // namespace mifvm

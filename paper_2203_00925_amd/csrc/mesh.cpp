@@ -117,6 +117,60 @@ void pack_sell(const std::vector<int64_t>& ptr, const std::vector<int32_t>& idx,
     }
 }
 
+// The distinct entities one tile names: collected, then numbered in ascending
+// order.  A small hash table instead of an array over all entities, so that
+// threads work on tiles of their own.
+class LocalSet {
+public:
+    std::vector<int32_t> list;            // ascending once numbered
+
+    void open() {
+        list.clear();
+        std::fill(key_.begin(), key_.end(), -1);
+    }
+    void take(int32_t e) {
+        const size_t at = find(e);
+        if (key_[at] == e) return;
+        key_[at] = e;
+        list.push_back(e);
+        if (2 * list.size() <= key_.size()) return;
+        key_.assign(2 * key_.size(), -1);
+        place_.resize(key_.size());
+        for (int32_t q : list) key_[find(q)] = q;
+    }
+    void number() {
+        std::sort(list.begin(), list.end());
+        for (size_t h = 0; h < list.size(); ++h) place_[find(list[h])] = int32_t(h);
+    }
+    int32_t operator[](int32_t e) const { return place_[find(e)]; }
+
+private:
+    size_t find(int32_t e) const {        // e's slot, or the free one where it goes
+        const size_t mask = key_.size() - 1;
+        size_t at = (uint32_t(e) * 2654435761u >> 8) & mask;
+        while (key_[at] != e && key_[at] != -1) at = (at + 1) & mask;
+        return at;
+    }
+    std::vector<int32_t> key_ = std::vector<int32_t>(1024, -1), place_ = std::vector<int32_t>(1024, 0);
+};
+
+// Lists of tiles, collected by chunks of them, one after the other: off[t + 1]
+// holds tile t's length on entry, the offsets on return; the longest list.
+int32_t join_lists(std::vector<int64_t>& off, std::vector<std::vector<int32_t>>& parts, std::vector<int32_t>& out) {
+    int64_t most = 0;
+    for (size_t t = 1; t < off.size(); ++t) {
+        most = std::max(most, off[t]);
+        off[t] += off[t - 1];
+    }
+    out.clear();
+    out.reserve(size_t(off.back()));
+    for (auto& p : parts) {
+        out.insert(out.end(), p.begin(), p.end());
+        std::vector<int32_t>().swap(p);
+    }
+    return int32_t(most);
+}
+
 }  // namespace
 
 int preprocess(const double* xyz, int64_t nv, const int32_t* tets, int64_t nc,
@@ -749,13 +803,8 @@ int preprocess(const double* xyz, int64_t nv, const int32_t* tets, int64_t nc,
         const int64_t T = M.tile_rows, nt = (nc + T - 1) / T;
         M.g_rows = int32_t(T);
         M.g_off.assign(nt + 1, 0);
-        M.g_idx.clear();
-        M.g_idx.reserve(size_t(nc) * 3);
         M.g_self.assign(nt, 0);
         M.gv_off.assign(nt + 1, 0);
-        M.gv_idx.clear();
-        M.gv_idx.reserve(size_t(nc) / 2 + 4);
-        M.g_max = M.gv_max = 0;
         M.g_cell.assign(8 * nc, 0);
         const int64_t ns = (nc + 63) / 64;
         M.ge_off.assign(ns + 1, 0);
@@ -765,92 +814,74 @@ int preprocess(const double* xyz, int64_t nv, const int32_t* tets, int64_t nc,
             M.ge_off[s + 1] = M.ge_off[s] + (w + 7) / 8 * 64;
         }
         M.ge_idx.assign(8 * M.ge_off[ns], 0);
-        std::fill(seen.begin(), seen.end(), -1);
-        std::vector<int32_t> v2l(nv, -1), buf;
-        for (int64_t t = 0; t < nt; ++t) {
-            const int64_t t0 = t * T, t1 = std::min(nc, t0 + T);
-            buf.clear();
-            auto take = [&](int32_t e) {
-                if (seen[e] != t) {
-                    seen[e] = t;
-                    buf.push_back(e);
-                }
-            };
-            for (int64_t r = t0; r < t1; ++r) take(int32_t(r));
-            for (int64_t e = M.eptr[t0]; e < M.eptr[t1]; ++e) take(M.eidx[e]);
-            for (int64_t r = t0; r < t1; ++r)
-                for (int k = 0; k < 4; ++k) take(M.c2n[k * nc + r]);
-            std::sort(buf.begin(), buf.end());
-            for (size_t h = 0; h < buf.size(); ++h) g2l[buf[h]] = int32_t(h);
-            M.g_self[t] = g2l[t0];
-            M.g_idx.insert(M.g_idx.end(), buf.begin(), buf.end());
-            M.g_off[t + 1] = (int64_t)M.g_idx.size();
-            M.g_max = std::max<int32_t>(M.g_max, (int32_t)buf.size());
-            buf.clear();
-            for (int64_t r = t0; r < t1; ++r)
-                for (int k = 0; k < 4; ++k) {
-                    const int32_t v = vold2new[cell_verts[new2old[r]][k]];
-                    if (v2l[v] == -1) {
-                        v2l[v] = 0;
-                        buf.push_back(v);
+        const int threads = setup_threads(nc);
+        std::vector<std::vector<int32_t>> halos(threads), verts(threads);
+        for_chunks(nt, threads, [&](int chunk, int64_t lo, int64_t hi) {
+            LocalSet ent, vert;
+            for (int64_t t = lo; t < hi; ++t) {
+                const int64_t t0 = t * T, t1 = std::min(nc, t0 + T);
+                ent.open();
+                vert.open();
+                for (int64_t r = t0; r < t1; ++r) ent.take(int32_t(r));
+                for (int64_t e = M.eptr[t0]; e < M.eptr[t1]; ++e) ent.take(M.eidx[e]);
+                for (int64_t r = t0; r < t1; ++r)
+                    for (int k = 0; k < 4; ++k) {
+                        ent.take(M.c2n[k * nc + r]);
+                        vert.take(vold2new[cell_verts[new2old[r]][k]]);
                     }
-                }
-            std::sort(buf.begin(), buf.end());
-            for (size_t q = 0; q < buf.size(); ++q) v2l[buf[q]] = int32_t(q);
-            M.gv_idx.insert(M.gv_idx.end(), buf.begin(), buf.end());
-            M.gv_off[t + 1] = (int64_t)M.gv_idx.size();
-            M.gv_max = std::max<int32_t>(M.gv_max, (int32_t)buf.size());
-            for (int64_t r = t0; r < t1; ++r) {
-                for (int k = 0; k < 4; ++k) {
-                    const int32_t code = M.c2f[k * nc + r], f = code >= 0 ? code : ~code;
-                    // the vertex across from face k
-                    int32_t opp = -1;
-                    for (int q = 0; q < 4; ++q) {
-                        const int32_t v = vold2new[cell_verts[new2old[r]][q]];
-                        if (v != M.fA[f] && v != M.fB[f] && v != M.fC[f]) opp = v;
+                ent.number();
+                vert.number();
+                M.g_self[t] = ent[int32_t(t0)];
+                halos[chunk].insert(halos[chunk].end(), ent.list.begin(), ent.list.end());
+                verts[chunk].insert(verts[chunk].end(), vert.list.begin(), vert.list.end());
+                M.g_off[t + 1] = (int64_t)ent.list.size();
+                M.gv_off[t + 1] = (int64_t)vert.list.size();
+                for (int64_t r = t0; r < t1; ++r) {
+                    for (int k = 0; k < 4; ++k) {
+                        const int32_t code = M.c2f[k * nc + r], f = code >= 0 ? code : ~code;
+                        // the vertex across from face k
+                        int32_t opp = -1;
+                        for (int q = 0; q < 4; ++q) {
+                            const int32_t v = vold2new[cell_verts[new2old[r]][q]];
+                            if (v != M.fA[f] && v != M.fB[f] && v != M.fC[f]) opp = v;
+                        }
+                        M.g_cell[8 * r + k] = (uint16_t)ent[M.c2n[k * nc + r]];
+                        M.g_cell[8 * r + 4 + k] = (uint16_t)vert[opp];
                     }
-                    M.g_cell[8 * r + k] = (uint16_t)g2l[M.c2n[k * nc + r]];
-                    M.g_cell[8 * r + 4 + k] = (uint16_t)v2l[opp];
-                }
-                const int64_t s = r >> 6, w = (M.ge_off[s + 1] - M.ge_off[s]) / 64 * 8, n = M.eptr[r + 1] - M.eptr[r];
-                for (int64_t k = 0; k < w; ++k) {
-                    const int32_t e = k < n ? M.eidx[M.eptr[r] + k] : int32_t(r);
-                    M.ge_idx[8 * (M.ge_off[s] + (k >> 3) * 64 + (r & 63)) + (k & 7)] = (uint16_t)g2l[e];
+                    const int64_t s = r >> 6, w = (M.ge_off[s + 1] - M.ge_off[s]) / 64 * 8, n = M.eptr[r + 1] - M.eptr[r];
+                    for (int64_t k = 0; k < w; ++k) {
+                        const int32_t e = k < n ? M.eidx[M.eptr[r] + k] : int32_t(r);
+                        M.ge_idx[8 * (M.ge_off[s] + (k >> 3) * 64 + (r & 63)) + (k & 7)] = (uint16_t)ent[e];
+                    }
                 }
             }
-            for (int32_t v : buf) v2l[v] = -1;
-            for (int64_t h = M.g_off[t]; h < M.g_off[t + 1]; ++h) g2l[M.g_idx[h]] = -1;
-        }
+        });
+        M.g_max = join_lists(M.g_off, halos, M.g_idx);
+        M.gv_max = join_lists(M.gv_off, verts, M.gv_idx);
     }
     mark("gradient tiles");
     // -- 16. halos of the vertex lists' slices ---------------------------------------
     {
         const int64_t ns = (nv + 63) / 64;
         M.nh_off.assign(ns + 1, 0);
-        M.nh_idx.clear();
-        M.nh_idx.reserve(size_t(nc) * 5 / 2);
         M.nl_idx.assign(M.node.idx.size(), 0);
-        M.nh_max = 0;
-        std::fill(seen.begin(), seen.end(), -1);
-        std::vector<int32_t> buf;
-        for (int64_t s = 0; s < ns; ++s) {
-            const int64_t v0 = s * 64, v1 = std::min(nv, v0 + 64);
-            buf.clear();
-            for (int64_t e = M.nptr[v0]; e < M.nptr[v1]; ++e)
-                if (seen[M.nidx[e]] != s) {
-                    seen[M.nidx[e]] = s;
-                    buf.push_back(M.nidx[e]);
-                }
-            std::sort(buf.begin(), buf.end());
-            for (size_t h = 0; h < buf.size(); ++h) g2l[buf[h]] = int32_t(h);
-            for (int64_t v = v0; v < v1; ++v)
-                for (int64_t k = 0; k < M.nptr[v + 1] - M.nptr[v]; ++k)
-                    M.nl_idx[M.node.off[s] + k * 64 + (v & 63)] = (uint16_t)g2l[M.nidx[M.nptr[v] + k]];
-            M.nh_idx.insert(M.nh_idx.end(), buf.begin(), buf.end());
-            M.nh_off[s + 1] = (int64_t)M.nh_idx.size();
-            M.nh_max = std::max<int32_t>(M.nh_max, (int32_t)buf.size());
-            for (int32_t e : buf) g2l[e] = -1;
-        }
+        const int threads = setup_threads(nv);
+        std::vector<std::vector<int32_t>> halos(threads);
+        for_chunks(ns, threads, [&](int chunk, int64_t lo, int64_t hi) {
+            LocalSet ent;
+            for (int64_t s = lo; s < hi; ++s) {
+                const int64_t v0 = s * 64, v1 = std::min(nv, v0 + 64);
+                ent.open();
+                for (int64_t e = M.nptr[v0]; e < M.nptr[v1]; ++e) ent.take(M.nidx[e]);
+                ent.number();
+                for (int64_t v = v0; v < v1; ++v)
+                    for (int64_t k = 0; k < M.nptr[v + 1] - M.nptr[v]; ++k)
+                        M.nl_idx[M.node.off[s] + k * 64 + (v & 63)] = (uint16_t)ent[M.nidx[M.nptr[v] + k]];
+                halos[chunk].insert(halos[chunk].end(), ent.list.begin(), ent.list.end());
+                M.nh_off[s + 1] = (int64_t)ent.list.size();
+            }
+        });
+        M.nh_max = join_lists(M.nh_off, halos, M.nh_idx);
         if (M.nh_max > 65536) {
             M.nh_max = 0;
             M.nh_off.clear();
