@@ -378,8 +378,9 @@ int mifvm_fgmres_attach(mifvm_state* st, int32_t m, void* d_ws, size_t ws_bytes)
 
 /* ---- captured replays and the autotuner -----------------------------------
  * mifvm_step_graph: as mifvm_step, but the n_steps x 3 stages are captured
- * once into hipGraphs (per n_steps; the calls that capture launch directly)
- * and replayed on `stream`, whatever dt; a kind that mifvm_set_bc changes
+ * once into hipGraphs (per n_steps; the calls that capture launch directly,
+ * as do calls on a stream the caller captures) and replayed on `stream`,
+ * whatever dt; a kind that mifvm_set_bc changes
  * drops every captured graph.
  * mifvm_autotune: times the CG schedule (chunk 8/16/32/64, direct launches
  * or graph replay) on short solves of the current system (f = U; P is

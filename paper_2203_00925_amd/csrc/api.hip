@@ -717,6 +717,15 @@ hipError_t enqueue_stages(State& s, bool timing, hipStream_t q) {
     return e;
 }
 
+// Whether the caller captures the stream: a graph launched on it then would
+// run at once and not be part of what is captured.
+bool caller_captures(hipStream_t hs) {
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(hs, &cap) == hipSuccess) return cap != hipStreamCaptureStatusNone;
+    (void)hipGetLastError();
+    return true;
+}
+
 // How many of a call's steps replay their stages as a graph.  All of them to
 // 96k cells: nine kernels launched one by one cost the host, or the gaps between
 // them, more than their work (a step and a wait, FP64: 3k cells launched 84.6
@@ -734,11 +743,7 @@ int steps_replayed(State& s, int n_steps, hipStream_t hs) {
     s.waited = false;
     const int n = s.d.nc <= kReplayCells ? n_steps : waited && s.d.nc <= kReplayWaited ? 1 : 0;
     if (n == 0 || s.timer.on || (s.step_calls++ == 0 && n < kLongCall)) return 0;
-    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(hs, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) {
-        (void)hipGetLastError();
-        return 0;
-    }
+    if (caller_captures(hs)) return 0;
     if (!s.stage_exec &&
         capture_graph(s, &s.stage_exec, [&](hipStream_t q) { return enqueue_stages(s, false, q); }) != hipSuccess) {
         (void)hipGetLastError();
@@ -793,7 +798,12 @@ int mifvm_step_graph(mifvm_state* st, int32_t n_steps, double dt, void* stream) 
     // memory, and serves every other dt behind a launch of its own.  Neither is
     // captured before its work is launched: the host captures while that runs.
     // 3,072 cells, ten steps: dt repeated 410 us, new in every call 424, new
-    // and captured into the graph each time 669.
+    // and captured into the graph each time 669.  A caller's own capture takes
+    // the launches.
+    if (caller_captures(hs)) {
+        HIPCHK(enqueue_steps(s, n_steps, dt, hs));
+        return MIFVM_OK;
+    }
     const double cfl = dt > 0.0 ? 0.0 : s.cfl;
     const bool repeated = dt == s.step_dt && cfl == s.step_cfl;
     s.step_dt = dt;

@@ -160,6 +160,29 @@ def test_captured_steps_serve_every_time_step(precision):
     assert within(1.2, new, lambda: a.step_graph(10, 1e-6))
 
 
+@pytest.mark.parametrize("calls", [0, 1, 2])
+def test_captured_steps_inside_the_callers_capture(calls):
+    """A caller captures step_graph before its graphs are there, and after: each
+    replay steps (a graph launched in the capture ran at once, and not again)."""
+    (a, _), (b, _) = state(), state()
+    for _ in range(calls):
+        a.step_graph(2, 1e-5)
+        b.step(2, 1e-5)
+    s, g = torch.cuda.Stream(), torch.cuda.CUDAGraph()
+    s.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.graph(g, stream=s):
+        a.step_graph(2, 1e-5, stream=s)
+    for _ in range(3):
+        g.replay()
+        torch.cuda.synchronize()
+        b.step(2, 1e-5)
+        assert a.conservation() == b.conservation()
+        assert torch.equal(a.get_field(B.FIELD_U), b.get_field(B.FIELD_U))
+    a.step_graph(2, 1e-5)                  # and its own replays go on
+    b.step(2, 1e-5)
+    assert torch.equal(a.get_field(B.FIELD_U), b.get_field(B.FIELD_U))
+
+
 def test_boundary_values_keep_the_captured_graphs():
     """Ramping a wall's value by set_bc, and assembling a matrix again, costs no
     capture: a solve that replays chunks of 512 iterations, ramped by set_bc or
